@@ -10,23 +10,20 @@
 //                   the read-back V) and the force gather; k_grid_step_wave
 //                   is the same in one wavefront when forces go through the
 //                   table in kernel-argument form.
-//   k_grid_add      one workgroup per grid: the hills the step appended
-//                   (FP64, list order) added to every node, then the list's
-//                   count advanced; the workgroup of grid 0 also advances
-//                   the device step counter.  With rebuild set, many
-//                   workgroups per grid refill it from the whole list.
+//   k_grid_tiles, k_grid_line
+//                   the hills the step appended, or a whole list (rebuild),
+//                   onto every node; after a step the list's count and the
+//                   device step counter advance.
 //   k_grid_eval     the read-back at arbitrary points.
 //
-// Node sums run in FP64 in the order the hills sit in the list, so a grid
-// holds the exact hill sum at its nodes up to the rounding of exp.
+// Node sums run in FP64 in a fixed order, so a grid holds the exact hill sum
+// at its nodes up to the rounding of its factors.
 #include "sx_internal.h"
 #include "dev_cv.h"
 #include "dev_gather.h"
 
 namespace sx {
 namespace {
-
-constexpr int kAddBlock = 1024;
 
 // The cell of xi: lower and upper node per CV and the fractions t; false
 // outside the range of a non-periodic CV (its nodes are then set to 0).
@@ -316,65 +313,309 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
     }
 }
 
-// hills [k0, k1) of list l onto nodes [first, N) of its grid, node stride
-// `stride`; rebuild: the nodes start from zero
-__device__ void add_hills(const GridArgs &g, int32_t l, int32_t k0, int32_t k1, bool rebuild, int64_t first,
-                          int64_t stride)
+// ---------------------------------------------------- hills onto the nodes
+// A hill's Gaussian is a product of one factor per CV, so over a block of
+// nodes the sums over hills are matrix products.  With the nodes' last CV as
+// columns and the CVs before it as rows, and per hill k
+//   L0(r) = h_k prod_{d < D-1} e_d,  R0(c) = e_{D-1},  e_d = exp(-u_d^2/2s_d^2),
+//   g_d = -u_d / s_d^2,  u_d = node - centre (minimum image),
+//   V += sum_k L0 R0,  G_d += sum_k (L0 g_d) R0 (d < D-1),  G_{D-1} += sum_k L0 (R0 g_{D-1}).
+//
+// k_grid_tiles (D >= 2): a workgroup owns a tile of 32 x 32 nodes; KG groups
+// of four wavefronts take 16 hills at a time, form the tile's 32 row and 32
+// column factors in LDS (64 exponentials for 1024 nodes) and multiply them
+// with v_mfma_f64_16x16x4_f64, each wavefront a 16 x 16 block of the 1 + D
+// sums; the groups' sums are joined in group order and added to the nodes, so
+// a grid's bits do not depend on the schedule.  FP64 multiply-adds bound it
+// (1 + D per (node, hill), 39 T/s), with the factors' exponentials (about 40
+// operations each, 1/16 per (node, hill)) on the vector units beside them.
+// KG = 4 fills the chip when a whole list is summed (the 256 tiles of
+// 512 x 512 nodes, 16 wavefronts a CU).  A step's few hills take KG = 1: less
+// to launch on the many steps that deposit nothing.
+// 100,000 hills onto 512 x 512 nodes: 4.85 ms (one exponential and two
+// divisions per (node, hill) and one lane per node: 121 ms).  256 hills: 25 us
+// (one workgroup for the whole grid: 76.8 ms).
+//
+// k_grid_line (D = 1): no product to share, one exponential per (node, hill);
+// a wavefront per 64 nodes and hill slice, 16 slices joined in order.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kTileSide = 32;   // nodes of a tile per side
+constexpr int kTileHills = 16;  // hills per stage of a group
+// LDS row stride (doubles): the four hills of a fragment start 32 banks apart
+constexpr int kTileLd = 48;
+constexpr int kLineSlices = 16;
+
+// 2^y for y <= 0 in FP64: y = n + f, |f| <= 1/2, and the Taylor series of
+// exp(f ln 2) to degree 13 (remainder below 5e-18), scaled by 2^n.  About
+// half the operations of exp(), whose other half serves arguments that do
+// not occur here; below 2^-1100 (and for y = -inf) the scaling gives 0, NaN
+// stays NaN.
+__device__ __forceinline__ double exp2_neg(double y)
 {
+    const double yc = y < -1100.0 ? -1100.0 : y;
+    const double n = rint(yc), f = yc - n;
+    double p = 1.3691488853904128880892e-12;  // ln2^13 / 13!, then down to ln2^0 / 0!
+    p = fma(p, f, 2.5678435993488205141995e-11);
+    p = fma(p, f, 4.4455382718708114975964e-10);
+    p = fma(p, f, 7.0549116208011233298754e-9);
+    p = fma(p, f, 1.0178086009239699727491e-7);
+    p = fma(p, f, 1.3215486790144309488404e-6);
+    p = fma(p, f, 1.5252733804059840280026e-5);
+    p = fma(p, f, 1.5403530393381609954437e-4);
+    p = fma(p, f, 1.3333558146428443423412e-3);
+    p = fma(p, f, 9.6181291076284771619791e-3);
+    p = fma(p, f, 5.5504108664821579953142e-2);
+    p = fma(p, f, 2.4022650695910071233355e-1);
+    p = fma(p, f, 6.9314718055994530941723e-1);
+    p = fma(p, f, 1.0);
+    return ldexp(p, (int)n);
+}
+
+// The factor e of CV d at displacement x - c, and g = -u / sigma^2.  The
+// image is that of rint(u / period): where the product with the reciprocal is
+// too near half a period to tell, the quotient decides.
+__device__ __forceinline__ void axis_factor(const GridArgs &g, int d, double x, double c, double &e, double &gd)
+{
+    double u = x - c;
+    if (g.period[d] > 0.0) {
+        double v = fma(-g.period[d], rint(u * g.inv_period[d]), u);
+        if (__builtin_expect(fabs(v) > 0.499999999 * g.period[d], 0)) v = fma(-g.period[d], rint(u / g.period[d]), u);
+        u = v;
+    }
+    e = exp2_neg(-(u * u) * (0.72134752044448170368 * g.inv_sig2[d]));  // log2(e) / 2
+    gd = -u * g.inv_sig2[d];
+}
+
+// After k_grid_step: the hills [k0, k1) a launch puts on grid l -- a rebuild
+// its whole list, a step the `pend` hills behind the count (none on most
+// steps).
+template <bool REBUILD>
+__device__ __forceinline__ void hill_range(const GridArgs &g, int32_t l, int32_t &k0, int32_t &k1)
+{
+    const int32_t cnt = g.count[l];
+    k0 = REBUILD ? 0 : cnt;
+    k1 = REBUILD ? cnt : cnt + g.pend[l];
+}
+
+// The end of a step's launch on grid l: the last of the list's workgroups to
+// arrive moves the count past the new hills.  Every workgroup has then read
+// count and pend (its ticket follows its use of them), and nothing it wrote
+// is read before the next launch, so the ticket orders no other memory.
+__device__ __forceinline__ void finish_add(const GridArgs &g, int32_t l, int32_t k1, int32_t per)
+{
+    if (threadIdx.x != 0) return;
+    if (atomicAdd(&g.tick[l], 1) != per - 1) return;
+    g.count[l] = k1;
+    g.pend[l] = 0;
+    g.tick[l] = 0;
+}
+
+// the step counter moves here (nothing else of the launch reads it)
+__device__ __forceinline__ void advance_step(const GridArgs &g)
+{
+    if (g.count_step && blockIdx.x == 0 && threadIdx.x == 0)
+        *g.dstep = g.step >= 0 ? g.step + 1 : *g.dstep + 1;
+}
+
+template <int D, int KG, bool REBUILD>
+__global__ void __launch_bounds__(256 * KG) k_grid_tiles(GridArgs g, int32_t l0, int32_t per)
+{
+    __shared__ double s_f[KG][D + 2][kTileHills][kTileLd];  // L0, L0 g_0 .., then R0, R0 g_last
+    if (!REBUILD) advance_step(g);
+    const int32_t l = l0 + (int32_t)blockIdx.x / per, wg = (int32_t)blockIdx.x % per;  // per workgroups a grid
+    int32_t k0, k1;
+    hill_range<REBUILD>(g, l, k0, k1);
+    if (!REBUILD && k1 == k0) return;  // uniform
+    const int grp = threadIdx.x >> 8, t = threadIdx.x & 255;
+    const int lane = t & 63, wr = (t >> 7) & 1, wc = (t >> 6) & 1;  // this wavefront's 16 x 16 block
+    const int64_t nc = g.n[D - 1], nr = g.N / nc;
+    const int64_t tc = (nc + kTileSide - 1) / kTileSide, tiles = tc * ((nr + kTileSide - 1) / kTileSide);
     const int64_t hb = (int64_t)g.wrec[l].hb4 * 4;
     double *Vg = g.V + (int64_t)l * g.N;
-    double *Gg = g.G + (int64_t)l * g.D * g.N;
-    for (int64_t node = first; node < g.N; node += stride) {
-        double x[kMaxBiasDim];
-        int64_t r = node;
-        for (int d = g.D - 1; d >= 0; --d) {
-            const int64_t i = r % g.n[d];
-            r /= g.n[d];
-            x[d] = g.lo[d] + (double)i * g.delta[d];
-        }
-        double v = rebuild ? 0.0 : Vg[node];
-        double gd[kMaxBiasDim];
-        for (int d = 0; d < g.D; ++d) gd[d] = rebuild ? 0.0 : Gg[(int64_t)d * g.N + node];
-        for (int32_t j = k0; j < k1; ++j) {
-            double q = 0.0, dl[kMaxBiasDim];
-            for (int d = 0; d < g.D; ++d) {
-                double u = x[d] - (double)g.c[d][hb + j];
-                if (g.period[d] > 0.0) u -= g.period[d] * rint(u / g.period[d]);
-                dl[d] = u;
-                q += u * u * (0.5 * g.inv_sig2[d]);
+    double *Gg = g.G + (int64_t)l * D * g.N;
+    const int fh = t >> 4, fq = t & 15;  // factors: hill fh of the stage, rows and columns fq, fq + 16
+    for (int64_t tile = wg; tile < tiles; tile += per) {
+        const int64_t r0 = tile / tc * kTileSide, c0 = tile % tc * kTileSide;
+        double xr[2][D - 1], xc[2];
+        bool okr[2], okc[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            int64_t r = r0 + fq + 16 * q;
+            okr[q] = r < nr;
+#pragma unroll
+            for (int d = D - 2; d >= 0; --d) {
+                xr[q][d] = g.lo[d] + (double)(r % g.n[d]) * g.delta[d];
+                r /= g.n[d];
             }
-            const double e = (double)g.h[hb + j] * exp(-q);
+            const int64_t c = c0 + fq + 16 * q;
+            okc[q] = c < nc;
+            xc[q] = g.lo[D - 1] + (double)c * g.delta[D - 1];
+        }
+        f64x4 acc[1 + D];  // V, G_0 .. G_{D-1}
+#pragma unroll
+        for (int q = 0; q <= D; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+        // the group's next hill of this lane, requested a stage ahead
+        float hc[D], hh = 0.f;
+        auto request = [&](int32_t k) {
+            const int64_t at = hb + (k < k1 ? k : k0);
+#pragma unroll
+            for (int d = 0; d < D; ++d) hc[d] = g.c[d][at];
+            hh = g.h[at];
+        };
+        // the factors of the group's stage at hill kb.  A hill past the range
+        // takes zero height on the first hill's centre; rows and columns past
+        // the grid are formed and not stored.
+        auto factors = [&](int32_t kb) {
+            const double h = kb + fh < k1 ? (double)hh : 0.0;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                double L = h, gd[D - 1], e, gl;
+#pragma unroll
+                for (int d = 0; d < D - 1; ++d) {
+                    axis_factor(g, d, xr[q][d], (double)hc[d], e, gd[d]);
+                    L *= e;
+                }
+                s_f[grp][0][fh][fq + 16 * q] = L;
+#pragma unroll
+                for (int d = 0; d < D - 1; ++d) s_f[grp][1 + d][fh][fq + 16 * q] = L * gd[d];
+                axis_factor(g, D - 1, xc[q], (double)hc[D - 1], e, gl);
+                s_f[grp][D][fh][fq + 16 * q] = e;
+                s_f[grp][D + 1][fh][fq + 16 * q] = e * gl;
+            }
+            request(kb + KG * kTileHills + fh);
+        };
+        auto products = [&]() {
+#pragma unroll
+            for (int ks = 0; ks < kTileHills / 4; ++ks) {
+                const int kk = 4 * ks + (lane >> 4), a = 16 * wr + (lane & 15), b = 16 * wc + (lane & 15);
+                const double l0v = s_f[grp][0][kk][a], e0 = s_f[grp][D][kk][b];
+                acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(l0v, e0, acc[0], 0, 0, 0);
+#pragma unroll
+                for (int d = 0; d < D - 1; ++d)
+                    acc[1 + d] = __builtin_amdgcn_mfma_f64_16x16x4f64(s_f[grp][1 + d][kk][a], e0, acc[1 + d], 0, 0, 0);
+                acc[D] = __builtin_amdgcn_mfma_f64_16x16x4f64(l0v, s_f[grp][D + 1][kk][b], acc[D], 0, 0, 0);
+            }
+        };
+        // Even groups form factors while odd groups multiply, then the other
+        // way round: every SIMD holds a wavefront of each group, so its
+        // matrix and vector units work at the same time.
+        const int32_t stages = (k1 - k0 + KG * kTileHills - 1) / (KG * kTileHills);
+        const int32_t kg0 = k0 + grp * kTileHills;
+        const bool odd = grp & 1;
+        if (stages > 0) request(kg0 + fh);
+        for (int32_t i = 0; i < stages + (KG > 1 ? 1 : 0); ++i) {
+            if (odd) {
+                if (i > 0) products();
+            } else if (i < stages) {
+                factors(kg0 + i * KG * kTileHills);
+            }
+            __syncthreads();
+            if (i < stages) {
+                if (odd)
+                    factors(kg0 + i * KG * kTileHills);
+                else
+                    products();
+            }
+            __syncthreads();
+        }
+        if (KG > 1) {  // join the groups' sums, group after group
+            double *red = &s_f[0][0][0][0];  // (KG - 1) x (1 + D) x 1024 doubles
+            static_assert((KG - 1) * (1 + D) * 1024 <= KG * (D + 2) * kTileHills * kTileLd, "LDS reuse");
+            if (grp > 0) {
+#pragma unroll
+                for (int q = 0; q <= D; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) red[(((grp - 1) * (1 + D) + q) * 4 + v) * 256 + t] = acc[q][v];
+            }
+            __syncthreads();
+            if (grp == 0) {
+#pragma unroll
+                for (int o = 0; o < KG - 1; ++o)
+#pragma unroll
+                    for (int q = 0; q <= D; ++q)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[q][v] += red[((o * (1 + D) + q) * 4 + v) * 256 + t];
+            }
+        }
+        if (grp == 0) {
+            // lane: column lane % 16, rows lane / 16 + 4 v of its block
+            const int64_t c = c0 + 16 * wc + (lane & 15);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t r = r0 + 16 * wr + (lane >> 4) + 4 * v;
+                if (r >= nr || c >= nc) continue;
+                const int64_t node = r * nc + c;
+                Vg[node] = REBUILD ? acc[0][v] : Vg[node] + acc[0][v];
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    double *p = Gg + (int64_t)d * g.N + node;
+                    *p = REBUILD ? acc[1 + d][v] : *p + acc[1 + d][v];
+                }
+            }
+        }
+        __syncthreads();  // s_f is free for the next tile
+    }
+    if (!REBUILD) finish_add(g, l, k1, per);
+}
+
+template <bool REBUILD>
+__global__ void __launch_bounds__(64 * kLineSlices) k_grid_line(GridArgs g, int32_t l0, int32_t per)
+{
+    __shared__ double s_r[kLineSlices][2][64];
+    if (!REBUILD) advance_step(g);
+    const int32_t l = l0 + (int32_t)blockIdx.x / per, wg = (int32_t)blockIdx.x % per;  // per workgroups a grid
+    int32_t k0, k1;
+    hill_range<REBUILD>(g, l, k0, k1);
+    if (!REBUILD && k1 == k0) return;  // uniform
+    const int lane = threadIdx.x & 63, slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t hb = (int64_t)g.wrec[l].hb4 * 4;
+    double *Vg = g.V + (int64_t)l * g.N, *Gg = g.G + (int64_t)l * g.N;
+    for (int64_t n0 = (int64_t)wg * 64; n0 < g.N; n0 += (int64_t)per * 64) {
+        const int64_t node = n0 + lane;
+        const double x = g.lo[0] + (double)node * g.delta[0];
+        double v = 0.0, gr = 0.0;
+        for (int32_t k = k0 + slice; k < k1; k += kLineSlices) {
+            double e, gd;
+            axis_factor(g, 0, x, (double)g.c[0][hb + k], e, gd);
+            e *= (double)g.h[hb + k];
             v += e;
-            for (int d = 0; d < g.D; ++d) gd[d] -= e * dl[d] * g.inv_sig2[d];
+            gr = fma(e, gd, gr);
         }
-        Vg[node] = v;
-        for (int d = 0; d < g.D; ++d) Gg[(int64_t)d * g.N + node] = gd[d];
+        s_r[slice][0][lane] = v;
+        s_r[slice][1][lane] = gr;
+        __syncthreads();
+        if (slice == 0 && node < g.N) {
+            for (int q = 1; q < kLineSlices; ++q) {
+                v += s_r[q][0][lane];
+                gr += s_r[q][1][lane];
+            }
+            Vg[node] = REBUILD ? v : Vg[node] + v;
+            Gg[node] = REBUILD ? gr : Gg[node] + gr;
+        }
+        __syncthreads();  // s_r is free for the next nodes
     }
+    if (!REBUILD) finish_add(g, l, k1, per);
 }
 
-// After k_grid_step: one workgroup per grid (gridDim.x = L).
-__global__ void __launch_bounds__(kAddBlock) k_grid_add(GridArgs g)
+// Grids l0 .. l0 + nl - 1: one workgroup per tile (D = 1: per 64 nodes), at
+// most `most` a grid.
+template <bool REBUILD>
+hipError_t launch_hills_on_grid(const GridArgs &g, int32_t l0, int32_t nl, int64_t most, hipStream_t s)
 {
-    const int32_t l = blockIdx.x;
-    const int32_t k0 = g.count[l], nnew = g.pend[l];
-    if (nnew > 0) add_hills(g, l, k0, k0 + nnew, false, threadIdx.x, kAddBlock);
-    __syncthreads();  // every node has read the window before it moves
-    if (threadIdx.x == 0) {
-        if (nnew > 0) {
-            g.count[l] = k0 + nnew;
-            g.pend[l] = 0;
-        }
-        if (l == 0 && g.count_step) *g.dstep = g.step >= 0 ? g.step + 1 : *g.dstep + 1;
+    constexpr int KG = REBUILD ? 4 : 1;
+    const int64_t nc = g.n[g.D - 1], nr = g.N / nc;
+    const int64_t tiles = g.D == 1 ? (g.N + 63) / 64
+                                   : ((nc + kTileSide - 1) / kTileSide) * ((nr + kTileSide - 1) / kTileSide);
+    const int32_t per = (int32_t)std::max<int64_t>(1, std::min<int64_t>(tiles, most));
+    if ((int64_t)per * nl > INT32_MAX) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)per * (unsigned)nl);
+    switch (g.D) {
+    case 1: hipLaunchKernelGGL(k_grid_line<REBUILD>, grid, dim3(64 * kLineSlices), 0, s, g, l0, per); break;
+    case 2: hipLaunchKernelGGL((k_grid_tiles<2, KG, REBUILD>), grid, dim3(256 * KG), 0, s, g, l0, per); break;
+    case 3: hipLaunchKernelGGL((k_grid_tiles<3, KG, REBUILD>), grid, dim3(256 * KG), 0, s, g, l0, per); break;
+    default: return hipErrorInvalidValue;
     }
-}
-
-// Rebuild grids l0 + blockIdx.x from their whole lists; the gridDim.y
-// workgroups of a grid split its nodes.
-__global__ void __launch_bounds__(kAddBlock) k_grid_rebuild(GridArgs g, int32_t l0)
-{
-    const int32_t l = l0 + blockIdx.x;
-    add_hills(g, l, 0, g.count[l], true, (int64_t)blockIdx.y * kAddBlock + threadIdx.x,
-              (int64_t)gridDim.y * kAddBlock);
+    return hipGetLastError();
 }
 
 __global__ void __launch_bounds__(kBlock) k_grid_eval(GridArgs g, int32_t l, const double *xi, int64_t n, double *V,
@@ -421,16 +662,15 @@ hipError_t launch_grid_step(const GridArgs &g0, hipStream_t s)
         hipLaunchKernelGGL(k_grid_step, dim3(g.tabs.W), dim3(kBlock), 0, s, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !add) return e;
-    hipLaunchKernelGGL(k_grid_add, dim3(g.L), dim3(kAddBlock), 0, s, g);
-    return hipGetLastError();
+    // about 1024 workgroups in all: on a step that deposits nothing each of
+    // them only reads its list's count of new hills
+    return launch_hills_on_grid<false>(g, 0, g.L, (1024 + g.L - 1) / g.L, s);
 }
 
 hipError_t launch_grid_rebuild(const GridArgs &g, int32_t l0, int32_t nl, hipStream_t s)
 {
     if (nl < 1 || l0 < 0 || l0 + nl > g.L) return hipErrorInvalidValue;
-    const int64_t nb = std::min<int64_t>((g.N + kAddBlock - 1) / kAddBlock, 1024);
-    hipLaunchKernelGGL(k_grid_rebuild, dim3(nl, (unsigned)nb), dim3(kAddBlock), 0, s, g, l0);
-    return hipGetLastError();
+    return launch_hills_on_grid<true>(g, l0, nl, 4096, s);
 }
 
 hipError_t launch_grid_eval(const GridArgs &g, int32_t l, const double *xi, int64_t n, double *V, double *dV,

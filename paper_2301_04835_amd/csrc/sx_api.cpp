@@ -71,7 +71,7 @@ struct Plan {
     int32_t mg_L = 0, mg_n[kMaxBiasDim] = {0, 0, 0};
     Sub s_mgV, s_mgG, s_mgPend;
     // harmonic windows: sample counts and sums (state), centres (workspace)
-    Sub s_umN, s_umS1, s_umS2, w_hbXi0;
+    Sub s_umN, s_umS1, s_umS2, w_hbXi0, w_mgTick;
     // ABF momentum estimator: previous W p, bias and flag per walker (state),
     // inverse masses per atom (workspace)
     Sub s_abfWp, s_abfB, s_abfHas, w_invm;
@@ -561,6 +561,7 @@ sx_status make_plan(sx_ctx *c)
     p.w_tiles = lw.take(sizeof(TileRec) * p.ntiles_max);
     p.w_wrec = lw.take(sizeof(WalkerRec) * p.W);
     p.w_hbXi0 = lw.take(c->method == M_HARMONIC ? sizeof(double) * p.W * p.D : 0);
+    p.w_mgTick = lw.take(c->mg_on ? sizeof(int32_t) * p.mg_L : 0);
     p.w_invm = lw.take(c->abf_est == 1 ? sizeof(double) * p.total_atoms : 0);
     p.w_slot_atom = lw.take(sizeof(int32_t) * p.nslots);
     p.w_slot_cv = lw.take(sizeof(int32_t) * p.nslots);
@@ -864,12 +865,14 @@ GridArgs grid_args(sx_ctx *c, const double *xi)
         g.lo[d] = c->mg_lo[d];
         g.delta[d] = (c->mg_hi[d] - c->mg_lo[d]) / c->mg_nbins[d];
         g.period[d] = per ? kTwoPi : 0.0;
+        g.inv_period[d] = per ? 1.0 / kTwoPi : 0.0;
         g.inv_sig2[d] = 1.0 / (c->sigma[d] * c->sigma[d]);
     }
     g.N = p.mg_N;
     g.V = at<double>(c->state, p.s_mgV);
     g.G = at<double>(c->state, p.s_mgG);
     g.pend = at<int32_t>(c->state, p.s_mgPend);
+    g.tick = at<int32_t>(c->ws, p.w_mgTick);
     for (int d = 0; d < kMaxBiasDim; ++d) g.c[d] = d < p.D ? at<float>(c->state, p.s_c[d]) : nullptr;
     g.h = at<float>(c->state, p.s_h);
     g.count = at<int32_t>(c->state, p.s_count);

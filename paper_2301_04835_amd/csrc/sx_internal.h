@@ -210,10 +210,11 @@ struct GridArgs {
     int32_t D, L, shared;                 // CVs, hill lists (grids), one list for all walkers
     int32_t nbins[kMaxBiasDim], n[kMaxBiasDim], per[kMaxBiasDim];  // bins, nodes, periodic
     double lo[kMaxBiasDim], delta[kMaxBiasDim];
-    double period[kMaxBiasDim], inv_sig2[kMaxBiasDim];
+    double period[kMaxBiasDim], inv_period[kMaxBiasDim], inv_sig2[kMaxBiasDim];
     int64_t N;                            // nodes per grid
     double *V, *G;                        // L x N, L x D x N
     int32_t *pend;                        // L: hills appended by the step, not yet on the grid
+    int32_t *tick;                        // L: workgroups done adding them (zero between launches)
     // hill lists: list l starts at wrec[l].hb4 * 4, holds wrec[l].cap
     float *c[kMaxBiasDim];
     float *h;
