@@ -15,17 +15,19 @@
 //               against W2 in bf16, FP32 accumulation, so 2 (1 + D) products
 //               share every W2 fragment.  y and dy/dxi are reduced across
 //               the 16 output lanes of each sample with shuffles.
-//   k_mlp_bwd   (training): reverse mode over the forward and its tangents
-//               for a Sobolev loss on (V, dV/dxi); 16 samples per workgroup
-//               (8 at H = 128) in LDS; the two H x H products (back through
-//               W2, and the W2 gradient) on the matrix cores with bf16-pair
-//               operands, the rest on VALU; per-workgroup gradients.
-//   k_mlp_adam  sums the workgroup gradients in order (FP64) and applies
+//   k_mlp_train (training): forward and reverse mode over the forward and
+//               its tangents for a Sobolev loss on (V, dV/dxi); 16 samples
+//               per workgroup (8 at H = 128) in LDS; the three H x H products
+//               on the matrix cores with bf16-pair operands, the rest on
+//               VALU; per-workgroup gradients.
+//   k_mlp_update sums the workgroup gradients in order (FP64) and applies
 //               Adam (Kingma & Ba 2015) to the FP32 master weights, then
 //               refreshes their bf16 copies.
 #include "sx_internal.h"
 #include "dev_cv.h"
 #include "dev_gather.h"
+
+#include <cmath>
 
 namespace sx {
 namespace {
@@ -85,9 +87,8 @@ __device__ __forceinline__ void featurize(const MlpArgs &a, const double *xi, fl
 
 // ------------------------------------------------------------------ forward
 // n samples xi[n][D] (FP64).  Outputs (each may be null): V[n], dV[n][D]
-// (FP64); for training, the per-sample a2[n][H], dz2[D][n][H], y[n],
-// dy[n][D] (FP32).  Inference with a certification mask: mask != null marks
-// samples whose cell is not certified (flag[i] = 1).
+// (FP64); with a certification mask flag[i] = 1 marks the samples whose cell
+// is not certified.
 // certification flag of one sample: 1 if its cell of the cert_n^D grid is
 // not certified (or lies outside the grid)
 template <int D>
@@ -149,7 +150,6 @@ __device__ __forceinline__ double step_dihedral(const MlpStep &st, int64_t si, i
 
 template <int H, int D, bool CVF>
 __global__ void __launch_bounds__(kBlock) k_mlp_fwd(MlpArgs a, const double *xi, int64_t n, double *V, double *dV,
-                                                     float *t_a2, float *t_dz2, float *t_y, float *t_dy,
                                                      uint8_t *flag, MlpStep st, int32_t step_on)
 {
     constexpr int F = 2 * D;
@@ -285,13 +285,8 @@ __global__ void __launch_bounds__(kBlock) k_mlp_fwd(MlpArgs a, const double *xi,
             const float a2 = tanh_fast(acc[r] + b2);
             const float g = 1.f - a2 * a2;
             yp[r] = fmaf(w3, a2, yp[r]);
-            const int64_t sr = crow0 + r;
-            if (t_a2 && sr < n) t_a2[sr * H + j] = a2;
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                dyp[d][r] = fmaf(w3, g * tacc[d][r], dyp[d][r]);
-                if (t_dz2 && sr < n) t_dz2[((int64_t)d * a.nmax + sr) * H + j] = tacc[d][r];
-            }
+            for (int d = 0; d < D; ++d) dyp[d][r] = fmaf(w3, g * tacc[d][r], dyp[d][r]);
         }
     }
     // reduce over the 16 output lanes of each row group (fixed butterfly)
@@ -329,12 +324,9 @@ __global__ void __launch_bounds__(kBlock) k_mlp_fwd(MlpArgs a, const double *xi,
                 finite = finite && isfinite(dvs[d]);
             }
             if (V) V[sr] = Vs;
-            if (t_y) t_y[sr] = y;
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
+            for (int d = 0; d < D; ++d)
                 if (dV) dV[sr * D + d] = dvs[d];
-                if (t_dy) t_dy[sr * D + d] = dyp[d][r];
-            }
             if (!flag) continue;
 #pragma unroll
             for (int d = 0; d < D; ++d) xs[d] = xo[r][d];
@@ -369,8 +361,8 @@ __global__ void __launch_bounds__(kBlock) k_mlp_fwd(MlpArgs a, const double *xi,
     }
 }
 
-// ------------------------------------------------------------------ reverse
-// S samples per workgroup.  Sobolev loss
+// ----------------------------------------------------------------- training
+// Sobolev loss
 //   L = (1/B) sum_b [alpha (y_b - V_b)^2 + beta sum_d (dy_bd - G_bd)^2]
 // Gradient of the forward above: activations rounded (bf16 hi + lo) where
 // the forward rounds them, the rounding itself passed straight through,
@@ -385,7 +377,7 @@ __device__ __forceinline__ float round_bf2(float x)
 }
 
 template <int H>
-__host__ __device__ constexpr int bwd_samples()
+__host__ __device__ constexpr int train_samples()
 {
     return H >= 128 ? 8 : 16;
 }
@@ -402,227 +394,300 @@ __device__ __forceinline__ void split8(const float (&v)[8], bf16x8 &hi, bf16x8 &
     }
 }
 
-// The reverse pass: per workgroup S samples, their value row and D tangent
-// rows stacked (row c S + sl: c = 0 the value, c = d + 1 tangent d; rows
-// padded with zeros to a multiple of 32).  The two H x H products run on
-// the matrix cores (v_mfma_f32_16x16x32_bf16, FP32 accumulation), every
-// FP32 operand entering as a bf16 pair:
-//   a1b rows  = z2b rows . W2        (M = rows, K = H, N = H; W2 exact bf16,
-//                                     staged transposed in LDS)
-//   dL/dW2    = z2b rows^T . act rows (M = H, K = rows, N = H; act = the
-//                                     forward's bf16-pair activations a1r,
-//                                     da1r_d; hi.hi + hi.lo + lo.hi)
-// the rest (features, tanh derivatives, the small layers, the loss) on the
-// vector units in FP32.  Every gradient entry has one owning lane (no
-// atomics); the workgroup's partial gradient and loss go to gpart[blockIdx].
+// Forward and reverse pass of S samples in one workgroup, nothing of a
+// sample leaving it: value row and D tangent rows of every sample stacked
+// (row c S + sl: c = 0 the value, c = d + 1 tangent d; rows padded with
+// zeros to a multiple of 32) in LDS.  The three H x H products run on the
+// matrix cores (v_mfma_f32_16x16x32_bf16, FP32 accumulation), every FP32
+// operand entering as a bf16 pair:
+//   z2 rows   = act rows . W2^T       (act = the bf16-pair activations a1r,
+//                                     da1r_d; W2 exact bf16, its fragments
+//                                     held in registers from the start)
+//   a1b rows  = z2b rows . W2         (W2 staged transposed in LDS)
+//   dL/dW2    = z2b rows^T . act rows (hi.hi + hi.lo + lo.hi)
+// the rest (features, tanh and its derivatives, the small layers, the loss)
+// on the vector units in FP32.  A lane keeps one unit and S H / 512 samples
+// through every elementwise phase, so a1, a2 and the tangents stay in its
+// registers.
+//
+// A batch of 4,096 is 256 workgroups, one per CU, and a chain of barriers:
+// latency bounds it, so the workgroup has eight wavefronts (two samples per
+// lane), every weight and target is requested before the features, and the
+// products that only write to other buffers share a phase.
+// 4,096 samples at H = 64, D = 2: 11.5 us (a forward kernel of 9.5 us that
+// wrote a2 and the tangents for a reverse kernel of 13.9 us to read).
+constexpr int kTrainBlock = 512;
+
 template <int H, int D>
-__global__ void __launch_bounds__(kBlock) k_mlp_bwd(MlpArgs a, const double *xi, const double *Vl, const double *Gl,
-                                                     int64_t n, float inv_b, float alpha, float beta,
-                                                     const float *t_a2, const float *t_dz2, const float *t_y,
-                                                     const float *t_dy, float *gpart)
+__global__ void __launch_bounds__(kTrainBlock) k_mlp_train(MlpArgs a, const double *xi, const double *Vl,
+                                                            const double *Gl, int64_t n, float inv_b, float alpha,
+                                                            float beta, float *gpart)
 {
     constexpr int F = 2 * D;
-    constexpr int S = bwd_samples<H>();
+    constexpr int S = train_samples<H>();
     constexpr int R = (1 + D) * S;          // stacked rows
+    constexpr int RT = (R + 15) / 16;       // 16-row tiles that hold samples
     constexpr int MP = (R + 31) / 32 * 32;  // rows padded to the product depth
     constexpr int HP = H + 4;               // LDS row stride (floats): strided column reads spread over banks
     constexpr int HT = H + 8;               // row stride of the transposed W2 (bf16)
+    constexpr int NT = H / 16, KB = H / 32, NW = kTrainBlock / 64;
+    constexpr int IT = S * H / kTrainBlock;  // samples per lane
+    constexpr int SQ = kTrainBlock / H;      // a lane's samples are SQ apart
     constexpr POff o = poff(H, F);
-    __shared__ float s_f[S][F], s_u[S][D][F];
-    __shared__ float s_yb[S], s_dyb[S][D];
+    static_assert(S * H % kTrainBlock == 0 && kTrainBlock % H == 0 && NW % NT == 0, "whole units per lane");
+    __shared__ float s_f[S][F], s_u[S][D][2];  // features; tangent d of its own two
+    __shared__ float s_yb[S], s_dyb[S][D], s_w3[H];
     __shared__ float s_zx[MP][HP];  // z2b, dz2b_d
     __shared__ float s_ac[MP][HP];  // a1r, da1r_d (the forward's matrix-core inputs)
-    __shared__ float s_x[MP][HP];   // a2, da2_d (phase 1); a1b, da1b_d (phase 2b); z1b, dz1b_d (phase 2c)
+    __shared__ float s_x[MP][HP];   // z2, dz2_d; then a2, da2_d
+    __shared__ float s_b[MP][HP];   // a1b, da1b_d; then z1b, dz1b_d
     __shared__ __bf16 s_w2t[H][HT];  // s_w2t[k][j] = W2[j][k]
-    __shared__ float s_loss[kBlock / 64];
+    __shared__ float s_loss[NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r16 = lane & 15, kg = lane >> 4;
     const int64_t b0 = (int64_t)blockIdx.x * S;
     float *gp = gpart + (int64_t)blockIdx.x * (o.P + 1);
-    // phase 0: features and the loss adjoints of y and dy; W2 staged
-    // transposed; padding rows zeroed
-    float lossp = 0.f;
-    if (tid < S) {
-        const int64_t s = b0 + tid;
-        const bool live = s < n;
-        double x[D];
+    // requested before anything waits: this lane's unit of layers 1 and 2,
+    // this wavefront's W2 fragments, and (lanes that will form a sample's
+    // loss, 16 a sample) the targets
+    const int unit = tid % H, sl0 = tid / H;
+    float w1[F], b1 = bf(a.Pb, o.b1 + unit), b2 = bf(a.Pb, o.b2 + unit), w3 = bf(a.Pb, o.w3 + unit);
 #pragma unroll
-        for (int d = 0; d < D; ++d) x[d] = live ? xi[s * D + d] : 0.0;
-        float f[F], u[D][F];
-        featurize<D>(a, x, f, u);
+    for (int q = 0; q < F; ++q) w1[q] = bf(a.Pb, o.W1 + unit * F + q);
+    const float b3 = bf(a.Pb, o.b3);
+    bf16x8 w2[KB];
 #pragma unroll
-        for (int q = 0; q < F; ++q) {
-            s_f[tid][q] = f[q];
+    for (int kb = 0; kb < KB; ++kb)
+        w2[kb] = *reinterpret_cast<const bf16x8 *>(a.Pb + o.W2 + (wave % NT * 16 + r16) * H + kb * 32 + kg * 8);
+    const int ls = tid / 16;  // sample of the loss lanes (tid < 16 S)
+    const bool loss_lane = tid < 16 * S, loss_live = loss_lane && b0 + ls < n;
+    double tV = 0.0, tG[D];
 #pragma unroll
-            for (int d = 0; d < D; ++d) s_u[tid][d][q] = u[d][q];
-        }
-        // targets in network units: (V - out_shift) / out_scale, G / out_scale
-        const double inv_sc = 1.0 / a.out_scale;
-        const float r0 = live ? t_y[s] - (float)((Vl[s] - a.out_shift) * inv_sc) : 0.f;
-        s_yb[tid] = 2.f * alpha * r0 * inv_b;
-        lossp += alpha * r0 * r0;
+    for (int d = 0; d < D; ++d) tG[d] = 0.0;
+    if (loss_live) {
+        tV = Vl[b0 + ls];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const float r1 = live ? t_dy[s * D + d] - (float)(Gl[s * D + d] * inv_sc) : 0.f;
-            s_dyb[tid][d] = 2.f * beta * r1 * inv_b;
-            lossp += beta * r1 * r1;
-        }
+        for (int d = 0; d < D; ++d) tG[d] = Gl[(b0 + ls) * D + d];
     }
-    for (int e = tid; e < H * H; e += kBlock) {
+    // phase 0: features (one lane per sample and CV); W2 staged transposed;
+    // padding rows zeroed
+    if (tid < S * D) {
+        const int sl = tid / D, d = tid % D;
+        const double x = b0 + sl < n ? xi[(b0 + sl) * D + d] : 0.0;
+        double f0, f1, u0, u1;
+        if (a.periodic[d]) {
+            sincos(x, &f0, &f1);
+            u0 = f1;
+            u1 = -f0;
+        } else {
+            f0 = (x - a.mu[d]) * a.inv_s[d];
+            f1 = f0 * f0;
+            u0 = a.inv_s[d];
+            u1 = 2.0 * f0 * a.inv_s[d];
+        }
+        s_f[sl][2 * d] = (float)f0;
+        s_f[sl][2 * d + 1] = (float)f1;
+        s_u[sl][d][0] = (float)u0;
+        s_u[sl][d][1] = (float)u1;
+    }
+    for (int e = tid; e < H * H; e += kTrainBlock) {
         const int j = e / H, k = e % H;
         s_w2t[k][j] = reinterpret_cast<const __bf16 *>(a.Pb)[o.W2 + e];
     }
-    for (int e = tid; e < (MP - R) * H; e += kBlock) {
+    for (int e = tid; e < (MP - R) * H; e += kTrainBlock) {
         const int m = R + e / H, k = e % H;
         s_zx[m][k] = 0.f;
         s_ac[m][k] = 0.f;
     }
+    if (tid < H) s_w3[tid] = w3;
     __syncthreads();
-    // phase 1 (sample sl, output unit j): y = w3.a2 + b3, dy_d = w3.da2_d,
-    // da2_d = (1 - a2^2) dz2_d  ->  adjoints of z2 and of the tangents dz2_d
-    for (int idx = tid; idx < S * H; idx += kBlock) {
-        const int sl = idx / H, j = idx % H;
-        const int64_t s = b0 + sl;
-        const bool live = s < n;
-        const float a2 = live ? t_a2[s * H + j] : 0.f;
-        const float g2 = 1.f - a2 * a2;
-        const float w3 = bf(a.Pb, o.w3 + j);
+    // phase 1: layer 1 and its tangents; the matrix-core inputs a1r, da1r_d
+    float a1[IT], dz1[IT][D];
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        const int sl = sl0 + i * SQ;
+        float z = b1;
+#pragma unroll
+        for (int q = 0; q < F; ++q) z = fmaf(w1[q], s_f[sl][q], z);
+        a1[i] = tanh_fast(z);
+        const float g1 = 1.f - a1[i] * a1[i];
+        s_ac[sl][unit] = round_bf2(a1[i]);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            dz1[i][d] = fmaf(w1[2 * d + 1], s_u[sl][d][1], w1[2 * d] * s_u[sl][d][0]);
+            s_ac[(d + 1) * S + sl][unit] = round_bf2(g1 * dz1[i][d]);
+        }
+    }
+    __syncthreads();
+    // phase 2 (matrix cores): z2 rows = act rows . W2^T, a wavefront one
+    // 16-wide column of tiles
+    for (int rt = wave / NT; rt < RT; rt += NW / NT) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = s_ac[rt * 16 + r16][kb * 32 + kg * 8 + q];
+            bf16x8 hi, lo;
+            split8(v, hi, lo);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, w2[kb], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, w2[kb], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s_x[rt * 16 + kg * 4 + i][wave % NT * 16 + r16] = acc[i];
+    }
+    __syncthreads();
+    // phase 3: a2 and da2_d = (1 - a2^2) dz2_d
+    float a2[IT], dz2[IT][D];
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        const int sl = sl0 + i * SQ;
+        a2[i] = tanh_fast(s_x[sl][unit] + b2);
+        s_x[sl][unit] = a2[i];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            dz2[i][d] = s_x[(d + 1) * S + sl][unit];
+            s_x[(d + 1) * S + sl][unit] = (1.f - a2[i] * a2[i]) * dz2[i][d];
+        }
+    }
+    __syncthreads();
+    // phase 4: y = w3.a2 + b3, dy_d = w3.da2_d (16 lanes a sample, a fixed
+    // butterfly), the loss and its adjoints of y and dy
+    float lossp = 0.f;
+    if (loss_lane) {  // whole wavefronts
+        float y = 0.f, dy[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) dy[d] = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const float w = s_w3[nt * 16 + r16];
+            y = fmaf(w, s_x[ls][nt * 16 + r16], y);
+#pragma unroll
+            for (int d = 0; d < D; ++d) dy[d] = fmaf(w, s_x[(d + 1) * S + ls][nt * 16 + r16], dy[d]);
+        }
+        for (int m = 1; m < 16; m <<= 1) {
+            y += __shfl_xor(y, m, 64);
+#pragma unroll
+            for (int d = 0; d < D; ++d) dy[d] += __shfl_xor(dy[d], m, 64);
+        }
+        if (r16 == 0) {
+            // targets in network units: (V - out_shift) / out_scale, G / out_scale
+            const double inv_sc = 1.0 / a.out_scale;
+            const float r0 = loss_live ? y + b3 - (float)((tV - a.out_shift) * inv_sc) : 0.f;
+            s_yb[ls] = 2.f * alpha * r0 * inv_b;
+            lossp += alpha * r0 * r0;
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const float r1 = loss_live ? dy[d] - (float)(tG[d] * inv_sc) : 0.f;
+                s_dyb[ls][d] = 2.f * beta * r1 * inv_b;
+                lossp += beta * r1 * r1;
+            }
+        }
+    }
+    __syncthreads();
+    // phase 5: adjoints of z2 and of the tangents dz2_d
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        const int sl = sl0 + i * SQ;
+        const float g2 = 1.f - a2[i] * a2[i];
         float a2b = s_yb[sl] * w3;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            const float dz2 = live ? t_dz2[((int64_t)d * a.nmax + s) * H + j] : 0.f;
             const float da2b = s_dyb[sl][d] * w3;
-            a2b += da2b * (-2.f * a2 * dz2);
-            s_zx[(d + 1) * S + sl][j] = da2b * g2;
-            s_x[(d + 1) * S + sl][j] = g2 * dz2;  // da2_d
+            a2b += da2b * (-2.f * a2[i] * dz2[i][d]);
+            s_zx[(d + 1) * S + sl][unit] = da2b * g2;
         }
-        s_zx[sl][j] = a2b * g2;
-        s_x[sl][j] = a2;
+        s_zx[sl][unit] = a2b * g2;
     }
     __syncthreads();
-    // phase 1b: b2, w3, b3 gradients (lane j owns unit j)
-    for (int j = tid; j < H; j += kBlock) {
-        float gb2 = 0.f, gw3 = 0.f;
+    // phase 6: a1b rows = z2b rows . W2 and dL/dW2[j][k] = sum over rows m
+    // of s_zx[m][j] s_ac[m][k] (matrix cores, 16 x 16 tiles dealt to the
+    // wavefronts), and the b2, w3, b3 gradients (a lane per unit)
+    for (int t = wave; t < RT * NT; t += NW) {
+        const int mt = t / NT, nt = t % NT;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            const int j0 = kb * 32 + kg * 8;
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = s_zx[mt * 16 + r16][j0 + q];
+            bf16x8 hi, lo;
+            split8(v, hi, lo);
+            const bf16x8 bw = *reinterpret_cast<const bf16x8 *>(&s_w2t[nt * 16 + r16][j0]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, bw, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, bw, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s_b[mt * 16 + kg * 4 + i][nt * 16 + r16] = acc[i];
+    }
+    for (int t = wave; t < NT * NT; t += NW) {
+        const int jt = t / NT, kt = t % NT;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < MP / 32; ++kb) {
+            const int m0 = kb * 32 + kg * 8;
+            float va[8], vb[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                va[q] = s_zx[m0 + q][jt * 16 + r16];
+                vb[q] = s_ac[m0 + q][kt * 16 + r16];
+            }
+            bf16x8 ah, al, bh, bl;
+            split8(va, ah, al);
+            split8(vb, bh, bl);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gp[o.W2 + (jt * 16 + kg * 4 + i) * H + kt * 16 + r16] = acc[i];
+    }
+    if (tid < H) {
+        float gb2 = 0.f;
+        for (int sl = 0; sl < S; ++sl) gb2 += s_zx[sl][tid];
+        gp[o.b2 + tid] = gb2;
+    } else if (tid < 2 * H) {
+        const int j = tid - H;
+        float gw3 = 0.f;
         for (int sl = 0; sl < S; ++sl) {
-            gb2 += s_zx[sl][j];
             gw3 += s_yb[sl] * s_x[sl][j];
 #pragma unroll
             for (int d = 0; d < D; ++d) gw3 += s_dyb[sl][d] * s_x[(d + 1) * S + sl][j];
         }
-        gp[o.b2 + j] = gb2;
         gp[o.w3 + j] = gw3;
-    }
-    if (tid == 0) {
+    } else if (tid == 2 * H) {
         float gb3 = 0.f;
         for (int sl = 0; sl < S; ++sl) gb3 += s_yb[sl];
         gp[o.b3] = gb3;
     }
-    // phase 2a (sample sl, input unit k): layer 1 recomputed, the forward's
-    // matrix-core inputs a1r and da1r_d kept
-    for (int idx = tid; idx < S * H; idx += kBlock) {
-        const int sl = idx / H, k = idx % H;
-        float z = bf(a.Pb, o.b1 + k), dz1[D];
-#pragma unroll
-        for (int d = 0; d < D; ++d) dz1[d] = 0.f;
-#pragma unroll
-        for (int q = 0; q < F; ++q) {
-            const float w = bf(a.Pb, o.W1 + k * F + q);
-            z = fmaf(w, s_f[sl][q], z);
-#pragma unroll
-            for (int d = 0; d < D; ++d) dz1[d] = fmaf(w, s_u[sl][d][q], dz1[d]);
-        }
-        const float a1 = tanh_fast(z), g1 = 1.f - a1 * a1;
-        s_ac[sl][k] = round_bf2(a1);
-#pragma unroll
-        for (int d = 0; d < D; ++d) s_ac[(d + 1) * S + sl][k] = round_bf2(g1 * dz1[d]);
-    }
-    __syncthreads();  // phase 1b has read s_x; s_zx and s_w2t complete
-    // phase 2b (matrix cores): s_x rows = s_zx rows . W2, 16 x 16 tiles dealt
-    // to the four wavefronts
-    {
-        const int r16 = lane & 15, kg = lane >> 4;
-        for (int t = wave; t < (MP / 16) * (H / 16); t += kBlock / 64) {
-            const int mt = t / (H / 16), nt = t % (H / 16);
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kb = 0; kb < H / 32; ++kb) {
-                const int j0 = kb * 32 + kg * 8;
-                float v[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = s_zx[mt * 16 + r16][j0 + q];
-                bf16x8 hi, lo;
-                split8(v, hi, lo);
-                const bf16x8 bw = *reinterpret_cast<const bf16x8 *>(&s_w2t[nt * 16 + r16][j0]);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, bw, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, bw, acc, 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s_x[mt * 16 + kg * 4 + i][nt * 16 + r16] = acc[i];
-        }
-    }
     __syncthreads();
-    // phase 2c (sample sl, input unit k): through tanh of layer 1:
-    // a1b = a1b' + sum_d da1b_d (-2 a1 dz1_d), z1b = a1b g1, dz1b_d = da1b_d g1
-    for (int idx = tid; idx < S * H; idx += kBlock) {
-        const int sl = idx / H, k = idx % H;
-        float z = bf(a.Pb, o.b1 + k), dz1[D];
+    // phase 7: through tanh of layer 1: a1b = a1b' + sum_d da1b_d (-2 a1 dz1_d),
+    // z1b = a1b g1, dz1b_d = da1b_d g1
 #pragma unroll
-        for (int d = 0; d < D; ++d) dz1[d] = 0.f;
-#pragma unroll
-        for (int q = 0; q < F; ++q) {
-            const float w = bf(a.Pb, o.W1 + k * F + q);
-            z = fmaf(w, s_f[sl][q], z);
-#pragma unroll
-            for (int d = 0; d < D; ++d) dz1[d] = fmaf(w, s_u[sl][d][q], dz1[d]);
-        }
-        const float a1 = tanh_fast(z), g1 = 1.f - a1 * a1;
-        float a1b = s_x[sl][k];
+    for (int i = 0; i < IT; ++i) {
+        const int sl = sl0 + i * SQ;
+        const float g1 = 1.f - a1[i] * a1[i];
+        float a1b = s_b[sl][unit];
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            const float da1b = s_x[(d + 1) * S + sl][k];
-            a1b += da1b * (-2.f * a1 * dz1[d]);
-            s_x[(d + 1) * S + sl][k] = da1b * g1;
+            const float da1b = s_b[(d + 1) * S + sl][unit];
+            a1b += da1b * (-2.f * a1[i] * dz1[i][d]);
+            s_b[(d + 1) * S + sl][unit] = da1b * g1;
         }
-        s_x[sl][k] = a1b * g1;
+        s_b[sl][unit] = a1b * g1;
     }
-    // phase 3a (matrix cores): dL/dW2[j][k] = sum over rows m of
-    // s_zx[m][j] s_ac[m][k]; 16 x 16 tiles of (j, k) dealt to the wavefronts
-    {
-        const int r16 = lane & 15, kg = lane >> 4;
-        for (int t = wave; t < (H / 16) * (H / 16); t += kBlock / 64) {
-            const int jt = t / (H / 16), kt = t % (H / 16);
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kb = 0; kb < MP / 32; ++kb) {
-                const int m0 = kb * 32 + kg * 8;
-                float va[8], vb[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    va[q] = s_zx[m0 + q][jt * 16 + r16];
-                    vb[q] = s_ac[m0 + q][kt * 16 + r16];
-                }
-                bf16x8 ah, al, bh, bl;
-                split8(va, ah, al);
-                split8(vb, bh, bl);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc, 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) gp[o.W2 + (jt * 16 + kg * 4 + i) * H + kt * 16 + r16] = acc[i];
-        }
-    }
-    __syncthreads();  // phase 2c's z1b, dz1b complete
-    // phase 3b: W1 and b1 gradients (lane-owned)
-    for (int e = tid; e < H * (F + 1); e += kBlock) {
+    __syncthreads();
+    // phase 8: W1 and b1 gradients (lane-owned), loss partial (fixed order)
+    for (int e = tid; e < H * (F + 1); e += kTrainBlock) {
         const int k = e / (F + 1), q = e % (F + 1);
         float g = 0.f;
         for (int sl = 0; sl < S; ++sl) {
             if (q == F) {
-                g += s_x[sl][k];
-            } else {
-                g = fmaf(s_x[sl][k], s_f[sl][q], g);
-#pragma unroll
-                for (int d = 0; d < D; ++d) g = fmaf(s_x[(d + 1) * S + sl][k], s_u[sl][d][q], g);
+                g += s_b[sl][k];
+            } else {  // feature q depends on CV q / 2 alone
+                g = fmaf(s_b[sl][k], s_f[sl][q], g);
+                g = fmaf(s_b[(q / 2 + 1) * S + sl][k], s_u[sl][q / 2][q & 1], g);
             }
         }
         if (q == F)
@@ -630,53 +695,64 @@ __global__ void __launch_bounds__(kBlock) k_mlp_bwd(MlpArgs a, const double *xi,
         else
             gp[o.W1 + k * F + q] = g;
     }
-    // loss partial (fixed reduction order)
     for (int m = 32; m > 0; m >>= 1) lossp += __shfl_xor(lossp, m, 64);
-    if ((tid & 63) == 0) s_loss[tid >> 6] = lossp;
+    if (lane == 0) s_loss[wave] = lossp;
     __syncthreads();
     if (tid == 0) {
         float l = 0.f;
-        for (int w = 0; w < kBlock / 64; ++w) l += s_loss[w];
+        for (int w = 0; w < NW; ++w) l += s_loss[w];
         gp[o.P] = l;
     }
 }
 
-// stage 1 of the gradient sum: lane p of slice y sums the workgroup
-// partials [y * per, (y + 1) * per) of parameter p (index P: the loss) in
-// order, in FP64
-__global__ void __launch_bounds__(kBlock) k_mlp_reduce(const float *gpart, int32_t nblk, int32_t P, int32_t per,
-                                                        double *red)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > P) return;
-    const int b0 = blockIdx.y * per, b1 = min(nblk, b0 + per);
-    double g = 0.0;
-    for (int b = b0; b < b1; ++b) g += (double)gpart[(int64_t)b * (P + 1) + p];
-    red[(int64_t)blockIdx.y * (P + 1) + p] = g;
-}
+// The ordered FP64 sum of the workgroup gradients (index P: the loss) and
+// Adam on the FP32 master values: a workgroup takes 32 parameters, 16 lanes
+// each sum a slice of the workgroups' records in order, the slices are added
+// in order, and one lane per parameter updates it and its bf16 copy.  bc1,
+// bc2: 1 - beta^t of Adam's bias correction (formed once on the host: two
+// pow() per parameter took half of a separate update kernel's 6.8 us).  32
+// parameters a workgroup keep 128-byte reads and give 143 workgroups at
+// H = 64; one launch for the sum and the update: 3.8 us (5.7 + 6.8 us).
+constexpr int kUpdParams = 32, kUpdSlices = 16;
 
-// stage 2, one lane per parameter: the slices in order, Adam on the FP32
-// master value, refresh of its bf16 copy; lane P writes the loss sum.
-__global__ void __launch_bounds__(kBlock) k_mlp_adam(MlpArgs a, const double *red, int32_t ns, int32_t P, int64_t t,
-                                                      float lr, double *loss_out, int32_t update, double *gsum)
+__global__ void __launch_bounds__(kUpdParams * kUpdSlices) k_mlp_update(MlpArgs a, const float *gpart, int32_t nblk,
+                                                                         int32_t P, double bc1, double bc2, float lr,
+                                                                         double *loss_out, int32_t update,
+                                                                         double *gsum)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > P) return;
+    __shared__ double s_g[kUpdSlices][kUpdParams];
+    const int q = threadIdx.x % kUpdParams, y = threadIdx.x / kUpdParams;
+    const int p = blockIdx.x * kUpdParams + q;
+    const bool live = p <= P;
+    float m0 = 0.f, v0 = 0.f, w0 = 0.f;
+    if (update && y == 0 && p < P) {
+        m0 = a.m[p];
+        v0 = a.v[p];
+        w0 = a.P32[p];
+    }
+    const int per = (nblk + kUpdSlices - 1) / kUpdSlices;
+    const int b1 = min(nblk, (y + 1) * per);
+    const float *gq = gpart + (live ? p : 0);
     double g = 0.0;
-    for (int y = 0; y < ns; ++y) g += red[(int64_t)y * (P + 1) + p];
+#pragma unroll 8
+    for (int b = y * per; b < b1; ++b) g += (double)gq[(int64_t)b * (P + 1)];
+    s_g[y][q] = g;
+    __syncthreads();
+    if (y != 0 || !live) return;
+    for (int k = 1; k < kUpdSlices; ++k) g += s_g[k][q];
     if (gsum) gsum[p] = g;
     if (p == P) {
         if (loss_out) *loss_out = g;  // sum of per-sample losses
         return;
     }
     if (!update) return;
-    const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
-    const double m = b1 * a.m[p] + (1.0 - b1) * g;
-    const double v = b2 * a.v[p] + (1.0 - b2) * g * g;
+    const double be1 = 0.9, be2 = 0.999, eps = 1e-8;
+    const double m = be1 * m0 + (1.0 - be1) * g;
+    const double v = be2 * v0 + (1.0 - be2) * g * g;
     a.m[p] = (float)m;
     a.v[p] = (float)v;
-    const double mh = m / (1.0 - pow(b1, (double)t)), vh = v / (1.0 - pow(b2, (double)t));
-    const float w = (float)((double)a.P32[p] - (double)lr * mh / (sqrt(vh) + eps));
+    const double mh = m / bc1, vh = v / bc2;
+    const float w = (float)((double)w0 - (double)lr * mh / (sqrt(vh) + eps));
     a.P32[p] = w;
     reinterpret_cast<__bf16 *>(a.Pw)[p] = (__bf16)w;
 }
@@ -689,8 +765,8 @@ __global__ void k_mlp_round(MlpArgs a, int32_t P)
 }
 
 template <int H, int D>
-hipError_t mlp_fwd_hd(const MlpArgs &a, const double *xi, int64_t n, double *V, double *dV, float *t_a2, float *t_dz2,
-                      float *t_y, float *t_dy, uint8_t *flag, hipStream_t s, const MlpStep *step)
+hipError_t mlp_fwd_hd(const MlpArgs &a, const double *xi, int64_t n, double *V, double *dV, uint8_t *flag,
+                      hipStream_t s, const MlpStep *step)
 {
     // one wavefront per 16 samples; single-wavefront workgroups spread a
     // small batch over as many CUs as it has wavefronts
@@ -701,30 +777,31 @@ hipError_t mlp_fwd_hd(const MlpArgs &a, const double *xi, int64_t n, double *V, 
     MlpStep st{};
     if (step) st = *step;
     if (step && step->fuse_cv)
-        hipLaunchKernelGGL((k_mlp_fwd<H, D, true>), dim3(blocks), dim3(64 * per), 0, s, a, xi, n, V, dV, t_a2, t_dz2,
-                           t_y, t_dy, flag, st, 1);
+        hipLaunchKernelGGL((k_mlp_fwd<H, D, true>), dim3(blocks), dim3(64 * per), 0, s, a, xi, n, V, dV, flag, st,
+                           1);
     else
-        hipLaunchKernelGGL((k_mlp_fwd<H, D, false>), dim3(blocks), dim3(64 * per), 0, s, a, xi, n, V, dV, t_a2, t_dz2,
-                           t_y, t_dy, flag, st, step ? 1 : 0);
+        hipLaunchKernelGGL((k_mlp_fwd<H, D, false>), dim3(blocks), dim3(64 * per), 0, s, a, xi, n, V, dV, flag,
+                           st, step ? 1 : 0);
     return hipGetLastError();
 }
 
 template <int H, int D>
-hipError_t mlp_bwd_hd(const MlpArgs &a, const double *xi, const double *Vl, const double *Gl, int64_t n, float inv_b,
-                      float alpha, float beta, const float *t_a2, const float *t_dz2, const float *t_y,
-                      const float *t_dy, float *gpart, int32_t &nblk, hipStream_t s)
+hipError_t mlp_train_hd(const MlpArgs &a, const double *xi, const double *Vl, const double *Gl, int64_t n, float alpha,
+                        float beta, float *gpart, hipStream_t s)
 {
-    constexpr int S = bwd_samples<H>();
-    nblk = (int32_t)((n + S - 1) / S);
-    hipLaunchKernelGGL((k_mlp_bwd<H, D>), dim3(nblk), dim3(kBlock), 0, s, a, xi, Vl, Gl, n, inv_b, alpha, beta, t_a2,
-                       t_dz2, t_y, t_dy, gpart);
+    hipLaunchKernelGGL((k_mlp_train<H, D>), dim3((unsigned)mlp_train_blocks(H, n)), dim3(kTrainBlock), 0, s, a, xi, Vl,
+                       Gl, n, 1.f / (float)n, alpha, beta, gpart);
     return hipGetLastError();
 }
 
 }  // namespace
 
 int32_t mlp_param_count(int32_t H, int32_t D) { return poff(H, 2 * D).P; }
-int32_t mlp_bwd_blocks(int32_t H, int64_t n) { return (int32_t)((n + (H >= 128 ? 8 : 16) - 1) / (H >= 128 ? 8 : 16)); }
+int32_t mlp_train_blocks(int32_t H, int64_t n)
+{
+    const int S = H >= 128 ? train_samples<128>() : train_samples<64>();
+    return (int32_t)((n + S - 1) / S);
+}
 
 #define SX_MLP_DISPATCH(FN, ...)                                                   \
     switch (a.H * 10 + a.D) {                                                      \
@@ -737,53 +814,37 @@ int32_t mlp_bwd_blocks(int32_t H, int64_t n) { return (int32_t)((n + (H >= 128 ?
     default: return hipErrorInvalidValue;                                          \
     }
 
-hipError_t launch_mlp_fwd(const MlpArgs &a, const double *xi, int64_t n, double *V, double *dV, float *t_a2,
-                          float *t_dz2, float *t_y, float *t_dy, uint8_t *flag, hipStream_t s, const MlpStep *step)
+hipError_t launch_mlp_fwd(const MlpArgs &a, const double *xi, int64_t n, double *V, double *dV, uint8_t *flag,
+                          hipStream_t s, const MlpStep *step)
 {
-    SX_MLP_DISPATCH(mlp_fwd_hd, a, xi, n, V, dV, t_a2, t_dz2, t_y, t_dy, flag, s, step)
+    SX_MLP_DISPATCH(mlp_fwd_hd, a, xi, n, V, dV, flag, s, step)
 }
 
-static hipError_t reduce_and_adam(const MlpArgs &a, const float *gpart, int32_t nblk, double *red, float lr, int64_t t,
-                                  double *loss_out, int32_t update, double *gsum, hipStream_t s)
+hipError_t launch_mlp_grad(const MlpArgs &a, const double *xi, const double *Vl, const double *Gl, int64_t n,
+                           float alpha, float beta, float *gpart, hipStream_t s)
+{
+    SX_MLP_DISPATCH(mlp_train_hd, a, xi, Vl, Gl, n, alpha, beta, gpart, s)
+}
+
+static hipError_t mlp_update(const MlpArgs &a, const float *gpart, int64_t n, float lr, int64_t t, double *loss_out,
+                             int32_t update, double *gsum, hipStream_t s)
 {
     const int P = mlp_param_count(a.H, a.D);
-    const int ns = nblk < kMlpRedSlices ? nblk : kMlpRedSlices;
-    const int per = (nblk + ns - 1) / ns;
-    const unsigned gx = (unsigned)((P + 1 + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3(gx, ns), dim3(kBlock), 0, s, gpart, nblk, P, per, red);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mlp_adam, dim3(gx), dim3(kBlock), 0, s, a, (const double *)red, ns, P, t, lr, loss_out, update,
-                       gsum);
+    const double bc1 = 1.0 - std::pow(0.9, (double)t), bc2 = 1.0 - std::pow(0.999, (double)t);
+    hipLaunchKernelGGL(k_mlp_update, dim3((unsigned)((P + kUpdParams) / kUpdParams)), dim3(kUpdParams * kUpdSlices), 0,
+                       s, a, gpart, mlp_train_blocks(a.H, n), P, bc1, bc2, lr, loss_out, update, gsum);
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_train_step(const MlpArgs &a, const double *xi, const double *Vl, const double *Gl, int64_t n,
-                                 float alpha, float beta, float lr, int64_t t, float *t_a2, float *t_dz2, float *t_y,
-                                 float *t_dy, float *gpart, double *red, double *loss_out, hipStream_t s)
+hipError_t launch_mlp_adam(const MlpArgs &a, const float *gpart, int64_t n, float lr, int64_t t, double *loss_out,
+                           hipStream_t s)
 {
-    hipError_t e = launch_mlp_fwd(a, xi, n, nullptr, nullptr, t_a2, t_dz2, t_y, t_dy, nullptr, s);
-    if (e != hipSuccess) return e;
-    int32_t nblk = 0;
-    const float inv_b = 1.f / (float)n;
-    switch (a.H * 10 + a.D) {
-    case 641: e = mlp_bwd_hd<64, 1>(a, xi, Vl, Gl, n, inv_b, alpha, beta, t_a2, t_dz2, t_y, t_dy, gpart, nblk, s); break;
-    case 642: e = mlp_bwd_hd<64, 2>(a, xi, Vl, Gl, n, inv_b, alpha, beta, t_a2, t_dz2, t_y, t_dy, gpart, nblk, s); break;
-    case 643: e = mlp_bwd_hd<64, 3>(a, xi, Vl, Gl, n, inv_b, alpha, beta, t_a2, t_dz2, t_y, t_dy, gpart, nblk, s); break;
-    case 1281: e = mlp_bwd_hd<128, 1>(a, xi, Vl, Gl, n, inv_b, alpha, beta, t_a2, t_dz2, t_y, t_dy, gpart, nblk, s); break;
-    case 1282: e = mlp_bwd_hd<128, 2>(a, xi, Vl, Gl, n, inv_b, alpha, beta, t_a2, t_dz2, t_y, t_dy, gpart, nblk, s); break;
-    case 1283: e = mlp_bwd_hd<128, 3>(a, xi, Vl, Gl, n, inv_b, alpha, beta, t_a2, t_dz2, t_y, t_dy, gpart, nblk, s); break;
-    default: return hipErrorInvalidValue;
-    }
-    if (e != hipSuccess) return e;
-    if (lr > 0.f) return reduce_and_adam(a, gpart, nblk, red, lr, t, loss_out, 1, nullptr, s);
-    return hipSuccess;  // gradient only: launch_mlp_grad_sum reads gpart
+    return mlp_update(a, gpart, n, lr, t, loss_out, 1, nullptr, s);
 }
 
-hipError_t launch_mlp_grad_sum(const MlpArgs &a, const float *gpart, int64_t n, double *red, double *gsum,
-                               hipStream_t s)
+hipError_t launch_mlp_grad_sum(const MlpArgs &a, const float *gpart, int64_t n, double *gsum, hipStream_t s)
 {
-    return reduce_and_adam(a, gpart, mlp_bwd_blocks(a.H, n), red, 0.f, 1, nullptr, 0, gsum, s);
+    return mlp_update(a, gpart, n, 0.f, 1, nullptr, 0, gsum, s);
 }
 
 // ------------------------------------------------------- certification mask

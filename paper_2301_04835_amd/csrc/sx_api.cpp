@@ -85,8 +85,8 @@ struct Plan {
     int32_t sgP = 0;
     int64_t sgN = 0, sgCells = 0, sgCorners = 0;
     Sub s_sgP32, s_sgPb, s_sgM, s_sgV, s_sgMask;
-    Sub w_sgX, w_sgVt, w_sgGt, w_sgVn, w_sgGn, w_sgA2, w_sgDz2, w_sgY, w_sgDy, w_sgGpart, w_sgGsum, w_sgLoss;
-    Sub w_sgFlag, w_sgRed;
+    Sub w_sgX, w_sgVt, w_sgGt, w_sgVn, w_sgGn, w_sgGpart, w_sgGsum, w_sgLoss;
+    Sub w_sgFlag;
     // workspace sub-buffers
     Sub w_xi, w_V, w_dV, w_J, w_J64, w_part, w_cnpart;
     int32_t abf_nblk = 0;  // ABF in two launches when > 0 (blocks of touched atoms)
@@ -580,21 +580,16 @@ sx_status make_plan(sx_ctx *c)
         p.w_jac = lw.take(16 * W * (size_t)cl.jtotal);
     }
     if (c->sg_H) {
-        const size_t N = (size_t)p.sgN, B = (size_t)c->sg_max_batch, H = (size_t)c->sg_H, D = (size_t)p.D;
+        const size_t N = (size_t)p.sgN, B = (size_t)c->sg_max_batch, D = (size_t)p.D;
         p.w_sgX = lw.take(sizeof(double) * N * D);
         p.w_sgVt = lw.take(sizeof(double) * N);
         p.w_sgGt = lw.take(sizeof(double) * N * D);
         p.w_sgVn = lw.take(sizeof(double) * N);
         p.w_sgGn = lw.take(sizeof(double) * N * D);
-        p.w_sgA2 = lw.take(sizeof(float) * B * H);
-        p.w_sgDz2 = lw.take(sizeof(float) * D * B * H);
-        p.w_sgY = lw.take(sizeof(float) * B);
-        p.w_sgDy = lw.take(sizeof(float) * B * D);
-        p.w_sgGpart = lw.take(sizeof(float) * (size_t)mlp_bwd_blocks(c->sg_H, (int64_t)B) * (p.sgP + 1));
+        p.w_sgGpart = lw.take(sizeof(float) * (size_t)mlp_train_blocks(c->sg_H, (int64_t)B) * (p.sgP + 1));
         p.w_sgGsum = lw.take(sizeof(double) * (p.sgP + 1));
         p.w_sgLoss = lw.take(sizeof(double));
         p.w_sgFlag = lw.take((size_t)p.W);
-        p.w_sgRed = lw.take(sizeof(double) * kMlpRedSlices * (p.sgP + 1));
     }
     p.ws_bytes = lw.cur;
     p.valid = true;
@@ -767,7 +762,6 @@ MlpArgs mlp_args(sx_ctx *c)
     a.P32 = at<float>(c->state, p.s_sgP32);
     a.m = at<float>(c->state, p.s_sgM);
     a.v = at<float>(c->state, p.s_sgV);
-    a.nmax = c->sg_max_batch;
     a.out_scale = c->sg_out_scale;
     a.out_shift = c->sg_out_shift;
     a.cert_n = c->sg_cert_n;
@@ -807,7 +801,7 @@ sx_status enqueue_surrogate_step(sx_ctx *c, const PosView &pv, int64_t step, dou
     } else if (sx_status s2 = launch_cvs(c, pv, xi, J)) {
         return s2;
     }
-    hipError_t e = launch_mlp_fwd(mlp_args(c), xi, p.W, V, dV, nullptr, nullptr, nullptr, nullptr, flag, c->stream, &st);
+    hipError_t e = launch_mlp_fwd(mlp_args(c), xi, p.W, V, dV, flag, c->stream, &st);
     if (e == hipSuccess) {
         SharedArgs a = shared_args(c, 0, xi, p.W, c->grid > 0 ? c->grid : kSharedTarget);
         a.fb = flag;
@@ -1044,8 +1038,7 @@ sx_status enqueue_step(sx_ctx *c, const void *pos, int32_t dtype, int32_t layout
         a.dt = c->abf_dt;
         if (c->funn_on) {  // the network's gradient at xi is the bias
             double *g = at<double>(c->ws, p.w_dV);
-            hipError_t e = launch_mlp_fwd(mlp_args(c), xi, p.W, at<double>(c->ws, p.w_V), g, nullptr, nullptr, nullptr,
-                                          nullptr, nullptr, c->stream);
+            hipError_t e = launch_mlp_fwd(mlp_args(c), xi, p.W, at<double>(c->ws, p.w_V), g, nullptr, c->stream);
             if (e != hipSuccess) return hip_fail(c, e, "FUNN network");
             a.b_ext = g;
         }
@@ -1927,8 +1920,7 @@ sx_status sx_surrogate_eval(sx_ctx *ctx, const double *xi, int64_t n, double *V_
     if (fallback && !ctx->sg_certified) return fail(ctx, SX_ESTATE, "surrogate not certified (sx_surrogate_certify)");
     if (n < 0 || (n > 0 && !xi)) return fail(ctx, SX_EINVAL, "bad query points");
     if (n == 0) return SX_OK;
-    hipError_t e = launch_mlp_fwd(mlp_args(ctx), xi, n, V_out, dVdxi_out, nullptr, nullptr, nullptr, nullptr, fallback,
-                                  ctx->stream);
+    hipError_t e = launch_mlp_fwd(mlp_args(ctx), xi, n, V_out, dVdxi_out, fallback, ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "surrogate forward");
     return SX_OK;
     SX_GUARD_END
@@ -1945,11 +1937,8 @@ sx_status sx_surrogate_loss_grad(sx_ctx *ctx, const double *xi, const double *V,
     const MlpArgs a = mlp_args(ctx);
     float *gpart = at<float>(ctx->ws, p.w_sgGpart);
     double *gsum = at<double>(ctx->ws, p.w_sgGsum);
-    double *red = at<double>(ctx->ws, p.w_sgRed);
-    hipError_t e = launch_mlp_train_step(a, xi, V, G, n, (float)alpha, (float)beta, 0.f, 1, at<float>(ctx->ws, p.w_sgA2),
-                                         at<float>(ctx->ws, p.w_sgDz2), at<float>(ctx->ws, p.w_sgY),
-                                         at<float>(ctx->ws, p.w_sgDy), gpart, red, nullptr, ctx->stream);
-    if (e == hipSuccess) e = launch_mlp_grad_sum(a, gpart, n, red, gsum, ctx->stream);
+    hipError_t e = launch_mlp_grad(a, xi, V, G, n, (float)alpha, (float)beta, gpart, ctx->stream);
+    if (e == hipSuccess) e = launch_mlp_grad_sum(a, gpart, n, gsum, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     std::vector<double> g(p.sgP + 1);
     if (e == hipSuccess) e = hipMemcpy(g.data(), gsum, sizeof(double) * (p.sgP + 1), hipMemcpyDeviceToHost);
@@ -1972,6 +1961,7 @@ sx_status sx_surrogate_fit(sx_ctx *ctx, const double *xi, const double *V, const
     if (steps < 0 || !(lr > 0) || lr_final < 0 || lr_final > lr) return fail(ctx, SX_EINVAL, "bad schedule");
     const MlpArgs a = mlp_args(ctx);
     double *loss = at<double>(ctx->ws, p.w_sgLoss);
+    float *gpart = at<float>(ctx->ws, p.w_sgGpart);
     int64_t last = 1;
     hipError_t e = hipSuccess;
     for (int32_t k = 0; k < steps && e == hipSuccess; ++k) {
@@ -1981,11 +1971,9 @@ sx_status sx_surrogate_fit(sx_ctx *ctx, const double *xi, const double *V, const
         const double lr_k = lr_final + (lr - lr_final) * 0.5 * (1.0 + std::cos(M_PI * k / std::max(1, steps)));
         ++ctx->sg_t;
         last = len;
-        e = launch_mlp_train_step(a, xi + i0 * p.D, V + i0, G + i0 * p.D, len, (float)alpha, (float)beta, (float)lr_k,
-                                  ctx->sg_t, at<float>(ctx->ws, p.w_sgA2), at<float>(ctx->ws, p.w_sgDz2),
-                                  at<float>(ctx->ws, p.w_sgY), at<float>(ctx->ws, p.w_sgDy),
-                                  at<float>(ctx->ws, p.w_sgGpart), at<double>(ctx->ws, p.w_sgRed),
-                                  k == steps - 1 ? loss : nullptr, ctx->stream);
+        e = launch_mlp_grad(a, xi + i0 * p.D, V + i0, G + i0 * p.D, len, (float)alpha, (float)beta, gpart, ctx->stream);
+        if (e == hipSuccess)
+            e = launch_mlp_adam(a, gpart, len, (float)lr_k, ctx->sg_t, k == steps - 1 ? loss : nullptr, ctx->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     double l = 0;
@@ -2093,8 +2081,7 @@ sx_status sx_surrogate_certify(sx_ctx *ctx, const double *lo, const double *hi, 
     if (sx_status st = exact_bias(ctx, X, M, at<double>(ctx->ws, p.w_sgVt), Gt)) return st;
     const MlpArgs a = mlp_args(ctx);
     uint8_t *mask = at<uint8_t>(ctx->state, p.s_sgMask);
-    e = launch_mlp_fwd(a, X, M, at<double>(ctx->ws, p.w_sgVn), Gn, nullptr, nullptr, nullptr, nullptr, nullptr,
-                       ctx->stream);
+    e = launch_mlp_fwd(a, X, M, at<double>(ctx->ws, p.w_sgVn), Gn, nullptr, ctx->stream);
     if (e == hipSuccess) e = launch_cert_mask(a, Gn, Gt, h, ctx->sg_tol, mask, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     std::vector<uint8_t> hm((size_t)p.sgCells);

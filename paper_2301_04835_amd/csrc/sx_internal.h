@@ -366,7 +366,6 @@ struct MlpArgs {
     const uint16_t *Pb;  // bf16 parameters (read)
     uint16_t *Pw;        // the same, written by the optimiser
     float *P32, *m, *v;  // FP32 master parameters, Adam moments
-    int64_t nmax;        // row stride of the training tangents
     double out_scale, out_shift;  // V = out_shift + out_scale * y (FP32 network output y)
     double cert_lo[kMaxBiasDim], cert_inv_h[kMaxBiasDim];
     int32_t cert_n;
@@ -411,22 +410,21 @@ hipError_t launch_cell_cv(const CellArgs &c, const CvSet &cs, const PosView &pos
 hipError_t launch_cell_vjp(const CellArgs &c, const CvSet &cs, const PosView &pos, const double *coef, double sign,
                            ForceView out, hipStream_t s);
 int32_t mlp_param_count(int32_t H, int32_t D);
-int32_t mlp_bwd_blocks(int32_t H, int64_t n);
-hipError_t launch_mlp_fwd(const MlpArgs &a, const double *xi, int64_t n, double *V, double *dV, float *t_a2,
-                          float *t_dz2, float *t_y, float *t_dy, uint8_t *flag, hipStream_t s,
-                          const MlpStep *step = nullptr);
-// one optimisation step over n samples: forward, reverse, Adam (lr > 0) or
-// only the loss (lr <= 0, gradients left in gpart)
-hipError_t launch_mlp_train_step(const MlpArgs &a, const double *xi, const double *Vl, const double *Gl, int64_t n,
-                                 float alpha, float beta, float lr, int64_t t, float *t_a2, float *t_dz2, float *t_y,
-                                 float *t_dy, float *gpart, double *red, double *loss_out, hipStream_t s);
+int32_t mlp_train_blocks(int32_t H, int64_t n);  // workgroups (gradient records) of n training samples
+hipError_t launch_mlp_fwd(const MlpArgs &a, const double *xi, int64_t n, double *V, double *dV, uint8_t *flag,
+                          hipStream_t s, const MlpStep *step = nullptr);
+// loss and gradient of n samples, one record of P + 1 floats per workgroup
+// (the last the loss) in gpart
+hipError_t launch_mlp_grad(const MlpArgs &a, const double *xi, const double *Vl, const double *Gl, int64_t n,
+                           float alpha, float beta, float *gpart, hipStream_t s);
+// Adam step t (from 1) with those records; loss_out (may be null): the sum
+// of the per-sample losses
+hipError_t launch_mlp_adam(const MlpArgs &a, const float *gpart, int64_t n, float lr, int64_t t, double *loss_out,
+                           hipStream_t s);
 hipError_t launch_mlp_round(const MlpArgs &a, hipStream_t s);
-// ordered FP64 sum of the per-workgroup gradients of the last reverse pass
-// over n samples into gsum[0..P) and the loss sum into gsum[P]; red:
-// kMlpRedSlices x (P + 1) doubles of scratch
-constexpr int kMlpRedSlices = 16;
-hipError_t launch_mlp_grad_sum(const MlpArgs &a, const float *gpart, int64_t n, double *red, double *gsum,
-                               hipStream_t s);
+// ordered FP64 sum of those records into gsum[0..P) and the loss sum into
+// gsum[P]
+hipError_t launch_mlp_grad_sum(const MlpArgs &a, const float *gpart, int64_t n, double *gsum, hipStream_t s);
 // certification: one lane per cell of the cert_n^D grid; dVhat and dV
 // [M][D] hold the network's and the exact gradient at the M grid corners
 // (row-major, the first CV slowest; periodic CVs: cert_n corners per CV,
