@@ -4,96 +4,197 @@
 //
 // Unlike the private-list sum, every hill is reused by every query, so the
 // work is bound by VALU arithmetic, not by HBM:
-//   * grid x: hill chunks (multiples of 256 hills, sized so that chunks x
-//     query blocks fill the chip); grid y: blocks of 64 Q queries;
-//   * the four wavefronts of a workgroup hold the same 64 Q queries (Q per
-//     lane) and split every staged group of 256 hills in four, so a small
-//     query set (a step's walkers) still gives several wavefronts per
-//     SIMD; a fixed-order LDS reduction joins the four;
-//   * staging converts each hill once: centres to FP64, scaled by
-//     s_d = sqrt(log2(e) / (2 sigma_d^2)), so that a (hill, query) pair costs
-//     the scaled displacement and its periodic wrap (FP64), the quadratic
-//     form (FP64 FMAs), one v_exp_f32, and FP64 sums of e and e * dx: about
-//     17 VALU operations for two CVs.  Summing the products e * dxi in FP32
-//     would lose digits where the terms of dV/dxi cancel;
+//   * grid x: hill chunks, an equal share of the hills in the list each
+//     (formed from the count on the device, so a list with spare capacity
+//     keeps every workgroup busy); grid y: blocks of ql Q queries;
+//   * the four wavefronts of a workgroup hold the same queries (Q per lane)
+//     and split every staged group of 256 hills in four; with fewer than 64
+//     queries, ql = 32, 16, 8 or 4 lanes hold them and the 64 / ql lane groups
+//     split the wavefront's hills (32 queries on 64 lanes left half of them
+//     idle); shuffles and a fixed-order LDS reduction join all of them;
+//   * staging converts each hill once to FP64: a periodic CV in turns less
+//     one half, so that f = fract(xi - c + 1/2) is the minimum image plus one
+//     half in two operations, and w f (f - 1) + w / 4 its term of the
+//     quadratic form in two more; another CV scaled by
+//     sqrt(log2(e) / (2 sigma^2)).  With the Gaussian (one v_exp_f32, half
+//     rate) and FP64 sums of e and e f, a (hill, query) pair of two periodic
+//     CVs takes 16 issue slots (18 with a scaled displacement and
+//     x - P rint(x / P)).  The sum of e (f - 1/2) is formed once per chunk.
+//     Summing the products in FP32 would lose digits where the terms of
+//     dV/dxi cancel;
 //   * periodicity is a template parameter (all, none, or per CV);
+//   * when every CV is a dihedral a step's workgroups evaluate their queries'
+//     CVs themselves (FP64) while their first hills are in flight, which
+//     saves the CV kernel's launch; the first chunk's workgroups store xi and
+//     the Jacobian for the finalize;
 //   * each (chunk, query) partial has one writer; the finalize kernel sums a
 //     query's chunks in chunk order (bitwise deterministic), forms dV/dxi,
-//     and appends one hill per walker for a deposition step, in walker order.
+//     and appends one hill per walker for a deposition step, in walker order;
+//     the last of its workgroups to arrive then moves the count.
+// A step of 256 walkers on 100,000 hills: 22.8 us (34.7 with a CV launch, a
+// count launch, 18 slots per pair and 784 unequal workgroups); 131,072 points
+// on 100,000 hills: 5.79 ms = 2.26 x 10^12 pairs/s, 36 T of the 38 T issue
+// slots/s a loop of multiply-adds reaches (6.24 ms).
 #include "sx_internal.h"
+#include "dev_cv.h"
 #include "dev_gather.h"
 
 namespace sx {
 namespace {
 
 constexpr int kStage = kBlock;  // hills staged in LDS at a time (one per lane)
-constexpr int kQueryLanes = 64;  // queries of a block per Q
+constexpr int64_t kMaxRecords = 8 * 65536;  // partial records of a sum at arbitrary points
 
 enum { kPerNone = 0, kPerAll = 1, kPerMixed = 2 };
 
-template <int D, int Q, int PER>
-__global__ void __launch_bounds__(kBlock) k_hill_shared(SharedArgs a)
+// Queries per lane (Q) and lanes that hold queries (ql) of a sum over nq
+// queries.  More queries per lane amortise the staged hills' LDS reads; they
+// need enough query blocks left to fill the chip: 4 from 8,192 points on, 2
+// from 1,024, else 1.
+void shared_shape(int64_t nq, int &Q, int &ql)
 {
-    __shared__ double s_c[D][kStage];
+    Q = nq >= 8192 ? 4 : nq >= 1024 ? 2 : 1;
+    ql = 64;
+    while (ql > 4 && nq <= ql / 2) ql /= 2;
+}
+
+// Dihedral d of the walker whose atoms start at aoff (T: the position type);
+// the atom indices and slot are selected by value from the kernel arguments.
+template <int D, typename T>
+__device__ __forceinline__ double query_dihedral(const CvSet &cs, const PosView &pos, int64_t aoff, int d, double3 (&g)[4],
+                                                 int32_t &slot0)
+{
+    int32_t at[4];
+    slot0 = cs.cv[0].slot0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) at[q] = cs.cv[0].atom[q];
+#pragma unroll
+    for (int dd = 1; dd < D; ++dd) {
+        slot0 = d == dd ? cs.cv[dd].slot0 : slot0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) at[q] = d == dd ? cs.cv[dd].atom[q] : at[q];
+    }
+    double3 r[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r[q] = ld_pos_t<T>(pos, aoff + at[q]);
+    return dihedral_fp64<true>(r, g);
+}
+
+template <int D, int Q, int PER, bool FUSE>
+__device__ __forceinline__ void hill_shared(const SharedArgs &a, const SharedCv *fc)
+{
+    __shared__ double s_c[kStage][D];
     __shared__ float s_h[kStage];
-    __shared__ double s_red[3][Q * (1 + D)][kQueryLanes];
+    __shared__ double s_red[3][Q * (1 + D)][64];
+    __shared__ double s_xi[FUSE ? D : 1][FUSE ? 64 * Q : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // the step counter moves here (the finalize, which may deposit, reads it)
     if (a.count_step && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
         *a.dstep = a.step >= 0 ? a.step + 1 : *a.dstep + 1;
     const int32_t n = *a.count;
-    const int64_t qb0 = (int64_t)blockIdx.y * kQueryLanes * Q;
+    // ql lanes hold queries; G = 64 / ql = 2^lg groups of them split the hills
+    const int lg = Q > 1 ? 0 : a.lg, ql = 64 >> lg, G = 1 << lg;
+    const int qlane = lane & (ql - 1), grp = lane >> (6 - lg);
+    const int64_t qb0 = (int64_t)blockIdx.y * ql * Q;
     const int64_t nq = a.nq;
-    double sc[D], per[D], iper[D];
+    // this workgroup's share of the hills
+    const int64_t share = (((int64_t)n + a.nchunk - 1) / a.nchunk + 3) / 4 * 4;
+    const int64_t h0 = min((int64_t)n, (int64_t)blockIdx.x * share), hend = min((int64_t)n, h0 + share);
+    // the first stage's hills, requested ahead of the CVs
+    float cn[D], hn = 0.f;
+    auto request = [&](int64_t k) {
+        const bool ok = k < hend;
+#pragma unroll
+        for (int d = 0; d < D; ++d) cn[d] = ok ? a.c[d][k] : 0.f;
+        hn = ok ? a.h[k] : 0.f;  // zero height: no contribution
+    };
+    request(h0 + threadIdx.x);
+    if (FUSE) {
+        for (int it = threadIdx.x; it < ql * Q * D; it += kBlock) {
+            const int d = it / (ql * Q), i = it % (ql * Q);
+            const int64_t w = qb0 + i;
+            if (w >= nq) continue;
+            const int64_t aoff = a.tabs.atom_off[w];
+            double3 g[4];
+            int32_t slot0;
+            const double x = fc->pos.f64 ? query_dihedral<D, double>(fc->cs, fc->pos, aoff, d, g, slot0)
+                                         : query_dihedral<D, float>(fc->cs, fc->pos, aoff, d, g, slot0);
+            s_xi[d][i] = x;
+            if (blockIdx.x == 0) {
+                fc->xi_ws[w * D + d] = x;
+                float *js = fc->J_ws + (w * a.nslots + slot0) * 3;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    js[3 * q] = (float)g[q].x;
+                    js[3 * q + 1] = (float)g[q].y;
+                    js[3 * q + 2] = (float)g[q].z;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // scale of CV d: turns (periodic), or units in which the quadratic form
+    // is the square; wt: the periodic CV's weight of f (f - 1) + 1/4
+    constexpr double kInvTurn = 0.15915494309189533577, kTurn = 6.2831853071795864769;
+    double sc[D], wt[D], q0 = 0.0;
     bool wrap[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        sc[d] = sqrt(0.7213475204444817 * a.inv_sig2[d]);  // log2(e) / 2 = 0.72134...
+        const double s2 = 0.72134752044448170368 * a.inv_sig2[d];  // log2(e) / (2 sigma^2)
         wrap[d] = PER == kPerAll || (PER == kPerMixed && a.period[d] > 0.0);
-        per[d] = a.period[d] * sc[d];
-        iper[d] = a.inv_period[d] / sc[d];
+        wt[d] = wrap[d] ? s2 * (kTurn * kTurn) : 0.0;
+        sc[d] = wrap[d] ? kInvTurn : sqrt(s2);
+        q0 += 0.25 * wt[d];
     }
     double xs[Q][D];
     bool live[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        const int64_t q = qb0 + lane + (int64_t)kQueryLanes * i;
+        const int64_t q = qb0 + qlane + (int64_t)ql * i;
         live[i] = q < nq;
 #pragma unroll
-        for (int d = 0; d < D; ++d) xs[i][d] = live[i] ? a.xi[q * D + d] * sc[d] : 0.0;
+        for (int d = 0; d < D; ++d) {
+            const double x = !live[i] ? 0.0 : FUSE ? s_xi[FUSE ? d : 0][FUSE ? qlane + ql * i : 0] : a.xi[q * D + d];
+            xs[i][d] = x * sc[d];
+        }
     }
     double acc[Q][1 + D];
 #pragma unroll
     for (int i = 0; i < Q; ++i)
 #pragma unroll
         for (int j = 0; j <= D; ++j) acc[i][j] = 0.0;
-    const int64_t h0 = (int64_t)blockIdx.x * a.chunk;
-    const int64_t hend = min((int64_t)n, h0 + a.chunk);
     for (int64_t s0 = h0; s0 < hend; s0 += kStage) {
-        const int64_t k = s0 + threadIdx.x;
-        const bool ok = k < hend;
 #pragma unroll
-        for (int d = 0; d < D; ++d) s_c[d][threadIdx.x] = ok ? (double)a.c[d][k] * sc[d] : 0.0;
-        s_h[threadIdx.x] = ok ? a.h[k] : 0.f;  // zero height: no contribution
+        for (int d = 0; d < D; ++d)
+            s_c[threadIdx.x][d] = wrap[d] ? fma((double)cn[d], sc[d], -0.5) : (double)cn[d] * sc[d];
+        s_h[threadIdx.x] = hn;
         __syncthreads();
-        // this wavefront's quarter of the staged hills
+        request(s0 + kStage + threadIdx.x);
+        // this wavefront's quarter of the staged hills in steps of 4 G, four
+        // neighbours per lane group (4 G <= 64, so at most 64 a wavefront)
         const int m = (int)min((int64_t)kStage, hend - s0);
-        const int j0 = wave * 64, j1 = min(j0 + 64, m);
-        for (int jb = j0; jb < j1; jb += 4) {
+        const int steps = ((m + 3) / 4 + 4 * G - 1) >> (2 + lg);
+        int jb = wave * steps * 4 * G + 4 * grp;
+        for (int st = 0; st < steps; ++st, jb += 4 * G) {
 #pragma unroll
-            for (int j = jb; j < jb + 4; ++j) {  // j < j0 + 64 <= kStage; past m: zero height
+            for (int u = 0; u < 4; ++u) {  // past m: zero height
+                const int j = jb + u;
                 double c[D];
 #pragma unroll
-                for (int d = 0; d < D; ++d) c[d] = s_c[d][j];
+                for (int d = 0; d < D; ++d) c[d] = s_c[j][d];
                 const float h = s_h[j];
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
-                    double x[D], qd = 0.0;
+                    double x[D], qd = q0;
 #pragma unroll
                     for (int d = 0; d < D; ++d) {
                         x[d] = xs[i][d] - c[d];
-                        if (wrap[d]) x[d] = fma(-per[d], rint(x[d] * iper[d]), x[d]);
-                        qd = fma(x[d], x[d], qd);
+                        if (wrap[d]) {
+                            x[d] = __builtin_amdgcn_fract(x[d]);
+                            qd = fma(x[d], fma(wt[d], x[d], -wt[d]), qd);
+                        } else {
+                            qd = fma(x[d], x[d], qd);
+                        }
                     }
                     const double e = (double)(h * __builtin_amdgcn_exp2f(-(float)qd));
                     acc[i][0] += e;
@@ -104,7 +205,11 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared(SharedArgs a)
         }
         __syncthreads();
     }
-    // join the four wavefronts in a fixed order (0 + 1 + 2 + 3)
+    // join the lane groups, then the four wavefronts in a fixed order (0 + 1 + 2 + 3)
+    if (Q == 1)
+        for (int o = ql; o < 64; o <<= 1)
+#pragma unroll
+            for (int j = 0; j <= D; ++j) acc[0][j] += __shfl_xor(acc[0][j], o, 64);
     if (wave > 0) {
 #pragma unroll
         for (int i = 0; i < Q; ++i)
@@ -112,7 +217,7 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared(SharedArgs a)
             for (int j = 0; j <= D; ++j) s_red[wave - 1][i * (1 + D) + j][lane] = acc[i][j];
     }
     __syncthreads();
-    if (wave != 0) return;
+    if (wave != 0 || grp != 0) return;
 #pragma unroll
     for (int w = 0; w < 3; ++w)
 #pragma unroll
@@ -122,12 +227,25 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared(SharedArgs a)
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         if (!live[i]) continue;
-        const int64_t q = qb0 + lane + (int64_t)kQueryLanes * i;
-        double *p = a.partial + ((int64_t)blockIdx.x * a.nq + q) * 4;
+        const int64_t q = qb0 + qlane + (int64_t)ql * i;
+        double *p = a.partial + ((int64_t)blockIdx.x * a.rec_ch + q * a.rec_q) * 4;
         p[0] = acc[i][0];
 #pragma unroll
-        for (int d = 0; d < D; ++d) p[1 + d] = acc[i][1 + d] / sc[d];  // back to CV units
+        for (int d = 0; d < D; ++d)  // back to CV units
+            p[1 + d] = wrap[d] ? kTurn * (acc[i][1 + d] - 0.5 * acc[i][0]) : acc[i][1 + d] / sc[d];
     }
+}
+
+template <int D, int Q, int PER>
+__global__ void __launch_bounds__(kBlock) k_hill_shared(SharedArgs a)
+{
+    hill_shared<D, Q, PER, false>(a, nullptr);
+}
+
+template <int D, int Q>
+__global__ void __launch_bounds__(kBlock) k_hill_shared_cv(SharedArgs a, SharedCv fc)
+{
+    hill_shared<D, Q, kPerAll, true>(a, &fc);
 }
 
 template <int N>
@@ -150,6 +268,24 @@ __device__ __forceinline__ void block_sum0(double (&v)[N], double *lds)
         }
 }
 
+// does this launch append hills?  (the step counter was moved by the sum)
+__device__ __forceinline__ bool deposits(const SharedArgs &a)
+{
+    return a.deposit == 2 || (a.deposit == 1 && a.stride > 0 && (*a.dstep - 1) % a.stride == 0);
+}
+
+// The count of a shared list moves by the walkers' hills when the last
+// workgroup of a depositing finalize arrives: by one thread per workgroup,
+// after the workgroup's threads have read the count (a barrier, or one
+// wavefront).  The ticket orders nothing else: the appended hills are read by
+// later launches.  (A kernel of its own for this took 3.4 us on every step.)
+__device__ __forceinline__ void shared_count(const SharedArgs &a, int32_t cnt)
+{
+    if (atomicAdd(a.tick, 1) != (int32_t)gridDim.x - 1) return;
+    *a.tick = 0;
+    if ((int64_t)cnt + a.nq <= a.cap) *a.count = (int32_t)(cnt + a.nq);
+}
+
 // per query: V, dV/dxi, outputs and (all or none) the appended hill;
 // w is the query's row (its walker, or its evaluation point)
 template <int D>
@@ -169,11 +305,9 @@ __device__ __forceinline__ void shared_finish(const SharedArgs &a, int64_t w, co
         if (a.xi_out) a.xi_out[w * D + d] = a.xi[w * D + d];
     }
     if (!finite && a.flags) atomicOr(a.flags, kFlagNonFinite);
-    bool dep = a.deposit == 2;
-    if (a.deposit == 1 && a.stride > 0) dep = (*a.dstep - 1) % a.stride == 0;
-    if (dep) {
+    if (deposits(a)) {
         // all walkers append in walker order at count + w (all or none);
-        // the count moves in the next kernel, after every lane read it
+        // the count moves once every workgroup has read it
         const int32_t n = *a.count;
         if ((int64_t)n + a.nq <= a.cap) {
             const int64_t k = (int64_t)n + w;
@@ -191,24 +325,30 @@ template <int D>
 __global__ void __launch_bounds__(kBlock) k_hill_shared_finalize(SharedArgs a)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= a.nq) return;
-    double acc[1 + D];
+    if (q < a.nq) {
+        double acc[1 + D];
 #pragma unroll
-    for (int j = 0; j <= D; ++j) acc[j] = 0.0;
-    for (int ch = 0; ch < a.nchunk; ++ch) {
-        const double *p = a.partial + ((int64_t)ch * a.nq + q) * 4;
+        for (int j = 0; j <= D; ++j) acc[j] = 0.0;
+#pragma unroll 4
+        for (int ch = 0; ch < a.nchunk; ++ch) {
+            const double *p = a.partial + ((int64_t)ch * a.rec_ch + q * a.rec_q) * 4;
 #pragma unroll
-        for (int j = 0; j <= D; ++j) acc[j] += p[j];
+            for (int j = 0; j <= D; ++j) acc[j] += p[j];
+        }
+        double dv[D];
+        shared_finish<D>(a, q, acc, dv);
+        if (a.do_forces) {  // coefficients -dV/dxi; this lane owns the walker's atoms
+            double coef[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) coef[d] = -dv[d];
+            const float *Jw = a.J + q * a.nslots * 3;
+            for (int u = 0; u < a.tabs.U; ++u) gather_atom(a.tabs, Jw, (int32_t)q, coef, a.F, u);
+        }
     }
-    double dv[D];
-    shared_finish<D>(a, q, acc, dv);
-    if (a.do_forces) {  // coefficients -dV/dxi; this lane owns the walker's atoms
-        double coef[D];
-#pragma unroll
-        for (int d = 0; d < D; ++d) coef[d] = -dv[d];
-        const float *Jw = a.J + q * a.nslots * 3;
-        for (int u = 0; u < a.tabs.U; ++u) gather_atom(a.tabs, Jw, (int32_t)q, coef, a.F, u);
-    }
+    if (!deposits(a)) return;  // uniform
+    const int32_t cnt = *a.count;
+    __syncthreads();
+    if (threadIdx.x == 0) shared_count(a, cnt);
 }
 
 // many chunks, or fallback sums: one workgroup per query (walker), lanes
@@ -225,7 +365,7 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared_finalize_wg(SharedArgs a
 #pragma unroll
     for (int j = 0; j <= D; ++j) acc[j] = 0.0;
     for (int ch = threadIdx.x; ch < a.nchunk; ch += kBlock) {
-        const double *p = a.partial + ((int64_t)ch * a.nq + q) * 4;
+        const double *p = a.partial + ((int64_t)ch * a.rec_ch + q * a.rec_q) * 4;
 #pragma unroll
         for (int j = 0; j <= D; ++j) acc[j] += p[j];
     }
@@ -235,6 +375,7 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared_finalize_wg(SharedArgs a
         shared_finish<D>(a, w, acc, dv);
 #pragma unroll
         for (int d = 0; d < D; ++d) s_coef[d] = -dv[d];
+        if (deposits(a)) shared_count(a, *a.count);  // this thread alone reads the count
     }
     if (!a.do_forces) return;  // uniform
     __syncthreads();
@@ -243,8 +384,8 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared_finalize_wg(SharedArgs a
 
 // The same in one wavefront, for steps that gather forces through the
 // table in kernel-argument form: every load is requested before the first
-// wait (each lane's first chunk record -- lanes past the count re-read the
-// last one and drop it, nchunk >= 1 -- the CV values, the deposit's count
+// wait (each lane's first four chunk records -- lanes past the count re-read
+// the last one and drop it, nchunk >= 1 -- the CV values, the deposit's count
 // and step, and a table row per lane with its Jacobian rows and force; lanes
 // past U re-read row U - 1 and store nothing); the records are summed
 // lane-strided and combined by a butterfly (every lane ends with the same
@@ -257,11 +398,13 @@ __global__ void __launch_bounds__(64) k_hill_shared_finalize_wave(SharedArgs a)
     const int lane = threadIdx.x;
     if (a.fb && !a.fb[w]) return;  // uniform per workgroup
     const int nch = a.nchunk;
-    double r0[1 + D];
-    {
-        const double *p = a.partial + ((int64_t)min(lane, nch - 1) * a.nq + q) * 4;
+    constexpr int RB = 4;  // records of a lane in flight
+    double r0[RB][1 + D];
 #pragma unroll
-        for (int j = 0; j <= D; ++j) r0[j] = p[j];
+    for (int b = 0; b < RB; ++b) {
+        const double *p = a.partial + ((int64_t)min(lane + 64 * b, nch - 1) * a.rec_ch + q * a.rec_q) * 4;
+#pragma unroll
+        for (int j = 0; j <= D; ++j) r0[b][j] = p[j];
     }
     double xi[D];
 #pragma unroll
@@ -274,15 +417,21 @@ __global__ void __launch_bounds__(64) k_hill_shared_finalize_wave(SharedArgs a)
     int32_t cvq[kSmallPer];
     float jr[kSmallPer][3];
     small_rows(a.small, a.J + w * a.nslots * 3, a.F, a.tabs.atom_off[w], min(lane, a.small.U - 1), sg, nent, cvq, jr);
-    // the first record kept or replaced by +0.0 through a bit mask, which
+    // the first records kept or replaced by +0.0 through a bit mask, which
     // uses the loaded value on every lane (a select lets the load move
     // under a branch)
-    const long long keep = lane < nch ? -1LL : 0LL;
     double acc[1 + D];
 #pragma unroll
-    for (int j = 0; j <= D; ++j) acc[j] = 0.0 + __longlong_as_double(__double_as_longlong(r0[j]) & keep);
-    for (int ch = lane + 64; ch < nch; ch += 64) {  // the same order as one loop from ch = lane
-        const double *p = a.partial + ((int64_t)ch * a.nq + q) * 4;
+    for (int j = 0; j <= D; ++j) acc[j] = 0.0;
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        const long long keep = lane + 64 * b < nch ? -1LL : 0LL;
+#pragma unroll
+        for (int j = 0; j <= D; ++j) acc[j] += __longlong_as_double(__double_as_longlong(r0[b][j]) & keep);
+    }
+#pragma unroll 4
+    for (int ch = lane + 64 * RB; ch < nch; ch += 64) {  // the same order as one loop from ch = lane
+        const double *p = a.partial + ((int64_t)ch * a.rec_ch + q * a.rec_q) * 4;
 #pragma unroll
         for (int j = 0; j <= D; ++j) acc[j] += p[j];
     }
@@ -316,6 +465,7 @@ __global__ void __launch_bounds__(64) k_hill_shared_finalize_wave(SharedArgs a)
             } else if (w == 0) {
                 atomicOr(a.flags, kFlagCapacity);
             }
+            shared_count(a, cnt);
         }
     }
     if (lane < a.small.U) {
@@ -457,16 +607,6 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared_qm(SharedArgs a)
     }
 }
 
-// the count of a shared list advances after the finalize kernel (kernel
-// boundary = every lane has read the old count)
-__global__ void k_shared_count(SharedArgs a)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    bool dep = a.deposit == 2;
-    if (a.deposit == 1 && a.stride > 0) dep = (*a.dstep - 1) % a.stride == 0;
-    if (dep && (int64_t)*a.count + a.nq <= a.cap) *a.count = (int32_t)(*a.count + a.nq);
-}
-
 // the one-wavefront finalize: forces through the kernel-argument table of
 // walkers (one query per walker, its records at query w)
 bool small_finalize(const SharedArgs &a)
@@ -475,12 +615,13 @@ bool small_finalize(const SharedArgs &a)
 }
 
 template <int D>
-hipError_t launch_shared_d(const SharedArgs &a, hipStream_t s)
+hipError_t launch_shared_d(const SharedArgs &a, const SharedCv *cv, hipStream_t s)
 {
     if (a.fb) {  // fallback walkers of a surrogate step: query-major sums, finalize per walker
         SharedArgs b = a;
-        b.chunk = kQmChunk;
         b.nchunk = (int32_t)std::max<int64_t>(1, (a.cap + kQmChunk - 1) / kQmChunk);
+        b.rec_ch = a.nq;
+        b.rec_q = 1;
         bool any = false, all = true;
         for (int d = 0; d < D; ++d) {
             any = any || a.period[d] > 0.0;
@@ -506,65 +647,81 @@ hipError_t launch_shared_d(const SharedArgs &a, hipStream_t s)
             hipLaunchKernelGGL((k_hill_shared_finalize_wg<D>), dim3((unsigned)a.nq), dim3(kBlock), 0, s, b);
         return hipGetLastError();
     }
-    // queries per lane: 1 for small query sets (more workgroups), 4 for many
-    const int Q = a.nq >= 65536 ? 4 : 1;
-    dim3 grid(a.nchunk, (unsigned)((a.nq + kQueryLanes * Q - 1) / (kQueryLanes * Q)));
+    SharedArgs b = a;
+    int Q, ql;
+    shared_shape(a.nq, Q, ql);
+    for (b.lg = 0; (ql << b.lg) < 64;) ++b.lg;
+    // many chunks: one wavefront (or workgroup) reads a query's records, kept
+    // next to each other; few: a lane per query reads them chunk after chunk
+    const bool per_query = a.nchunk >= 32;
+    b.rec_ch = per_query ? 1 : a.nq;
+    b.rec_q = per_query ? a.nchunk : 1;
+    const dim3 grid(a.nchunk, (unsigned)((a.nq + ql * Q - 1) / (ql * Q)));
     bool any = false, all = true;
     for (int d = 0; d < D; ++d) {
         any = any || a.period[d] > 0.0;
         all = all && a.period[d] > 0.0;
     }
     const int per = all ? kPerAll : (any ? kPerMixed : kPerNone);
-#define SX_SHARED_LAUNCH(QQ, PP) hipLaunchKernelGGL((k_hill_shared<D, QQ, PP>), grid, dim3(kBlock), 0, s, a)
-    if (Q == 4) {
-        if (per == kPerAll) SX_SHARED_LAUNCH(4, kPerAll);
-        else if (per == kPerNone) SX_SHARED_LAUNCH(4, kPerNone);
-        else SX_SHARED_LAUNCH(4, kPerMixed);
-    } else {
-        if (per == kPerAll) SX_SHARED_LAUNCH(1, kPerAll);
-        else if (per == kPerNone) SX_SHARED_LAUNCH(1, kPerNone);
-        else SX_SHARED_LAUNCH(1, kPerMixed);
+#define SX_SHARED_LAUNCH(QQ)                                                                                       \
+    case QQ:                                                                                                       \
+        if (cv) hipLaunchKernelGGL((k_hill_shared_cv<D, QQ>), grid, dim3(kBlock), 0, s, b, *cv);                   \
+        else if (per == kPerAll) hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerAll>), grid, dim3(kBlock), 0, s, b); \
+        else if (per == kPerNone) hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerNone>), grid, dim3(kBlock), 0, s, b); \
+        else hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerMixed>), grid, dim3(kBlock), 0, s, b);                   \
+        break;
+    if (cv && !all) return hipErrorInvalidValue;  // dihedrals only
+    switch (Q) {
+        SX_SHARED_LAUNCH(1)
+        SX_SHARED_LAUNCH(2)
+        SX_SHARED_LAUNCH(4)
+    default: return hipErrorInvalidValue;
     }
 #undef SX_SHARED_LAUNCH
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.nchunk >= 32 && small_finalize(a))
-        hipLaunchKernelGGL((k_hill_shared_finalize_wave<D>), dim3((unsigned)a.nq), dim3(64), 0, s, a);
-    else if (a.nchunk >= 32)
-        hipLaunchKernelGGL((k_hill_shared_finalize_wg<D>), dim3((unsigned)a.nq), dim3(kBlock), 0, s, a);
+    if (per_query && small_finalize(b))
+        hipLaunchKernelGGL((k_hill_shared_finalize_wave<D>), dim3((unsigned)a.nq), dim3(64), 0, s, b);
+    else if (per_query)
+        hipLaunchKernelGGL((k_hill_shared_finalize_wg<D>), dim3((unsigned)a.nq), dim3(kBlock), 0, s, b);
     else
         hipLaunchKernelGGL((k_hill_shared_finalize<D>), dim3((unsigned)((a.nq + kBlock - 1) / kBlock)), dim3(kBlock),
-                           0, s, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (a.deposit == 2 || (a.deposit == 1 && a.stride > 0)) {
-        hipLaunchKernelGGL(k_shared_count, dim3(1), dim3(64), 0, s, a);
-        e = hipGetLastError();
-    }
-    return e;
+                           0, s, b);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-void shared_split(int64_t cap, int64_t nq, int32_t &chunk, int32_t &nchunk, int32_t target)
+// Every workgroup has an equal share of the hills and the queries, so the
+// chunks are chosen to give each of the 256 CUs the same number of
+// workgroups: k = 4 by default (8 with 4 queries per lane, whose workgroups
+// run for milliseconds), fewer where the capacity has too few stages.  256
+// walkers on 100,000 hills, us per step: 27.6 (k = 1), 23.7 (2), 22.6 (3),
+// 22.8 (4), 24.3 (6), 25.1 (8); 100 walkers on 50,000 hills in three CVs:
+// 14.9 at 2 x 256 workgroups, 16.7 at 548.
+int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target)
 {
-    const int Q = nq >= 65536 ? 4 : 1;
-    const int64_t nqb = std::max<int64_t>(1, (nq + (int64_t)kQueryLanes * Q - 1) / ((int64_t)kQueryLanes * Q));
-    const int64_t stages = std::max<int64_t>(1, (cap + kStage - 1) / kStage);
-    // about `target` workgroups (chunks x query blocks), at least one stage each
-    int64_t nc = std::min<int64_t>(stages, std::max<int64_t>(1, (target + nqb - 1) / nqb));
-    const int64_t per = (stages + nc - 1) / nc;  // stages per chunk
-    chunk = (int32_t)(per * kStage);
-    nchunk = (int32_t)((cap + chunk - 1) / chunk);
-    if (nchunk < 1) nchunk = 1;
+    constexpr int kCus = 256;
+    int Q, ql;
+    shared_shape(nq, Q, ql);
+    if (target <= 0) target = (Q == 4 ? 8 : 4) * kCus;
+    const int64_t nqb = std::max<int64_t>(1, (nq + (int64_t)ql * Q - 1) / ((int64_t)ql * Q));
+    const int64_t most = std::min<int64_t>((cap + kStage - 1) / kStage, kMaxRecords / std::max<int64_t>(1, nq));
+    int64_t nc = target < kCus ? target / nqb : most;
+    for (int64_t k = target / kCus; k >= 1; --k)
+        if (k * kCus / nqb <= most) {
+            nc = k * kCus / nqb;
+            break;
+        }
+    return (int32_t)std::max<int64_t>(1, std::min(nc, most));
 }
 
-hipError_t launch_hill_shared(const SharedArgs &a, hipStream_t s)
+hipError_t launch_hill_shared(const SharedArgs &a, hipStream_t s, const SharedCv *cv)
 {
     switch (a.D) {
-    case 1: return launch_shared_d<1>(a, s);
-    case 2: return launch_shared_d<2>(a, s);
-    case 3: return launch_shared_d<3>(a, s);
+    case 1: return launch_shared_d<1>(a, cv, s);
+    case 2: return launch_shared_d<2>(a, cv, s);
+    case 3: return launch_shared_d<3>(a, cv, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -71,7 +71,7 @@ struct Plan {
     int32_t mg_L = 0, mg_n[kMaxBiasDim] = {0, 0, 0};
     Sub s_mgV, s_mgG, s_mgPend;
     // harmonic windows: sample counts and sums (state), centres (workspace)
-    Sub s_umN, s_umS1, s_umS2, w_hbXi0, w_mgTick;
+    Sub s_umN, s_umS1, s_umS2, w_hbXi0, w_mgTick, w_shTick;
     // ABF momentum estimator: previous W p, bias and flag per walker (state),
     // inverse masses per atom (workspace)
     Sub s_abfWp, s_abfB, s_abfHas, w_invm;
@@ -466,11 +466,9 @@ sx_status make_plan(sx_ctx *c)
     // in batches of kEvalBatch for any list): partial records
     int64_t maxcap = 1;
     for (int w = 0; w < nlists; ++w) maxcap = std::max<int64_t>(maxcap, p.hill_cap[w]);
-    int32_t ch, nch;
     p.shared_records = 0;
     if (c->method == M_METAD) {
-        shared_split(maxcap, kEvalBatch, ch, nch);
-        p.shared_records = (int64_t)nch * kEvalBatch;
+        p.shared_records = (int64_t)shared_chunks(maxcap, kEvalBatch) * kEvalBatch;
         if (c->shared)  // the step's sum at any tuning: at most one chunk per 256-hill stage
             p.shared_records = std::max<int64_t>(p.shared_records, (maxcap + 255) / 256 * (int64_t)p.W);
     }
@@ -561,6 +559,7 @@ sx_status make_plan(sx_ctx *c)
     p.w_tiles = lw.take(sizeof(TileRec) * p.ntiles_max);
     p.w_wrec = lw.take(sizeof(WalkerRec) * p.W);
     p.w_hbXi0 = lw.take(c->method == M_HARMONIC ? sizeof(double) * p.W * p.D : 0);
+    p.w_shTick = lw.take(c->method == M_METAD ? sizeof(int32_t) : 0);
     p.w_mgTick = lw.take(c->mg_on ? sizeof(int32_t) * p.mg_L : 0);
     p.w_invm = lw.take(c->abf_est == 1 ? sizeof(double) * p.total_atoms : 0);
     p.w_slot_atom = lw.take(sizeof(int32_t) * p.nslots);
@@ -702,7 +701,7 @@ HillArgs hill_args(sx_ctx *c, const double *xi)
 
 // Shared-list sum arguments over list `wl` (the shared list, or walker wl's
 // private list) at nq query points xi.
-SharedArgs shared_args(sx_ctx *c, int wl, const double *xi, int64_t nq, int32_t target = kSharedTarget)
+SharedArgs shared_args(sx_ctx *c, int wl, const double *xi, int64_t nq, int32_t target = 0)
 {
     const Plan &p = c->plan;
     SharedArgs a{};
@@ -723,7 +722,8 @@ SharedArgs shared_args(sx_ctx *c, int wl, const double *xi, int64_t nq, int32_t 
     a.xi = xi;
     a.nq = nq;
     a.partial = at<double>(c->ws, p.w_part);
-    shared_split(a.cap, nq, a.chunk, a.nchunk, target);
+    a.nchunk = shared_chunks(a.cap, nq, target);
+    a.tick = at<int32_t>(c->ws, p.w_shTick);
     a.stride = c->stride;
     a.height = c->height;
     a.inv_kdT = c->kdT > 0 && std::isfinite(c->kdT) ? 1.0 / c->kdT : 0.0;
@@ -803,7 +803,7 @@ sx_status enqueue_surrogate_step(sx_ctx *c, const PosView &pv, int64_t step, dou
     }
     hipError_t e = launch_mlp_fwd(mlp_args(c), xi, p.W, V, dV, flag, c->stream, &st);
     if (e == hipSuccess) {
-        SharedArgs a = shared_args(c, 0, xi, p.W, c->grid > 0 ? c->grid : kSharedTarget);
+        SharedArgs a = shared_args(c, 0, xi, p.W, c->grid);
         a.fb = flag;
         a.V_ws = V;
         a.dV_ws = dV;
@@ -938,6 +938,8 @@ sx_status enqueue_step(sx_ctx *c, const void *pos, int32_t dtype, int32_t layout
                            p.small.U > 0 && forces != nullptr && p.nslots <= 4 * kMaxBiasDim;
     // the harmonic kernel evaluates dihedral CVs itself
     const bool fuse_harmonic = c->method == M_HARMONIC && p.all_dihedral;
+    // the shared sum evaluates dihedral CVs itself
+    const bool fuse_shared = c->method == M_METAD && c->shared && !c->mg_on && !c->sg_on && p.all_dihedral;
     if (c->sg_on) return enqueue_surrogate_step(c, pv, step, xi, J, xi_out, V_out, dVdxi_out, forces, layout);
     double *J64 = c->method == M_ABF ? at<double>(c->ws, p.w_J64) : nullptr;
     // ABF in two launches (without FUNN, which reads xi first) sums the
@@ -946,7 +948,7 @@ sx_status enqueue_step(sx_ctx *c, const void *pos, int32_t dtype, int32_t layout
     for (int d = 0; d < p.cs.ncv; ++d) ncn_all += p.cs.cv[d].kind == CV_COORD;
     const bool abf_fold = c->method == M_ABF && p.abf_nblk > 0 && !c->funn_on && ncn_all > 0 &&
                           ncn_all <= kMaxBiasDim;
-    if (!fuse && !fuse_grid && !fuse_harmonic) {
+    if (!fuse && !fuse_grid && !fuse_harmonic && !fuse_shared) {
         sx_status st = launch_cvs(c, pv, xi, J64 ? nullptr : J, J64, !abf_fold);
         if (st != SX_OK) return st;
     }
@@ -972,7 +974,7 @@ sx_status enqueue_step(sx_ctx *c, const void *pos, int32_t dtype, int32_t layout
         if (e != hipSuccess) return hip_fail(c, e, "bias-grid kernels");
         if (sx_status st = cell_forces(c, pv, g.dV_ws, -1.0, forces, layout)) return st;
     } else if (c->method == M_METAD && c->shared) {
-        SharedArgs a = shared_args(c, 0, xi, p.W, c->grid > 0 ? c->grid : kSharedTarget);
+        SharedArgs a = shared_args(c, 0, xi, p.W, c->grid);
         a.V_ws = at<double>(c->ws, p.w_V);
         a.dV_ws = at<double>(c->ws, p.w_dV);
         a.xi_out = xi_out;
@@ -982,7 +984,14 @@ sx_status enqueue_step(sx_ctx *c, const void *pos, int32_t dtype, int32_t layout
         a.count_step = 1;
         a.step = step;
         set_forces(c, a, J, forces, layout);
-        hipError_t e = launch_hill_shared(a, c->stream);
+        SharedCv cv;
+        if (fuse_shared) {
+            cv.cs = p.cs;
+            cv.pos = pv;
+            cv.xi_ws = xi;
+            cv.J_ws = J;
+        }
+        hipError_t e = launch_hill_shared(a, c->stream, fuse_shared ? &cv : nullptr);
         if (e != hipSuccess) return hip_fail(c, e, "shared hill-sum kernels");
         if (sx_status st = cell_forces(c, pv, a.dV_ws, -1.0, forces, layout)) return st;
     } else if (c->method == M_METAD) {

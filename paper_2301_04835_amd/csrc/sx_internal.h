@@ -285,8 +285,11 @@ struct SharedArgs {
     // fallback mode (fb != null): nq = W and only walkers w with fb[w] = 1
     // are summed; walker w's records sit at query index w
     const uint8_t *fb;
-    double *partial;   // nchunk x nq x 4
-    int32_t chunk, nchunk;
+    double *partial;   // nchunk x nq records of 4: record (chunk, query) at chunk rec_ch + query rec_q
+    int64_t rec_ch, rec_q;
+    int32_t nchunk;      // chunks
+    int32_t lg;          // 64 >> lg lanes of a wavefront hold queries (the launcher sets lg and the strides)
+    int32_t *tick;       // workgroups of a depositing finalize that are done (zero between launches)
     double *V_ws, *dV_ws, *xi_out, *V_out, *dV_out;  // may be null
     int32_t deposit, count_step, stride;
     int64_t step;
@@ -299,6 +302,15 @@ struct SharedArgs {
     WalkerTabs tabs;
     ForceView F;
     SmallTabs small;  // the gather table in kernel-argument form (on = 0: the walker tables)
+};
+
+// A shared step whose CVs are all dihedrals: the sum evaluates them from the
+// positions (values into xi_ws, gradients into J_ws).
+struct SharedCv {
+    CvSet cs;
+    PosView pos;
+    double *xi_ws;
+    float *J_ws;
 };
 
 // What a surrogate step adds to the network's forward pass: per-walker
@@ -394,12 +406,11 @@ hipError_t launch_scale_f64(double *x, int64_t n, double a, hipStream_t s);
 hipError_t launch_grid_rebuild(const GridArgs &g, int32_t l0, int32_t nl, hipStream_t s);
 hipError_t launch_grid_eval(const GridArgs &g, int32_t l, const double *xi, int64_t n, double *V, double *dV,
                             hipStream_t s);
-// chunking of a shared-list sum over nq queries: chunk (hills) and count
-// chunking of a shared-list sum: about `target` workgroups, chunks of whole
-// 256-hill stages (nchunk <= ceil(cap / 256))
-constexpr int32_t kSharedTarget = 2048;
-void shared_split(int64_t cap, int64_t nq, int32_t &chunk, int32_t &nchunk, int32_t target = kSharedTarget);
-hipError_t launch_hill_shared(const SharedArgs &a, hipStream_t s);
+// hill chunks of a shared-list sum over nq queries: about `target`
+// workgroups (0: the default), at most one chunk per 256 hills of capacity
+// and at most 8 x 65536 (chunk, query) records unless one chunk has more
+int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target = 0);
+hipError_t launch_hill_shared(const SharedArgs &a, hipStream_t s, const SharedCv *cv = nullptr);
 // cell lists (which & 1), then every cell-list coordination number's value
 // into xi and the gradients of its members (which & 2)
 hipError_t launch_cell_cv(const CellArgs &c, const CvSet &cs, const PosView &pos, double *xi, hipStream_t s,
