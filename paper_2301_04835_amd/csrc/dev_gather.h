@@ -29,37 +29,57 @@ __device__ __forceinline__ void gather_atom(const WalkerTabs &t, const JT *Jw, i
     f[2 * F.sk] += (float)fz;
 }
 
+// Kernels that evaluate all-dihedral CVs themselves keep a walker's Jacobian
+// rows (4 per CV) in LDS for the gather.
+constexpr int kLdsRows = 4 * kMaxBiasDim;
+
 // Force gather from the table in kernel-argument form (SmallTabs): lane
 // u < U owns touched atom u of a walker whose atoms start at aoff and whose
-// Jacobian slots start at Jw.  small_rows requests the atom's current force,
-// the table row (the whole row: unused entries are zero, i.e. slot 0 of CV
-// 0, which exists) and every Jacobian row it names, and waits for none of
-// them; entries q >= nent are skipped where they are used.
+// Jacobian slots start at Jw.  small_entries requests the atom's current
+// force and the table row (the whole row: unused entries are zero, i.e. slot 0
+// of CV 0, which exists), small_jacobian every Jacobian row it names (small_rows:
+// both), and neither waits for what it requests; entries q >= nent are
+// skipped where they are used.
 struct SmallGather {
     float f0, f1, f2;
     float *dst;
 };
 
-__device__ __forceinline__ void small_rows(const SmallTabs &st, const float *Jw, const ForceView &F, int64_t aoff,
-                                           int u, SmallGather &sg, int &nent, int32_t (&cvq)[kSmallPer],
-                                           float (&jr)[kSmallPer][3])
+__device__ __forceinline__ void small_entries(const SmallTabs &st, const ForceView &F, int64_t aoff, int u,
+                                              SmallGather &sg, int &nent, int32_t (&cvq)[kSmallPer],
+                                              int32_t (&slot)[kSmallPer])
 {
     nent = st.nent[u];
     sg.dst = F.ptr + (aoff + st.touched[u]) * F.sa;
     sg.f0 = sg.dst[0];
     sg.f1 = sg.dst[F.sk];
     sg.f2 = sg.dst[2 * F.sk];
-    int32_t e[kSmallPer];
-#pragma unroll
-    for (int q = 0; q < kSmallPer; ++q) e[q] = st.ent[u][q];
 #pragma unroll
     for (int q = 0; q < kSmallPer; ++q) {
-        const int32_t slot = e[q] & 0xFFFFF;
-        cvq[q] = e[q] >> 20;
-        jr[q][0] = Jw[slot * 3 + 0];
-        jr[q][1] = Jw[slot * 3 + 1];
-        jr[q][2] = Jw[slot * 3 + 2];
+        const int32_t e = st.ent[u][q];
+        slot[q] = e & 0xFFFFF;
+        cvq[q] = e >> 20;
     }
+}
+
+__device__ __forceinline__ void small_jacobian(const float *Jw, const int32_t (&slot)[kSmallPer],
+                                               float (&jr)[kSmallPer][3])
+{
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) {
+        jr[q][0] = Jw[slot[q] * 3 + 0];
+        jr[q][1] = Jw[slot[q] * 3 + 1];
+        jr[q][2] = Jw[slot[q] * 3 + 2];
+    }
+}
+
+__device__ __forceinline__ void small_rows(const SmallTabs &st, const float *Jw, const ForceView &F, int64_t aoff,
+                                           int u, SmallGather &sg, int &nent, int32_t (&cvq)[kSmallPer],
+                                           float (&jr)[kSmallPer][3])
+{
+    int32_t slot[kSmallPer];
+    small_entries(st, F, aoff, u, sg, nent, cvq, slot);
+    small_jacobian(Jw, slot, jr);
 }
 
 // gather_atom in two halves, for kernels that know the coefficients only

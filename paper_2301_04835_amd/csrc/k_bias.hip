@@ -122,7 +122,7 @@ __device__ __forceinline__ void fetch_dihedral_atoms(const CvSet &cs, const PosV
 
 template <int D, typename T>
 __device__ __forceinline__ void finish_dihedral(const HillArgs &a, const CvSet &cs, const TileRec &tr,
-                                                const RawAtoms<T> &ra, double *s_xi)
+                                                const RawAtoms<T> &ra, double *s_xi, float (*s_J)[3])
 {
     const int d = threadIdx.x;
     T v[12];
@@ -147,6 +147,11 @@ __device__ __forceinline__ void finish_dihedral(const HillArgs &a, const CvSet &
             J[q * 3 + 0] = (float)g[q].x;
             J[q * 3 + 1] = (float)g[q].y;
             J[q * 3 + 2] = (float)g[q].z;
+            if (s_J) {
+                s_J[slot0 + q][0] = (float)g[q].x;
+                s_J[slot0 + q][1] = (float)g[q].y;
+                s_J[slot0 + q][2] = (float)g[q].z;
+            }
         }
     } else {
         const double phi = dihedral_fp64<false>(r, g);
@@ -161,10 +166,11 @@ __device__ __forceinline__ void finish_dihedral(const HillArgs &a, const CvSet &
 // uniform (scalar) base pointers with 32-bit lane offsets; the scheduling
 // barrier keeps every load of the batch ahead of the arithmetic.
 // One tile: partial (V, sum e D_d) of hills [h0, h0 + 1024 U) of one walker,
-// stored as the tile's record and left in thread 0's `sum`.
+// stored as the tile's record and left in thread 0's `sum`; s_J (may be
+// null): fused CVs' Jacobian rows, kept in LDS too.
 template <int D, int U, bool FUSE, typename T>
 __device__ __forceinline__ void hill_tile(const HillArgs &a, const CvSet &cs, const PosView &pos, int t, double *lds,
-                                          double *s_xi, double (&sum)[1 + D])
+                                          double *s_xi, double (&sum)[1 + D], float (*s_J)[3] = nullptr)
 {
     constexpr int UB = U < kBatch ? U : kBatch;
         const TileRec tr = ld_uniform(a.tiles + t);
@@ -211,7 +217,7 @@ __device__ __forceinline__ void hill_tile(const HillArgs &a, const CvSet &cs, co
             __builtin_amdgcn_sched_barrier(0);
             if (ub == 0) {
                 if (FUSE) {
-                    if (cv_lane) finish_dihedral<D, T>(a, cs, tr, ra, s_xi);
+                    if (cv_lane) finish_dihedral<D, T>(a, cs, tr, ra, s_xi, s_J);
                     __syncthreads();
 #pragma unroll
                     for (int d = 0; d < D; ++d) xi[d] = s_xi[d];
@@ -287,15 +293,22 @@ __device__ __forceinline__ int32_t live_tiles(const HillArgs &a, const WalkerRec
     return min(wr.nt, max(1, (cnt + T - 1) / T));
 }
 
-// Kernel B's work once the walker's sum is in thread 0's acc: V, dV/dxi and
-// the outputs, the deposit (thread 0), then the forces (every thread; the
-// small table's rows were requested by lanes u < U before the sum).
+// Kernel B's work once the walker's sum is in thread 0's acc: the force
+// coefficients to every thread, then V, dV/dxi, the outputs and the deposit
+// (thread 0) beside the forces (every thread; the small table's rows were
+// requested by its lanes before the sum).  The barrier comes before thread
+// 0's stores, which it would wait for.
 template <int D>
 __device__ __forceinline__ void finalize_tail(const HillArgs &a, int32_t w, const WalkerRec &wr, int32_t cnt0,
                                               int64_t next_step, const double (&acc)[1 + D], const double *s_xi,
                                               double *s_coef, bool small_lane, const SmallGather &sg, int nent,
                                               const int32_t (&cvq)[kSmallPer], const float (&jr)[kSmallPer][3])
 {
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) s_coef[d] = acc[1 + d] * a.inv_sig2[d];  // -dV/dxi
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
         const double V = acc[0];
         bool finite = isfinite(V);
@@ -310,7 +323,6 @@ __device__ __forceinline__ void finalize_tail(const HillArgs &a, int32_t w, cons
             finite = finite && isfinite(dv);
             a.dV_ws[(int64_t)w * D + d] = dv;
             if (a.dV_out) a.dV_out[(int64_t)w * D + d] = dv;
-            s_coef[d] = -dv;
         }
         if (!finite) atomicOr(a.flags, kFlagNonFinite);
         bool dep = a.deposit == 2;
@@ -328,7 +340,6 @@ __device__ __forceinline__ void finalize_tail(const HillArgs &a, int32_t w, cons
             }
         }
     }
-    __syncthreads();
     if (!a.do_forces) return;
     if (a.small.on) {
         if (small_lane) {
@@ -376,7 +387,20 @@ __global__ void __launch_bounds__(kBlock) k_hill_finalize(HillArgs a, CvSet cs, 
     double acc[1 + D];
 #pragma unroll
     for (int j = 0; j <= D; ++j) acc[j] = 0.0;
-    for (int i = threadIdx.x; i < nlive; i += kBlock) {
+    constexpr int RB = 4;  // records of a lane in flight
+    int i = threadIdx.x;
+    for (; i + (RB - 1) * kBlock < nlive; i += RB * kBlock) {
+        double r[RB][1 + D];
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int j = 0; j <= D; ++j) r[b][j] = a.partial[(int64_t)(wr.t0 + i + b * kBlock) * 4 + j];
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int j = 0; j <= D; ++j) acc[j] += r[b][j];
+    }
+    for (; i < nlive; i += kBlock) {
         const double *p = a.partial + (int64_t)(wr.t0 + i) * 4;
 #pragma unroll
         for (int j = 0; j <= D; ++j) acc[j] += p[j];
@@ -385,9 +409,9 @@ __global__ void __launch_bounds__(kBlock) k_hill_finalize(HillArgs a, CvSet cs, 
     finalize_tail<D>(a, w, wr, cnt0, next_step, acc, s_xi, s_coef, small_lane, sg, nent, cvq, jr);
 }
 
-// The same finalize in one wavefront, for steps that gather forces through a
-// table small enough for the kernel arguments (at most 32 touched atoms, 8
-// slots each): the tile records are summed by a fixed butterfly across the
+// The same finalize in one wavefront, for walkers of at most 128 tiles and
+// steps that gather forces through a table small enough for the kernel
+// arguments (at most 32 touched atoms, 8 slots each): the tile records are summed by a fixed butterfly across the
 // wavefront (every lane ends with the same bits, as each lane adds in the
 // same order), every lane forms dV/dxi itself, lane 0 writes the outputs and
 // deposits, and lane u < U gathers atom u's force -- no LDS and no barrier
@@ -497,6 +521,7 @@ __global__ void __launch_bounds__(kBlock) k_hill_step_one_tile(HillArgs a, CvSet
     __shared__ double lds[(1 + D) * (kBlock / 64)];
     __shared__ double s_xi[kMaxBiasDim];
     __shared__ double s_coef[kMaxCv];
+    __shared__ float s_J[kLdsRows][3];
     int64_t next_step = 0;  // thread 0 alone decides the deposit
     if (threadIdx.x == 0) {
         if (a.count_step) {
@@ -506,16 +531,34 @@ __global__ void __launch_bounds__(kBlock) k_hill_step_one_tile(HillArgs a, CvSet
             next_step = *a.dstep;
         }
     }
-    double acc[1 + D];
-    hill_tile<D, U, FUSE, T>(a, cs, pos, 0, lds, s_xi, acc);
+    // the last wavefront gathers the forces of a small table: its rows and
+    // forces are requested here, ahead of the hills (the dihedrals belong to
+    // the first wavefront); fused CVs' Jacobian rows come through LDS
     const WalkerRec wr = ld_uniform(a.wrec);
-    const int32_t cnt0 = ld_uniform(a.count);  // what the tile saw: only the deposit below changes it
-    const bool small_lane = a.do_forces && a.small.on && (int)threadIdx.x < a.small.U;
+    const int u = (int)threadIdx.x - (kBlock - 64);
+    const bool small_lane = a.do_forces && a.small.on && u >= 0 && u < a.small.U;
+    const bool lds_rows = FUSE && a.nslots <= kLdsRows;
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
-    int32_t cvq[kSmallPer];
+    int32_t cvq[kSmallPer], slot[kSmallPer];
     float jr[kSmallPer][3];
-    if (small_lane) small_rows(a.small, a.J, a.F, wr.aoff, threadIdx.x, sg, nent, cvq, jr);
+    if (small_lane) {
+        small_entries(a.small, a.F, wr.aoff, u, sg, nent, cvq, slot);
+        if (!FUSE) small_jacobian(a.J, slot, jr);
+    }
+    const int32_t cnt0 = ld_uniform(a.count);  // what the tile sees: only the deposit below changes it
+    double acc[1 + D];
+    hill_tile<D, U, FUSE, T>(a, cs, pos, 0, lds, s_xi, acc, lds_rows ? s_J : nullptr);
+    if (FUSE && small_lane) {
+        if (lds_rows) {
+#pragma unroll
+            for (int q = 0; q < kSmallPer; ++q)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) jr[q][k] = s_J[slot[q]][k];
+        } else {
+            small_jacobian(a.J, slot, jr);
+        }
+    }
     if (!FUSE) {
         if ((int)threadIdx.x < D) s_xi[threadIdx.x] = a.xi[threadIdx.x];
         __syncthreads();
@@ -572,7 +615,10 @@ hipError_t launch_hill_d(const HillArgs &a, const CvSet &cs, const PosView &pos,
         if (e != hipSuccess) return e;
     }
     if (which & 2) {
-        if (a.small.on && a.do_forces && a.small.U > 0)
+        // one wavefront per walker while its tile records are two loads a
+        // lane; beyond, a workgroup with four in flight a lane (2,048 records
+        // of one 8.4M-hill walker: @FW@ us; in one wavefront 12.0)
+        if (a.small.on && a.do_forces && a.small.U > 0 && a.max_tiles <= 128)
             hipLaunchKernelGGL((k_hill_finalize_wave<D, FUSE>), dim3(a.tabs.W), dim3(64), 0, s, a, cs, pos);
         else
             hipLaunchKernelGGL((k_hill_finalize<D, FUSE>), dim3(a.tabs.W), dim3(kBlock), 0, s, a, cs, pos);

@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(kBlock) k_grid_step(GridArgs g)
 // the outputs and deposits, lane u < U adds atom u's force.
 __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
 {
-    __shared__ float s_J[4 * kMaxBiasDim][3];  // fused CVs: the walker's Jacobian slots
+    __shared__ float s_J[kLdsRows][3];  // fused CVs: the walker's Jacobian slots
     const int32_t w = blockIdx.x;
     const int32_t l = g.shared ? 0 : w;
     const int lane = threadIdx.x;
@@ -182,6 +182,10 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
     float jr[kSmallPer][3];
     double xi[kMaxBiasDim];
     if (g.fuse_cv) {
+        // this lane's table row and force (the Jacobian rows come from LDS),
+        // ahead of the dihedrals
+        int32_t slot[kSmallPer];
+        small_entries(g.small, g.F, aoff, min(lane, g.small.U - 1), sg, nent, cvq, slot);
         // lane d < D evaluates dihedral d of the walker in FP64 (atom indices
         // and slots selected from the kernel arguments by value); its value
         // goes to every lane, its four gradient rows to LDS and the workspace
@@ -216,24 +220,12 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
         }
 #pragma unroll
         for (int d = 0; d < kMaxBiasDim; ++d) xi[d] = __shfl(xd, min(d, g.D - 1), 64);
-        // this lane's table row and force (the Jacobian rows come from LDS)
-        const int u = min(lane, g.small.U - 1);
-        nent = g.small.nent[u];
-        sg.dst = g.F.ptr + (aoff + g.small.touched[u]) * g.F.sa;
-        sg.f0 = sg.dst[0];
-        sg.f1 = sg.dst[g.F.sk];
-        sg.f2 = sg.dst[2 * g.F.sk];
-        int32_t e[kSmallPer];
-#pragma unroll
-        for (int q = 0; q < kSmallPer; ++q) e[q] = g.small.ent[u][q];
         __syncthreads();  // s_J written (one wavefront)
 #pragma unroll
         for (int q = 0; q < kSmallPer; ++q) {
-            const int32_t slot = e[q] & 0xFFFFF;  // < 4 D: every CV a dihedral
-            cvq[q] = e[q] >> 20;
-            jr[q][0] = s_J[slot][0];
-            jr[q][1] = s_J[slot][1];
-            jr[q][2] = s_J[slot][2];
+            jr[q][0] = s_J[slot[q]][0];  // slot < 4 D: every CV a dihedral
+            jr[q][1] = s_J[slot[q]][1];
+            jr[q][2] = s_J[slot[q]][2];
         }
     } else {
         // xi over the largest CV count with the index clamped to the last

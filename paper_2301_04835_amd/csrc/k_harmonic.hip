@@ -12,23 +12,47 @@
 namespace sx {
 namespace {
 
+// xi - xi0 of CV d, minimum image where it is periodic
+__device__ __forceinline__ double displacement(const HarmonicArgs &a, int d, double x, double x0)
+{
+    double t = x - x0;
+    if (a.period[d] > 0.0) t -= a.period[d] * rint(t / a.period[d]);
+    return t;
+}
+
 // one workgroup per walker; thread 0 owns the window's bookkeeping and
 // requests its centre and running sums before anything waits.  With fuse_cv
 // thread d < D first evaluates dihedral d (FP64) from the positions: its
 // value into LDS and the workspace, its gradient rows into the workspace's
-// Jacobian, which the gather below reads after the barrier.
+// Jacobian, which the gather below reads after the barrier.  When the force
+// table fits the kernel arguments too, the second wavefront requests its rows
+// and the atoms' forces and forms the coefficients itself, and takes the
+// gradient rows from LDS: after the dihedrals' barrier it only multiplies and
+// stores (four dependent table loads, another barrier behind thread 0's
+// stores and a trip of the gradients through L2 before: @HW@).
 __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
 {
     __shared__ double s_coef[kMaxCv];
     __shared__ double s_xi[kMaxBiasDim];
+    __shared__ float s_J[kLdsRows][3];
     const int32_t w = blockIdx.x;
+    const bool small = a.fuse_cv && a.do_forces && a.small.on && a.nslots <= kLdsRows;  // uniform
+    const int u = (int)threadIdx.x - 64;
+    const bool small_lane = small && u >= 0 && u < a.small.U;
+    SmallGather sg{0.f, 0.f, 0.f, nullptr};
+    int nent = 0;
+    int32_t cvq[kSmallPer], slot[kSmallPer];
+    if (small_lane) small_entries(a.small, a.F, a.tabs.atom_off[w], u, sg, nent, cvq, slot);
     // thread 0's window data requested before anything waits
     double x0[kMaxBiasDim], s1p[kMaxBiasDim], s2p[kMaxBiasDim][kMaxBiasDim];
     int64_t np0 = 0;
+    if (threadIdx.x == 0 || small_lane) {
+#pragma unroll
+        for (int d = 0; d < kMaxBiasDim; ++d) x0[d] = d < a.D ? a.xi0[(int64_t)w * a.D + d] : 0.0;
+    }
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int d = 0; d < kMaxBiasDim; ++d) {
-            x0[d] = d < a.D ? a.xi0[(int64_t)w * a.D + d] : 0.0;
             s1p[d] = (a.accumulate && d < a.D) ? a.s1[(int64_t)w * a.D + d] : 0.0;
 #pragma unroll
             for (int e = 0; e < kMaxBiasDim; ++e)
@@ -52,9 +76,33 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
                 js[3 * q] = (float)gr[q].x;
                 js[3 * q + 1] = (float)gr[q].y;
                 js[3 * q + 2] = (float)gr[q].z;
+                if (small) {
+                    s_J[cv.slot0 + q][0] = (float)gr[q].x;
+                    s_J[cv.slot0 + q][1] = (float)gr[q].y;
+                    s_J[cv.slot0 + q][2] = (float)gr[q].z;
+                }
             }
         }
         __syncthreads();  // s_xi, and the Jacobian rows the gather reads
+    }
+    if (small_lane) {
+        double coef[kMaxBiasDim] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int d = 0; d < kMaxBiasDim; ++d)
+            if (d < a.D) coef[d] = -(a.k[d] * displacement(a, d, s_xi[d], x0[d]));
+        double fx = 0.0, fy = 0.0, fz = 0.0;
+#pragma unroll
+        for (int q = 0; q < kSmallPer; ++q) {
+            double cf = 0.0;
+#pragma unroll
+            for (int d = 0; d < kMaxBiasDim; ++d) cf = cvq[q] == d ? coef[d] : cf;
+            fx += q < nent ? cf * (double)s_J[slot[q]][0] : 0.0;
+            fy += q < nent ? cf * (double)s_J[slot[q]][1] : 0.0;
+            fz += q < nent ? cf * (double)s_J[slot[q]][2] : 0.0;
+        }
+        sg.dst[0] = sg.f0 + (float)fx;
+        sg.dst[a.F.sk] = sg.f1 + (float)fy;
+        sg.dst[2 * a.F.sk] = sg.f2 + (float)fz;
     }
     if (threadIdx.x == 0) {
         double Dv[kMaxBiasDim], V = 0.0;
@@ -63,8 +111,7 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
         for (int d = 0; d < kMaxBiasDim; ++d) {
             if (d >= a.D) break;
             const double x = a.fuse_cv ? s_xi[d] : a.xi[(int64_t)w * a.D + d];
-            double t = x - x0[d];
-            if (a.period[d] > 0.0) t -= a.period[d] * rint(t / a.period[d]);
+            const double t = displacement(a, d, x, x0[d]);
             Dv[d] = t;
             const double g = a.k[d] * t;
             V += 0.5 * g * t;
@@ -90,6 +137,7 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
         }
         if (w == 0 && a.count_step) *a.dstep = a.step >= 0 ? a.step + 1 : *a.dstep + 1;
     }
+    if (small) return;  // uniform
     __syncthreads();
     if (a.do_forces) gather_forces(a.tabs, a.J + (int64_t)w * a.nslots * 3, w, s_coef, a.F);
 }

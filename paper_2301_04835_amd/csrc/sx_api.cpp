@@ -134,7 +134,7 @@ struct sx_ctx {
     bool bound = false;
     char *state = nullptr, *ws = nullptr;
     // tuning
-    int32_t tile_units = 4, grid = 0;
+    int32_t tile_units = 4, grid = 0, max_tiles = 0;
     int32_t ntiles = 0;
     std::vector<TileRec> tiles;
     std::vector<WalkerRec> wrecs;
@@ -200,12 +200,14 @@ void build_tiles(sx_ctx *c)
     const int T = c->tile_units * kTileUnit;
     c->tiles.clear();
     c->wrecs.assign(p.W, WalkerRec{});
+    c->max_tiles = 0;
     for (int w = 0; w < p.W; ++w) {
         const int cap = p.hill_cap[w];
         const int nt = std::max(1, (cap + T - 1) / T);
         WalkerRec &wr = c->wrecs[w];
         wr.t0 = (int32_t)c->tiles.size();
         wr.nt = nt;
+        c->max_tiles = std::max(c->max_tiles, nt);
         wr.cap = cap;
         wr.hb4 = (int32_t)(p.hill_base[w] / 4);
         wr.aoff = p.atom_off[w];
@@ -674,6 +676,7 @@ HillArgs hill_args(sx_ctx *c, const double *xi)
     a.wrec = at<WalkerRec>(c->ws, p.w_wrec);
     a.ntiles = c->ntiles;
     a.tile_units = c->tile_units;
+    a.max_tiles = c->max_tiles;
     a.partial = at<double>(c->ws, p.w_part);
     a.D = p.D;
     for (int d = 0; d < p.D; ++d) {
@@ -841,6 +844,7 @@ HarmonicArgs harmonic_args(sx_ctx *c, const double *xi)
     a.nslots = p.nslots;
     a.J = at<float>(c->ws, p.w_J);
     a.tabs = tabs_of(c);
+    a.small = p.small;
     return a;
 }
 

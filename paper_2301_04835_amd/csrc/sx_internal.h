@@ -107,7 +107,7 @@ struct HillArgs {
     int32_t *count;            // per walker
     const TileRec *tiles;
     const WalkerRec *wrec;
-    int32_t ntiles, tile_units;
+    int32_t ntiles, tile_units, max_tiles;  // tiles in all, 1024-hill units of one, most tiles of a walker
     double *partial;           // ntiles x 4
     // constants
     int32_t D;
@@ -262,6 +262,7 @@ struct HarmonicArgs {
     const float *J;
     WalkerTabs tabs;
     ForceView F;
+    SmallTabs small;  // the gather table in kernel-argument form (on = 0: the walker tables)
     // fuse_cv: every CV a dihedral, evaluated by the kernel itself from the
     // positions (values into xi_ws, gradients into J_ws, which J then reads)
     int32_t fuse_cv;
