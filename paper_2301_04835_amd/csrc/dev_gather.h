@@ -36,50 +36,73 @@ constexpr int kLdsRows = 4 * kMaxBiasDim;
 // Force gather from the table in kernel-argument form (SmallTabs): lane
 // u < U owns touched atom u of a walker whose atoms start at aoff and whose
 // Jacobian slots start at Jw.  small_entries requests the atom's current
-// force and the table row (the whole row: unused entries are zero, i.e. slot 0
-// of CV 0, which exists), small_jacobian every Jacobian row it names (small_rows:
-// both), and neither waits for what it requests; entries q >= nent are
-// skipped where they are used.
+// force and the table row, small_jacobian every Jacobian row it names
+// (small_rows: both), and neither waits for what it requests.  Only the rows
+// of the table's first `most` entries are read and summed (a uniform bound:
+// two for dihedrals that share atoms); a row's entries between its own nent
+// and that are zero, i.e. slot 0 of CV 0, which exists, and small_forces skips
+// them.
 struct SmallGather {
     float f0, f1, f2;
     float *dst;
 };
 
+// e: the row's entries as stored (slot | cv << 20), decoded where they are
+// used: decoding them here would wait for each in turn
 __device__ __forceinline__ void small_entries(const SmallTabs &st, const ForceView &F, int64_t aoff, int u,
-                                              SmallGather &sg, int &nent, int32_t (&cvq)[kSmallPer],
-                                              int32_t (&slot)[kSmallPer])
+                                              SmallGather &sg, int &nent, int32_t (&e)[kSmallPer])
 {
     nent = st.nent[u];
     sg.dst = F.ptr + (aoff + st.touched[u]) * F.sa;
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) e[q] = st.ent[u][q];  // two wide loads
     sg.f0 = sg.dst[0];
     sg.f1 = sg.dst[F.sk];
     sg.f2 = sg.dst[2 * F.sk];
-#pragma unroll
-    for (int q = 0; q < kSmallPer; ++q) {
-        const int32_t e = st.ent[u][q];
-        slot[q] = e & 0xFFFFF;
-        cvq[q] = e >> 20;
-    }
 }
 
-__device__ __forceinline__ void small_jacobian(const float *Jw, const int32_t (&slot)[kSmallPer],
+// Jw: the walker's rows in memory, three floats each (or in LDS, &s_J[0][0])
+__device__ __forceinline__ void small_jacobian(const SmallTabs &st, const float *Jw, const int32_t (&e)[kSmallPer],
                                                float (&jr)[kSmallPer][3])
 {
 #pragma unroll
     for (int q = 0; q < kSmallPer; ++q) {
-        jr[q][0] = Jw[slot[q] * 3 + 0];
-        jr[q][1] = Jw[slot[q] * 3 + 1];
-        jr[q][2] = Jw[slot[q] * 3 + 2];
+        if (q >= st.most) continue;
+        const float *js = Jw + (e[q] & 0xFFFFF) * 3;
+        jr[q][0] = js[0];
+        jr[q][1] = js[1];
+        jr[q][2] = js[2];
     }
 }
 
 __device__ __forceinline__ void small_rows(const SmallTabs &st, const float *Jw, const ForceView &F, int64_t aoff,
-                                           int u, SmallGather &sg, int &nent, int32_t (&cvq)[kSmallPer],
+                                           int u, SmallGather &sg, int &nent, int32_t (&e)[kSmallPer],
                                            float (&jr)[kSmallPer][3])
 {
-    int32_t slot[kSmallPer];
-    small_entries(st, F, aoff, u, sg, nent, cvq, slot);
-    small_jacobian(Jw, slot, jr);
+    small_entries(st, F, aoff, u, sg, nent, e);
+    small_jacobian(st, Jw, e, jr);
+}
+
+// the atom's force: its old value plus sum coef[cv] J over its entries
+template <int N>
+__device__ __forceinline__ void small_forces(const SmallTabs &st, const ForceView &F, const SmallGather &sg, int nent,
+                                             const int32_t (&e)[kSmallPer], const float (&jr)[kSmallPer][3],
+                                             const double (&coef)[N])
+{
+    double fx = 0.0, fy = 0.0, fz = 0.0;
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) {
+        if (q >= st.most) continue;
+        double cf = 0.0;
+#pragma unroll
+        for (int d = 0; d < N; ++d) cf = (e[q] >> 20) == d ? coef[d] : cf;
+        fx += q < nent ? cf * (double)jr[q][0] : 0.0;
+        fy += q < nent ? cf * (double)jr[q][1] : 0.0;
+        fz += q < nent ? cf * (double)jr[q][2] : 0.0;
+    }
+    sg.dst[0] = sg.f0 + (float)fx;
+    sg.dst[F.sk] = sg.f1 + (float)fy;
+    sg.dst[2 * F.sk] = sg.f2 + (float)fz;
 }
 
 // gather_atom in two halves, for kernels that know the coefficients only

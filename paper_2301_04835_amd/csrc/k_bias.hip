@@ -302,7 +302,7 @@ template <int D>
 __device__ __forceinline__ void finalize_tail(const HillArgs &a, int32_t w, const WalkerRec &wr, int32_t cnt0,
                                               int64_t next_step, const double (&acc)[1 + D], const double *s_xi,
                                               double *s_coef, bool small_lane, const SmallGather &sg, int nent,
-                                              const int32_t (&cvq)[kSmallPer], const float (&jr)[kSmallPer][3])
+                                              const int32_t (&ent)[kSmallPer], const float (&jr)[kSmallPer][3])
 {
     if (threadIdx.x == 0) {
 #pragma unroll
@@ -343,17 +343,10 @@ __device__ __forceinline__ void finalize_tail(const HillArgs &a, int32_t w, cons
     if (!a.do_forces) return;
     if (a.small.on) {
         if (small_lane) {
-            double fx = 0.0, fy = 0.0, fz = 0.0;
+            double coef[D];
 #pragma unroll
-            for (int q = 0; q < kSmallPer; ++q) {
-                const double cf = s_coef[cvq[q]];
-                fx += q < nent ? cf * (double)jr[q][0] : 0.0;
-                fy += q < nent ? cf * (double)jr[q][1] : 0.0;
-                fz += q < nent ? cf * (double)jr[q][2] : 0.0;
-            }
-            sg.dst[0] = sg.f0 + (float)fx;
-            sg.dst[a.F.sk] = sg.f1 + (float)fy;
-            sg.dst[2 * a.F.sk] = sg.f2 + (float)fz;
+            for (int d = 0; d < D; ++d) coef[d] = s_coef[d];
+            small_forces(a.small, a.F, sg, nent, ent, jr, coef);
         }
     } else {
         gather_forces(a.tabs, a.J + (int64_t)w * a.nslots * 3, w, s_coef, a.F);
@@ -379,10 +372,10 @@ __global__ void __launch_bounds__(kBlock) k_hill_finalize(HillArgs a, CvSet cs, 
     const bool small_lane = a.do_forces && a.small.on && (int)threadIdx.x < a.small.U;
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
-    int32_t cvq[kSmallPer];
+    int32_t ent[kSmallPer];
     float jr[kSmallPer][3];
     if (small_lane)
-        small_rows(a.small, a.J + (int64_t)w * a.nslots * 3, a.F, wr.aoff, threadIdx.x, sg, nent, cvq, jr);
+        small_rows(a.small, a.J + (int64_t)w * a.nslots * 3, a.F, wr.aoff, threadIdx.x, sg, nent, ent, jr);
     if ((int)threadIdx.x < D) s_xi[threadIdx.x] = (FUSE ? a.xi_save : a.xi)[(int64_t)w * D + threadIdx.x];
     double acc[1 + D];
 #pragma unroll
@@ -406,7 +399,7 @@ __global__ void __launch_bounds__(kBlock) k_hill_finalize(HillArgs a, CvSet cs, 
         for (int j = 0; j <= D; ++j) acc[j] += p[j];
     }
     block_sum0<1 + D>(acc, lds);  // also orders the s_xi writes
-    finalize_tail<D>(a, w, wr, cnt0, next_step, acc, s_xi, s_coef, small_lane, sg, nent, cvq, jr);
+    finalize_tail<D>(a, w, wr, cnt0, next_step, acc, s_xi, s_coef, small_lane, sg, nent, ent, jr);
 }
 
 // The same finalize in one wavefront, for walkers of at most 128 tiles and
@@ -428,7 +421,7 @@ __global__ void __launch_bounds__(64) k_hill_finalize_wave(HillArgs a, CvSet cs,
     const bool small_lane = lane < a.small.U;  // launched only when forces are gathered
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
-    int32_t cvq[kSmallPer];
+    int32_t ent[kSmallPer];
     float jr[kSmallPer][3];
     // requested before anything waits, with no branch between the loads:
     // the first tile record of each lane (lanes past the walker's live tiles
@@ -445,7 +438,7 @@ __global__ void __launch_bounds__(64) k_hill_finalize_wave(HillArgs a, CvSet cs,
     double xi[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) xi[d] = (FUSE ? a.xi_save : a.xi)[(int64_t)w * D + d];
-    small_rows(a.small, a.J + (int64_t)w * a.nslots * 3, a.F, wr.aoff, min(lane, a.small.U - 1), sg, nent, cvq, jr);
+    small_rows(a.small, a.J + (int64_t)w * a.nslots * 3, a.F, wr.aoff, min(lane, a.small.U - 1), sg, nent, ent, jr);
     // the record is kept or replaced by +0.0 through a bit mask, which uses
     // the loaded value on every lane (a select lets the load move under a branch)
     const long long keep = lane < nlive ? -1LL : 0LL;
@@ -493,21 +486,7 @@ __global__ void __launch_bounds__(64) k_hill_finalize_wave(HillArgs a, CvSet cs,
             }
         }
     }
-    if (small_lane) {
-        double fx = 0.0, fy = 0.0, fz = 0.0;
-#pragma unroll
-        for (int q = 0; q < kSmallPer; ++q) {
-            double cf = 0.0;
-#pragma unroll
-            for (int d = 0; d < D; ++d) cf = cvq[q] == d ? coef[d] : cf;
-            fx += q < nent ? cf * (double)jr[q][0] : 0.0;
-            fy += q < nent ? cf * (double)jr[q][1] : 0.0;
-            fz += q < nent ? cf * (double)jr[q][2] : 0.0;
-        }
-        sg.dst[0] = sg.f0 + (float)fx;
-        sg.dst[a.F.sk] = sg.f1 + (float)fy;
-        sg.dst[2 * a.F.sk] = sg.f2 + (float)fz;
-    }
+    if (small_lane) small_forces(a.small, a.F, sg, nent, ent, jr, coef);
 }
 
 // The whole step in one launch when all the hills are one tile (one walker
@@ -540,30 +519,26 @@ __global__ void __launch_bounds__(kBlock) k_hill_step_one_tile(HillArgs a, CvSet
     const bool lds_rows = FUSE && a.nslots <= kLdsRows;
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
-    int32_t cvq[kSmallPer], slot[kSmallPer];
+    int32_t ent[kSmallPer];
     float jr[kSmallPer][3];
     if (small_lane) {
-        small_entries(a.small, a.F, wr.aoff, u, sg, nent, cvq, slot);
-        if (!FUSE) small_jacobian(a.J, slot, jr);
+        small_entries(a.small, a.F, wr.aoff, u, sg, nent, ent);
+        if (!FUSE) small_jacobian(a.small, a.J, ent, jr);
     }
     const int32_t cnt0 = ld_uniform(a.count);  // what the tile sees: only the deposit below changes it
     double acc[1 + D];
     hill_tile<D, U, FUSE, T>(a, cs, pos, 0, lds, s_xi, acc, lds_rows ? s_J : nullptr);
     if (FUSE && small_lane) {
-        if (lds_rows) {
-#pragma unroll
-            for (int q = 0; q < kSmallPer; ++q)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) jr[q][k] = s_J[slot[q]][k];
-        } else {
-            small_jacobian(a.J, slot, jr);
-        }
+        if (lds_rows)
+            small_jacobian(a.small, &s_J[0][0], ent, jr);
+        else
+            small_jacobian(a.small, a.J, ent, jr);
     }
     if (!FUSE) {
         if ((int)threadIdx.x < D) s_xi[threadIdx.x] = a.xi[threadIdx.x];
         __syncthreads();
     }
-    finalize_tail<D>(a, 0, wr, cnt0, next_step, acc, s_xi, s_coef, small_lane, sg, nent, cvq, jr);
+    finalize_tail<D>(a, 0, wr, cnt0, next_step, acc, s_xi, s_coef, small_lane, sg, nent, ent, jr);
 }
 
 template <int D, bool FUSE, typename T>
@@ -617,7 +592,7 @@ hipError_t launch_hill_d(const HillArgs &a, const CvSet &cs, const PosView &pos,
     if (which & 2) {
         // one wavefront per walker while its tile records are two loads a
         // lane; beyond, a workgroup with four in flight a lane (2,048 records
-        // of one 8.4M-hill walker: @FW@ us; in one wavefront 12.0)
+        // of one 8.4M-hill walker: 5.2 us; in one wavefront 12.0)
         if (a.small.on && a.do_forces && a.small.U > 0 && a.max_tiles <= 128)
             hipLaunchKernelGGL((k_hill_finalize_wave<D, FUSE>), dim3(a.tabs.W), dim3(64), 0, s, a, cs, pos);
         else

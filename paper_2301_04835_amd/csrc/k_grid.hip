@@ -178,14 +178,13 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
     const int64_t aoff = g.tabs.atom_off[w];
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
-    int32_t cvq[kSmallPer];
+    int32_t ent[kSmallPer];
     float jr[kSmallPer][3];
     double xi[kMaxBiasDim];
     if (g.fuse_cv) {
         // this lane's table row and force (the Jacobian rows come from LDS),
         // ahead of the dihedrals
-        int32_t slot[kSmallPer];
-        small_entries(g.small, g.F, aoff, min(lane, g.small.U - 1), sg, nent, cvq, slot);
+        small_entries(g.small, g.F, aoff, min(lane, g.small.U - 1), sg, nent, ent);
         // lane d < D evaluates dihedral d of the walker in FP64 (atom indices
         // and slots selected from the kernel arguments by value); its value
         // goes to every lane, its four gradient rows to LDS and the workspace
@@ -221,19 +220,14 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
 #pragma unroll
         for (int d = 0; d < kMaxBiasDim; ++d) xi[d] = __shfl(xd, min(d, g.D - 1), 64);
         __syncthreads();  // s_J written (one wavefront)
-#pragma unroll
-        for (int q = 0; q < kSmallPer; ++q) {
-            jr[q][0] = s_J[slot[q]][0];  // slot < 4 D: every CV a dihedral
-            jr[q][1] = s_J[slot[q]][1];
-            jr[q][2] = s_J[slot[q]][2];
-        }
+        small_jacobian(g.small, &s_J[0][0], ent, jr);  // slot < 4 D: every CV a dihedral
     } else {
         // xi over the largest CV count with the index clamped to the last
         // CV (in bounds, the extra entries unused), so the loads are issued
         // together
 #pragma unroll
         for (int d = 0; d < kMaxBiasDim; ++d) xi[d] = g.xi[(int64_t)w * g.D + min(d, g.D - 1)];
-        small_rows(g.small, g.J + (int64_t)w * g.nslots * 3, g.F, aoff, min(lane, g.small.U - 1), sg, nent, cvq, jr);
+        small_rows(g.small, g.J + (int64_t)w * g.nslots * 3, g.F, aoff, min(lane, g.small.U - 1), sg, nent, ent, jr);
     }
     int32_t i0[kMaxBiasDim], i1[kMaxBiasDim];
     double t[kMaxBiasDim];
@@ -289,19 +283,10 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
         }
     }
     if (lane < g.small.U) {
-        double fx = 0.0, fy = 0.0, fz = 0.0;
+        double coef[kMaxBiasDim];
 #pragma unroll
-        for (int q = 0; q < kSmallPer; ++q) {
-            double cf = 0.0;
-#pragma unroll
-            for (int d = 0; d < kMaxBiasDim; ++d) cf = (d < g.D && cvq[q] == d) ? -G[d] : cf;
-            fx += q < nent ? cf * (double)jr[q][0] : 0.0;
-            fy += q < nent ? cf * (double)jr[q][1] : 0.0;
-            fz += q < nent ? cf * (double)jr[q][2] : 0.0;
-        }
-        sg.dst[0] = sg.f0 + (float)fx;
-        sg.dst[g.F.sk] = sg.f1 + (float)fy;
-        sg.dst[2 * g.F.sk] = sg.f2 + (float)fz;
+        for (int d = 0; d < kMaxBiasDim; ++d) coef[d] = -G[d];
+        small_forces(g.small, g.F, sg, nent, ent, jr, coef);
     }
 }
 

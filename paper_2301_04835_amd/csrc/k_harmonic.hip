@@ -29,7 +29,8 @@ __device__ __forceinline__ double displacement(const HarmonicArgs &a, int d, dou
 // and the atoms' forces and forms the coefficients itself, and takes the
 // gradient rows from LDS: after the dihedrals' barrier it only multiplies and
 // stores (four dependent table loads, another barrier behind thread 0's
-// stores and a trip of the gradients through L2 before: @HW@).
+// stores and a trip of the gradients through L2 before: 256 windows 5.93 us,
+// now 5.66).
 __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
 {
     __shared__ double s_coef[kMaxCv];
@@ -41,8 +42,8 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
     const bool small_lane = small && u >= 0 && u < a.small.U;
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
-    int32_t cvq[kSmallPer], slot[kSmallPer];
-    if (small_lane) small_entries(a.small, a.F, a.tabs.atom_off[w], u, sg, nent, cvq, slot);
+    int32_t ent[kSmallPer];
+    if (small_lane) small_entries(a.small, a.F, a.tabs.atom_off[w], u, sg, nent, ent);
     // thread 0's window data requested before anything waits
     double x0[kMaxBiasDim], s1p[kMaxBiasDim], s2p[kMaxBiasDim][kMaxBiasDim];
     int64_t np0 = 0;
@@ -62,24 +63,35 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
     }
     if (a.fuse_cv) {
         if ((int)threadIdx.x < a.D) {
-            const CvDesc &cv = a.cs.cv[threadIdx.x];
+            // atom indices and slot selected by value from the kernel
+            // arguments: no load between them and the positions
+            int32_t at[4], slot0 = a.cs.cv[0].slot0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) at[q] = a.cs.cv[0].atom[q];
+#pragma unroll
+            for (int d = 1; d < kMaxBiasDim; ++d) {
+                const bool me = (int)threadIdx.x == d;
+                slot0 = me ? a.cs.cv[d].slot0 : slot0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) at[q] = me ? a.cs.cv[d].atom[q] : at[q];
+            }
             const int64_t aoff = a.tabs.atom_off[w];
             double3 r[4], gr[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) r[q] = ld_pos(a.pos, aoff + cv.atom[q]);
+            for (int q = 0; q < 4; ++q) r[q] = ld_pos(a.pos, aoff + at[q]);
             const double x = dihedral_fp64<true>(r, gr);
             s_xi[threadIdx.x] = x;
             a.xi_ws[(int64_t)w * a.D + threadIdx.x] = x;
-            float *js = a.J_ws + ((int64_t)w * a.nslots + cv.slot0) * 3;
+            float *js = a.J_ws + ((int64_t)w * a.nslots + slot0) * 3;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 js[3 * q] = (float)gr[q].x;
                 js[3 * q + 1] = (float)gr[q].y;
                 js[3 * q + 2] = (float)gr[q].z;
                 if (small) {
-                    s_J[cv.slot0 + q][0] = (float)gr[q].x;
-                    s_J[cv.slot0 + q][1] = (float)gr[q].y;
-                    s_J[cv.slot0 + q][2] = (float)gr[q].z;
+                    s_J[slot0 + q][0] = (float)gr[q].x;
+                    s_J[slot0 + q][1] = (float)gr[q].y;
+                    s_J[slot0 + q][2] = (float)gr[q].z;
                 }
             }
         }
@@ -90,19 +102,9 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
 #pragma unroll
         for (int d = 0; d < kMaxBiasDim; ++d)
             if (d < a.D) coef[d] = -(a.k[d] * displacement(a, d, s_xi[d], x0[d]));
-        double fx = 0.0, fy = 0.0, fz = 0.0;
-#pragma unroll
-        for (int q = 0; q < kSmallPer; ++q) {
-            double cf = 0.0;
-#pragma unroll
-            for (int d = 0; d < kMaxBiasDim; ++d) cf = cvq[q] == d ? coef[d] : cf;
-            fx += q < nent ? cf * (double)s_J[slot[q]][0] : 0.0;
-            fy += q < nent ? cf * (double)s_J[slot[q]][1] : 0.0;
-            fz += q < nent ? cf * (double)s_J[slot[q]][2] : 0.0;
-        }
-        sg.dst[0] = sg.f0 + (float)fx;
-        sg.dst[a.F.sk] = sg.f1 + (float)fy;
-        sg.dst[2 * a.F.sk] = sg.f2 + (float)fz;
+        float jr[kSmallPer][3];
+        small_jacobian(a.small, &s_J[0][0], ent, jr);
+        small_forces(a.small, a.F, sg, nent, ent, jr, coef);
     }
     if (threadIdx.x == 0) {
         double Dv[kMaxBiasDim], V = 0.0;

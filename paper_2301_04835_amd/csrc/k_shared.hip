@@ -414,9 +414,9 @@ __global__ void __launch_bounds__(64) k_hill_shared_finalize_wave(SharedArgs a)
     const int32_t cnt = a.deposit ? *a.count : 0;
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
-    int32_t cvq[kSmallPer];
+    int32_t ent[kSmallPer];
     float jr[kSmallPer][3];
-    small_rows(a.small, a.J + w * a.nslots * 3, a.F, a.tabs.atom_off[w], min(lane, a.small.U - 1), sg, nent, cvq, jr);
+    small_rows(a.small, a.J + w * a.nslots * 3, a.F, a.tabs.atom_off[w], min(lane, a.small.U - 1), sg, nent, ent, jr);
     // the first records kept or replaced by +0.0 through a bit mask, which
     // uses the loaded value on every lane (a select lets the load move
     // under a branch)
@@ -469,19 +469,10 @@ __global__ void __launch_bounds__(64) k_hill_shared_finalize_wave(SharedArgs a)
         }
     }
     if (lane < a.small.U) {
-        double fx = 0.0, fy = 0.0, fz = 0.0;
+        double coef[D];
 #pragma unroll
-        for (int qq = 0; qq < kSmallPer; ++qq) {
-            double cf = 0.0;
-#pragma unroll
-            for (int d = 0; d < D; ++d) cf = cvq[qq] == d ? -dv[d] : cf;
-            fx += qq < nent ? cf * (double)jr[qq][0] : 0.0;
-            fy += qq < nent ? cf * (double)jr[qq][1] : 0.0;
-            fz += qq < nent ? cf * (double)jr[qq][2] : 0.0;
-        }
-        sg.dst[0] = sg.f0 + (float)fx;
-        sg.dst[a.F.sk] = sg.f1 + (float)fy;
-        sg.dst[2 * a.F.sk] = sg.f2 + (float)fz;
+        for (int d = 0; d < D; ++d) coef[d] = -dv[d];
+        small_forces(a.small, a.F, sg, nent, ent, jr, coef);
     }
 }
 

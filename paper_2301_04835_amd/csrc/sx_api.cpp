@@ -442,6 +442,7 @@ sx_status make_plan(sx_ctx *c)
         for (int u = 0; u < p.U; ++u) {
             p.small.touched[u] = p.touched[u];
             p.small.nent[u] = p.inv_ptr[u + 1] - p.inv_ptr[u];
+            p.small.most = std::max(p.small.most, p.small.nent[u]);
             for (int q = p.inv_ptr[u]; q < p.inv_ptr[u + 1]; ++q)
                 p.small.ent[u][q - p.inv_ptr[u]] = p.inv_slot[q] | (p.slot_cv[p.inv_slot[q]] << 20);
         }

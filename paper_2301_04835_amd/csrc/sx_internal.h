@@ -94,6 +94,7 @@ struct __align__(16) WalkerRec {
 constexpr int kSmallU = 32, kSmallPer = 8;
 struct SmallTabs {
     int32_t on, U;
+    int32_t most;  // largest nent
     int32_t touched[kSmallU];
     int32_t nent[kSmallU];
     int32_t ent[kSmallU][kSmallPer];  // slot | cv << 20
