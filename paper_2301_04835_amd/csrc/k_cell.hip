@@ -16,11 +16,11 @@
 //                  the block are staged in LDS relative to the block's
 //                  origin (a cell's offset is its cell step times the cell
 //                  edge, periodic wrap included), slice by slice, so each
-//                  home cell's neighbours form one contiguous range; eight
-//                  lanes own one home atom and walk that range: FP32 pair
-//                  terms, the switch sum (the CV value, on the A side) and
-//                  the gradient sum_j f(r_ij)(r_i - r_j) of each (CV, side)
-//                  use, stored per member (no atomics, fixed order).
+//                  home cell's neighbours form one contiguous range; a
+//                  wavefront takes 16 home atoms against their range: FP32
+//                  pair terms, the switch sum (the CV value, on the A side)
+//                  and the gradient sum_j f(r_ij)(r_i - r_j) of each (CV,
+//                  side) use, stored per member (no atomics, fixed order).
 //   k_cn_cell_fin  per (walker, CV): the column-block partials in order.
 //   k_cell_gather  the vector-Jacobian product from the stored gradients,
 //                  one lane per member in member order (groups identical
@@ -174,13 +174,6 @@ __device__ __attribute__((noinline)) bool cut_exact(PosView pos, int64_t aoff, i
     return !(r >= rcut);
 }
 
-__device__ __forceinline__ bool within_cut(float r2, const CvDesc &cv, const CellArgs &c, const PosView &pos,
-                                           int64_t aoff, int32_t ai, int32_t aj)
-{
-    if (fabsf(r2 - cv.rcut2) > 1e-5f * cv.rcut2) return r2 < cv.rcut2;
-    return cut_exact(pos, aoff, ai, aj, c.L[0], c.L[1], c.L[2], cv.rcut);
-}
-
 __device__ __forceinline__ const CvDesc &cell_cv(const CvSet &cs, int k)
 {
     int c = 0;
@@ -195,17 +188,22 @@ __device__ __forceinline__ const CvDesc &cell_cv(const CvSet &cs, int k)
 // the neighbour sub-cells of the block's k-th home sub-cell (z offsets
 // -rz .. rz around it) are the contiguous range s_seg[n^2 k] ..
 // s_seg[n^2 (k + 2 rz + 1)].  Positions
-// relative to the origin of cell (cx, cy, z0), times sc; entries
-// [r0, r0 + kColStage) of the region, followed by kStride atoms far outside
-// any cut (index -1), so a lane reading four partners kLpa apart from any
-// start below the count stays inside.  Returns how many are real.
+// relative to the origin of cell (cx, cy, z0), times sc, and their squared
+// length; entries [r0, r0 + kColStage) of the region, behind kFar entries and
+// followed by kTiles tiles outside any cut.  Returns how many are real.  Its
+// loads are waited for, not its instructions: with a sub-cell's two starts
+// and eight of its members in flight per thread instead of one load at a time
+// the pair pass without its pairs took 483 us, 514 before.
 constexpr int kJacBlock = 256;
-constexpr int kLpa = 8;                     // lanes per home atom
-constexpr int kApp = kJacBlock / kLpa;      // home atoms per pass
-constexpr int kStride = 4 * kLpa;           // partners per lane step
-constexpr int kColStage = 1536;             // partner atoms staged per round (24 KB)
+constexpr int kTile = 16;                       // home atoms of a wavefront, partners of a tile
+constexpr int kApp = kTile * kJacBlock / 64;    // home atoms per pass
+constexpr int kColStage = 1728;                 // partner atoms staged per round (28 KB: five workgroups a CU)
+constexpr int kTiles = 8;                       // tiles tested per step: one 32-bit mask
+constexpr int kFar = 4;                         // partners beyond every cut ahead of the staged ones
+constexpr int kStageLd = kFar + kColStage + kTiles * kTile + 12;  // with a step of padding
+static_assert(kStageLd % 64 == 16, "the four coordinates' reads of a tile hit different banks");
+constexpr int kLoads = 8;                       // members of a sub-cell in flight per thread
 constexpr int kRegMax = (2 * kXYReach + 1) * (2 * kXYReach + 1) * (kCzMax + 2 * kZReach);
-
 constexpr int kRegPer = (kRegMax + kJacBlock - 1) / kJacBlock;  // region sub-cells per thread
 
 // i + o wrapped into [0, n) for -n <= i + o < 2n (no division)
@@ -215,57 +213,66 @@ __device__ __forceinline__ int wrap_cell(int v, int n)
     return v >= n ? v - n : v;
 }
 
+struct Staged {
+    float c[4][kStageLd];  // x, y, z, x^2 + y^2 + z^2
+};
+
 template <int RXY>
 __device__ __forceinline__ int stage_column(const CellArgs &c, int w, int gp, int cx, int cy, int z0, int czb, int r0,
-                                            float sc, float4 *s_p, int32_t *s_seg, int32_t *s_first, int32_t *s_wsum)
+                                            float sc, float lim, Staged &sp, int32_t *s_seg,
+                                            int32_t *s_first, int32_t *s_wsum, int32_t *s_odd)
 {
     const int32_t *cst = c.cstart + ((int64_t)w * c.G + gp) * (c.ncell + 1);
     const float4 *srt = c.sorted + (int64_t)w * c.gtotal + c.goff[gp];
     constexpr int side = 2 * RXY + 1, nxy = side * side;  // RXY = c.rxy: divisions by constants
     const int nreg = nxy * (czb + 2 * c.rz);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // thread tid owns region sub-cells [tid kRegPer, (tid + 1) kRegPer): their
-    // first sorted member to s_first and, until the scan below, their member
-    // count to s_seg (one at a time: few registers live)
-    int loc = 0;
-#pragma unroll 1
-    for (int q = 0; q < kRegPer; ++q) {
-        const int t = tid * kRegPer + q;
-        if (t >= nreg) break;
-        const int sl = t / nxy, xy = t % nxy;
-        const int ox = xy / side - RXY, oy = xy % side - RXY, oz = sl - c.rz;
-        // |ox|, |oy| <= rxy < nc and -rz <= z0 + oz < nc2 + rz with rz <= nc2
-        const int nx = wrap_cell(cx + ox, c.nc[0]), ny = wrap_cell(cy + oy, c.nc[1]);
-        const int nz = wrap_cell(z0 + oz, c.nc[2]);
-        const int nb = (nx * c.nc[1] + ny) * c.nc[2] + nz;
-        const int f = cst[nb], n = cst[nb + 1] - f;
-        s_first[t] = f;
-        s_seg[t] = n;
-        loc += n;
-    }
-    // exclusive scan of the counts over the workgroup: inclusive scan inside
-    // each wavefront, then the wavefronts' totals in order
-    int x = loc;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) s_wsum[wave] = x;
-    __syncthreads();
-    int base = x - loc, total = 0;
+    if (tid == 0) *s_odd = 0;
+    // thread tid's sub-cells are tid, tid + 256, ..: first sorted member and
+    // member count, all loads in flight together; then an exclusive scan of
+    // the counts, inside each wavefront and over the wavefronts' totals in order
+    constexpr int kWaves = kJacBlock / 64;
+    int n[kRegPer], x[kRegPer];
 #pragma unroll
-    for (int wv = 0; wv < kJacBlock / 64; ++wv) {
-        const int ws = s_wsum[wv];
-        base += wv < wave ? ws : 0;
-        total += ws;
-    }
-#pragma unroll 1
     for (int q = 0; q < kRegPer; ++q) {
-        const int t = tid * kRegPer + q;
-        if (t >= nreg) break;
-        const int n = s_seg[t];  // this thread's own count
-        s_seg[t] = base;
-        base += n;
+        const int t = q * kJacBlock + tid;
+        n[q] = 0;
+        if (t < nreg) {
+            const int sl = t / nxy, xy = t % nxy;
+            const int ox = xy / side - RXY, oy = xy % side - RXY, oz = sl - c.rz;
+            // |ox|, |oy| <= rxy < nc and -rz <= z0 + oz < nc2 + rz with rz <= nc2
+            const int nx = wrap_cell(cx + ox, c.nc[0]), ny = wrap_cell(cy + oy, c.nc[1]);
+            const int nz = wrap_cell(z0 + oz, c.nc[2]);
+            const int nb = (nx * c.nc[1] + ny) * c.nc[2] + nz;
+            const int f = cst[nb];
+            n[q] = cst[nb + 1] - f;
+            s_first[t] = f;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kRegPer; ++q) {
+        if (q * kJacBlock >= nreg) break;  // uniform
+        x[q] = n[q];
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(x[q], o, 64);
+            if (lane >= o) x[q] += y;
+        }
+        if (lane == 63) s_wsum[q * kWaves + wave] = x[q];
+    }
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int q = 0; q < kRegPer; ++q) {
+        if (q * kJacBlock >= nreg) break;
+        int base = total + x[q] - n[q];
+#pragma unroll
+        for (int wv = 0; wv < kWaves; ++wv) {
+            const int ws = s_wsum[q * kWaves + wv];
+            base += wv < wave ? ws : 0;
+            total += ws;
+        }
+        const int t = q * kJacBlock + tid;
+        if (t < nreg) s_seg[t] = base;
     }
     if (tid == 0) s_seg[nreg] = total;
     __syncthreads();
@@ -280,36 +287,96 @@ __device__ __forceinline__ int stage_column(const CellArgs &c, int w, int gp, in
         const int sl = t / nxy, xy = t % nxy;
         const int ox = xy / side - RXY, oy = xy % side - RXY, oz = sl - c.rz;
         const float shx = (float)(ox * c.clen[0]), shy = (float)(oy * c.clen[1]), shz = (float)(oz * c.clen[2]);
-        for (int e = e0; e < e1; ++e) {
-            float4 v = srt[f + (e - sg)];
-            v.x = (v.x + shx) * sc;
-            v.y = (v.y + shy) * sc;
-            v.z = (v.z + shz) * sc;
-            s_p[e - r0] = v;
+        for (int eb = e0; eb < e1; eb += kLoads) {  // past the last member: its copy, dropped
+            float4 v[kLoads];
+#pragma unroll
+            for (int l = 0; l < kLoads; ++l) v[l] = srt[f + (min(eb + l, e1 - 1) - sg)];
+#pragma unroll
+            for (int l = 0; l < kLoads; ++l) {
+                const int e = eb + l;
+                if (e >= e1) break;
+                const float px = (v[l].x + shx) * sc, py = (v[l].y + shy) * sc, pz = (v[l].z + shz) * sc;
+                sp.c[0][kFar + e - r0] = px;
+                sp.c[1][kFar + e - r0] = py;
+                sp.c[2][kFar + e - r0] = pz;
+                const float p2 = fmaf(px, px, fmaf(py, py, pz * pz));
+                sp.c[3][kFar + e - r0] = p2;
+                if (!(p2 <= lim)) *s_odd = 1;  // not a position of the region (NaN): no cull in this window
+            }
         }
     }
-    for (int j = m + tid; j < m + kStride; j += blockDim.x) s_p[j] = make_float4(1e6f, 1e6f, 1e6f, __int_as_float(-1));
+    if (tid < kFar + kTiles * kTile) {
+        const int e = tid < kFar ? tid : m + tid;
+        sp.c[0][e] = sp.c[1][e] = sp.c[2][e] = 1e9f;
+        sp.c[3][e] = 1e30f;
+    }
     __syncthreads();
     return m;
 }
 
-// One workgroup of 256 threads per (column block, group, walker); kLpa
-// lanes per home atom (the members of the block's cells, contiguous in the
-// sorted order), kApp home atoms per pass.  For every use (CV, partner
-// group) of the group each lane walks every kLpa-th partner of its home
-// cell's contiguous range, four at a time, accumulating in FP32 the switch sum (A
-// side of the CV: the CV value) and the gradient sum_j f(r_ij) (r_i - r_j);
-// the atom's lanes combine in a fixed butterfly and the gradient is stored per
-// member and use (the VJP reads it).  A group's own CV counts its self pair
-// (r = 0: s = 1 exactly, zero gradient), so the A-side sum drops 1 per atom
-// instead of testing every pair.
-// Four partners p[0], p[kLpa], p[2 kLpa], p[3 kLpa] of one home atom (o):
-// the cut decision, the switch sum and the gradient sum.  In the (6, 12)
-// form the coordinates are in units of r0 (x^2 = r^2 / r0^2 directly) and
-// the gradient term is x^4 s^2 (r_i - r_j) / r0, the factor -6 / r0 applied
-// once per atom; otherwise plain units and f of switch_fn.  TAIL: partners
-// at or past pe do not count.  SIDEA: the switch sum is wanted (the A side
-// of the CV); on the B side only the gradient is.
+// One workgroup of 256 threads per (column block, group, walker).  A
+// wavefront takes 16 home atoms at a time (the members of the block's cells,
+// contiguous in the sorted order) and, for every use (CV, partner group) of
+// the group, the union of their home cells' contiguous partner ranges (what it
+// adds to an atom's own range lies beyond the cut) in two passes:
+//
+//   cull  four in five candidates lie outside the cut.  A tile of 16 partners
+//         against the 16 home atoms is one v_mfma_f32_16x16x4_f32,
+//         D = |p|^2 - 2 p.o + (|o|^2 - R^2), R^2 the squared cut plus the
+//         product's rounding error (below 8 2^-24 (|o| + |p|)^2), so no pair
+//         that the float32 or the exact decision counts is lost; a window with
+//         a position outside that bound (no number) keeps every pair.  A lane
+//         holds home atom lane % 16 and four partners of the tile; the signs
+//         of eight tiles are its 32-bit word;
+//   pairs the kept partners, two at a time: FP32 differences, the switch sum
+//         (A side of the CV: the CV value) and the gradient sum
+//         sum_j f(r_ij) (r_i - r_j).
+//
+// The atom's four lanes combine in a fixed butterfly and the gradient is
+// stored per member and use (the VJP reads it).  A group's own CV counts its
+// self pair (r = 0: s = 1 exactly, zero gradient), so the A-side sum drops 1
+// per atom instead of testing every pair.
+//
+// With every candidate evaluated in FP32 (19 operations and a 16-byte LDS read
+// each, 8 lanes an atom) the pass was bound by VALU issue and LDS reads: 32
+// walkers of 60,000 atoms in three groups and three CVs took 1,287 us; with a
+// cull on the vector units (7 operations, three LDS words) 982, with this one
+// (one LDS word per lane and four shifts for 256 tests) 926, with the lanes'
+// words queued one deep so that a wavefront waits for its fullest lane over
+// the range and not per word 897, and with far partners in place of masked
+// lanes (52 instructions for two pairs, 66 before) 868.  VALU issue still
+// bounds it: 1 in 3 instructions belongs to the cull, and of the pair
+// loop's lanes 2 in 3 hold a pair.
+struct PairCtx {
+    float rc2s, bandcs, rc2;  // squared cut and its band in the units of t, squared cut
+    float cull2;              // R^2
+    int64_t aoff;
+    const float4 *srt;        // the partner group's sorted members
+    const int32_t *s_seg, *s_first;
+    int nreg, r0;             // region sub-cells, first entry of the staged window
+    float lim;                // largest |o|^2, |p|^2 that the cull's error bound covers
+};
+
+// The atom index of staged entry e of the region (rare: the exact cut
+// decision): its sub-cell by bisection of the region's starts.
+__device__ __attribute__((noinline)) int32_t staged_atom(const float4 *srt, const int32_t *s_seg,
+                                                        const int32_t *s_first, int nreg, int e)
+{
+    int lo = 0, hi = nreg - 1;  // the last sub-cell that starts at or before e
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (s_seg[mid] <= e) lo = mid; else hi = mid - 1;
+    }
+    return __float_as_int(srt[s_first[lo] + (e - s_seg[lo])].w);
+}
+
+// Two kept partners of one home atom (o), at byte offsets e of the staged
+// arrays (a far partner in the place of a missing one: it adds zero).  The
+// cut decision, the switch sum and the gradient sum.  In the (6, 12) form the
+// coordinates are in units of r0 (x^2 = r^2 / r0^2 directly) and the gradient
+// term is x^4 s^2 (r_i - r_j) / r0, the factor -6 / r0 applied once per atom;
+// otherwise plain units and f of switch_fn.  SIDEA: the switch sum is wanted
+// (the A side of the CV); on the B side only the gradient is.
 //
 // The cut enters the (6, 12) switch without a select: t = (r^2 - rc^2) 2^100
 // (one fma; scaling by a power of two keeps the rounding of r^2 - rc^2, so
@@ -319,37 +386,45 @@ __device__ __forceinline__ int stage_column(const CellArgs &c, int w, int gp, in
 // (rc^2 in r0 units: 7e25 at rc = 2.4 r0, above 3e24 for any cut beyond
 // r0 / 2), so s < 3e-25 and x^4 s^2 underflows to zero or a denormal: it
 // adds nothing measurable to the gradient and less than 3e-25 to the switch
-// sum, far below the sum's last bit.  Partners that do not count (tail,
-// exact decision outside) get t = +inf, s = 0.
+// sum, far below the sum's last bit.  A partner that the exact decision
+// drops gets t = +inf, s = 0; a far one (1e9) has t = +inf by itself.
 constexpr float kTScale = 0x1p100f;
 
-template <bool S612, bool TAIL, bool SIDEA>
-__device__ __forceinline__ void pair4(const float4 *p, const float4 *pe, float3 o, float rc2s, float bandcs,
-                                      float rc2, const CvDesc &cv, const CellArgs &c, const PosView &pos,
-                                      int64_t aoff, int32_t me, float &sA, float &gx, float &gy, float &gz)
+struct HomeSum {  // of one home atom
+    float s, x, y, z;
+};
+
+// coordinate d of the staged entry at byte offset e
+__device__ __forceinline__ float staged(const Staged &sp, int d, int e)
 {
-    float dx[4], dy[4], dz[4], r2[4], t[4];
+    return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(sp.c[d]) + e);
+}
+
+template <bool S612, bool SIDEA>
+__device__ __forceinline__ void pair2(const Staged &sp, const int (&e)[2], float3 o, int32_t me,
+                                      const PairCtx &k, const CvDesc &cv, const CellArgs &c, const PosView &pos,
+                                      HomeSum &g)
+{
+    float dx[2], dy[2], dz[2], r2[2], t[2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const float4 pj = p[q * kLpa];  // < pe + kStride: padded
-        dx[q] = o.x - pj.x;
-        dy[q] = o.y - pj.y;
-        dz[q] = o.z - pj.z;
+    for (int q = 0; q < 2; ++q) {
+        dx[q] = o.x - staged(sp, 0, e[q]);
+        dy[q] = o.y - staged(sp, 1, e[q]);
+        dz[q] = o.z - staged(sp, 2, e[q]);
         r2[q] = fmaf(dx[q], dx[q], fmaf(dy[q], dy[q], dz[q] * dz[q]));
-        t[q] = S612 ? fmaf(r2[q], kTScale, -rc2s) : r2[q] - rc2;
-        if (TAIL && p + q * kLpa >= pe) t[q] = __builtin_inff();
+        t[q] = S612 ? fmaf(r2[q], kTScale, -k.rc2s) : r2[q] - k.rc2;
     }
-    const float tmin = fminf(fminf(fabsf(t[0]), fabsf(t[1])), fminf(fabsf(t[2]), fabsf(t[3])));
-    if (tmin <= bandcs) {  // rare: the edge of the cut
+    if (fminf(fabsf(t[0]), fabsf(t[1])) <= k.bandcs) {  // rare: the edge of the cut
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (fabsf(t[q]) <= bandcs)
-                t[q] = cut_exact(pos, aoff, me, __float_as_int(p[q * kLpa].w), c.L[0], c.L[1], c.L[2], cv.rcut)
+        for (int q = 0; q < 2; ++q)
+            if (fabsf(t[q]) <= k.bandcs)
+                t[q] = cut_exact(pos, k.aoff, me, staged_atom(k.srt, k.s_seg, k.s_first, k.nreg, k.r0 + e[q] / 4 - kFar), c.L[0],
+                                 c.L[1], c.L[2], cv.rcut)
                            ? -1.0f
                            : __builtin_inff();
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 2; ++q) {
         float f;
         if (S612) {
             const float x4 = r2[q] * r2[q];
@@ -357,44 +432,95 @@ __device__ __forceinline__ void pair4(const float4 *p, const float4 *pe, float3 
             // the signed-integer order agrees with the float order here
             const float den = __int_as_float(max(__float_as_int(fmaf(x4, r2[q], 1.0f)), __float_as_int(t[q])));
             const float sv = __builtin_amdgcn_rcpf(den);
-            if (SIDEA) sA += sv;
+            if (SIDEA) g.s += sv;
             f = x4 * sv * sv;
         } else {
             const bool in = t[q] < 0.f;
             float sv;
             switch_fn(r2[q], cv, sv, f);
-            if (SIDEA) sA += in ? sv : 0.f;
+            if (SIDEA) g.s += in ? sv : 0.f;
             f = in ? f : 0.f;
         }
-        gx = fmaf(f, dx[q], gx);
-        gy = fmaf(f, dy[q], gy);
-        gz = fmaf(f, dz[q], gz);
+        g.x = fmaf(f, dx[q], g.x);
+        g.y = fmaf(f, dy[q], g.y);
+        g.z = fmaf(f, dz[q], g.z);
     }
 }
 
-// One home atom's partners [p, pe) of the staged window, every kLpa-th from
-// this lane's start, four per step; pe3 = max(pe - 3 kLpa, window start):
-// a step starting below pe3 reads only partners below pe.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Partners [b0, b1) of the staged window (uniform per wavefront) against its
+// 16 home atoms; live: this lane's atom counts.  bo: the lane's word of the
+// home operand, (-2 x, -2 y, -2 z, 1) by lane / 16; co = |o|^2 - R^2.
 template <bool S612, bool SIDEA>
-__device__ __forceinline__ void home_pairs(const float4 *p, const float4 *pe, const float4 *pe3, float3 o,
-                                           float rc2s, float bandcs, float rc2, const CvDesc &cv, const CellArgs &c,
-                                           const PosView &pos, int64_t aoff, int32_t me, float &sA, float &gx,
-                                           float &gy, float &gz)
+__device__ __forceinline__ void home_pairs(const Staged &sp, int b0, int b1, float3 o, float bo, float co, bool live, bool odd,
+                                           int32_t me, const PairCtx &k, const CvDesc &cv, const CellArgs &c,
+                                           const PosView &pos, HomeSum &g)
 {
-    for (; p < pe3; p += kStride)
-        pair4<S612, false, SIDEA>(p, pe, o, rc2s, bandcs, rc2, cv, c, pos, aoff, me, sA, gx, gy, gz);
-    if (p < pe) pair4<S612, true, SIDEA>(p, pe, o, rc2s, bandcs, rc2, cv, c, pos, aoff, me, sA, gx, gy, gz);
+    const int lane = threadIdx.x & 63, quad = lane >> 4;
+    // row r of a tile is its partner 4 (r % 4) + r / 4, so that a lane's rows
+    // 4 quad + v are the partners quad + 4 v: an atom's lanes take every
+    // fourth partner and keep about as many each
+    const float *const pa = &sp.c[quad][kFar + 4 * (lane & 3) + ((lane & 15) >> 2)];
+    const f32x4 cc = {co, co, co, co};
+    uint32_t m0 = 0, m1 = 0;  // kept partners of the lane's current word and of the next
+    int e0 = 0;               // byte offset of bit 0 of m0 in a staged array
+    float a[kTiles];
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) a[t] = pa[b0 + t * kTile];
+    for (int j = b0; j < b1; j += kTiles * kTile) {
+        // eight tiles; a tile at or past b1 holds partners beyond every cut,
+        // or padding
+        f32x4 D[kTiles];
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], bo, cc, 0, 0, 0);
+        const int jn = j + kTiles * kTile;
+        if (jn < b1) {  // uniform: the next tiles' words, in flight during this mask's pairs
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t) a[t] = pa[jn + t * kTile];
+        }
+        uint32_t m = 0;  // bit i: partner quad + 4 i of the word's
+#pragma unroll
+        for (int t = kTiles - 1; t >= 0; --t)
+#pragma unroll
+            for (int v = 3; v >= 0; --v)
+                m = __builtin_amdgcn_alignbit(m, __float_as_uint(D[t][v]), 31);  // 2 m + (D < 0)
+        if (odd) {  // all of [j, b1)
+            const int n = (b1 - j - quad + 3) >> 2;
+            m = n <= 0 ? 0u : (n >= 32 ? ~0u : (1u << n) - 1u);
+        }
+        // the word waits behind the lane's last one, so that lanes with few
+        // partners in one word run ahead into the next; after the last word
+        // both drain.  A lane without a partner takes a far one.
+        m1 = live ? m : 0u;
+        const bool last = jn >= b1;
+        for (;;) {
+            const bool next = m0 == 0;
+            m0 = next ? m1 : m0;
+            m1 = next ? 0u : m1;
+            e0 = next ? 4 * (kFar + j + quad) : e0;
+            if (!__any(last ? m0 != 0 : m1 != 0)) break;  // m1 is empty if m0 is
+            int e[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                e[q] = m0 != 0 ? e0 + 16 * __builtin_ctz(m0) : 0;
+                m0 &= m0 - 1u;
+            }
+            pair2<S612, SIDEA>(sp, e, o, me, k, cv, c, pos, g);
+        }
+    }
 }
 
 template <bool S612, int RXY>
 __global__ void __launch_bounds__(kJacBlock, 5) k_cell_jac(CellArgs c, CvSet cs, PosView pos)
 {
-    __shared__ float4 s_p[kColStage + kStride];
-    __shared__ int32_t s_seg[kRegMax + 1], s_first[kRegMax], s_wsum[kJacBlock / 64];
+    __shared__ Staged s_p;
+    __shared__ int32_t s_seg[kRegMax + 1], s_first[kRegMax], s_wsum[kRegPer * kJacBlock / 64];
     __shared__ double s_red[kJacBlock / 64];
+    __shared__ int32_t s_odd;
     __shared__ int32_t s_home[kCzMax + 1];  // sorted position of the block's home cells
     const int blk = blockIdx.x, g = blockIdx.y, w = blockIdx.z;
-    const int tid = threadIdx.x, sub = tid & (kLpa - 1), wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int zb = blk % c.nzb, cy = (blk / c.nzb) % c.nc[1], cx = blk / (c.nzb * c.nc[1]);
     // blocks split the column evenly: nzb blocks of at most kCzMax cells
     const int z0 = zb * c.nc[2] / c.nzb, czb = (zb + 1) * c.nc[2] / c.nzb - z0;
@@ -415,42 +541,51 @@ __global__ void __launch_bounds__(kJacBlock, 5) k_cell_jac(CellArgs c, CvSet cs,
         // coordinate scale, squared cut, its band, and the gradient factor
         const float sc = S612 ? cv.inv_r0 : 1.0f;
         const float rc2 = cv.rcut2 * sc * sc, bandc = 1e-5f * rc2, gsc = S612 ? -6.0f * cv.inv_r0 : 1.0f;
-        // the cut test's difference and band in the units of pair4's t
+        // the cut test's difference and band in the units of pair2's t
         const float rc2s = S612 ? rc2 * kTScale : rc2, bandcs = S612 ? bandc * kTScale : bandc;
+        const float ext = c.ext * sc;  // |o|, |p| <= sqrt(3) ext; the factor below is 8 2^-24 x 12, rounded up
+        PairCtx pc{rc2s, bandcs, rc2, rc2 * 1.0001f + 6e-6f * ext * ext, aoff,
+                   c.sorted + (int64_t)w * c.gtotal + c.goff[c.inv_p[g][u]], s_seg, s_first, nreg, 0,
+                   3.003f * ext * ext};
         double ssum = 0.0;  // this lane's switch sums (A side), over its home atoms
         for (int r0 = 0;; r0 += kColStage) {
-            const int m = stage_column<RXY>(c, w, c.inv_p[g][u], cx, cy, z0, czb, r0, sc, s_p, s_seg, s_first, s_wsum);
-            for (int h0 = a0; h0 + (64 / kLpa) * wave < a1; h0 += kApp) {  // uniform per wavefront
-                const int i = h0 + tid / kLpa;
+            const int m = stage_column<RXY>(c, w, c.inv_p[g][u], cx, cy, z0, czb, r0, sc, pc.lim,
+                                            s_p, s_seg, s_first, s_wsum, &s_odd);
+            pc.r0 = r0;
+            for (int h0 = a0 + kTile * wave; h0 < a1; h0 += kApp) {  // uniform per wavefront
+                const int i = h0 + (lane & 15);
                 const bool live = i < a1;
-                const float4 pi = sg[live ? i : a0];
-                int k = 0;  // this atom's home cell within the block: the last k with s_home[k] <= i
-                for (int hi = czb - 1; k < hi;) {
-                    const int mid = (k + hi + 1) >> 1;
-                    if (s_home[mid] <= i) k = mid; else hi = mid - 1;
+                const float4 pi = sg[live ? i : a1 - 1];  // past the last atom: its copy, dropped
+                int kc = 0;  // this atom's home cell within the block: the last kc with s_home[kc] <= i
+                for (int hi = czb - 1; kc < hi;) {
+                    const int mid = (kc + hi + 1) >> 1;
+                    if (s_home[mid] <= min(i, a1 - 1)) kc = mid; else hi = mid - 1;
                 }
-                // this atom's partners in the staged window
-                const int b0 = max(0, s_seg[nxy * k] - r0), b1 = live ? min(m, s_seg[nxy * k + span] - r0) : 0;
-                // home atoms are stored relative to their own cell: the k-th
-                // cell of the block sits k cell edges above the block origin
-                const float3 o = make_float3(pi.x * sc, pi.y * sc, (pi.z + (float)(k * c.clen[2])) * sc);
+                // partners in the staged window of the first atom's cell to the last's
+                const int kf = __builtin_amdgcn_readlane(kc, 0), kl = __builtin_amdgcn_readlane(kc, 15);
+                const int b0 = max(0, s_seg[nxy * kf] - r0), b1 = min(m, s_seg[nxy * kl + span] - r0);
+                // home atoms are stored relative to their own cell: the kc-th
+                // cell of the block sits kc cell edges above the block origin
+                const float3 o = make_float3(pi.x * sc, pi.y * sc, (pi.z + (float)(kc * c.clen[2])) * sc);
+                const int quad = lane >> 4;
+                const float bo = quad == 3 ? 1.0f : -2.0f * (quad == 0 ? o.x : quad == 1 ? o.y : o.z);
+                const float o2 = fmaf(o.x, o.x, fmaf(o.y, o.y, o.z * o.z)), co = o2 - pc.cull2;
+                const bool odd = s_odd != 0 || !(o2 <= pc.lim);
                 const int32_t me = __float_as_int(pi.w);
-                float sA = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-                const float4 *const p0 = s_p + (b0 + sub), *const pe = s_p + b1;
-                const float4 *const pe3 = s_p + max(b1 - 3 * kLpa, 0);
+                HomeSum gs{0.f, 0.f, 0.f, 0.f};
                 if (sideA)
-                    home_pairs<S612, true>(p0, pe, pe3, o, rc2s, bandcs, rc2, cv, c, pos, aoff, me, sA, gx, gy, gz);
+                    home_pairs<S612, true>(s_p, b0, b1, o, bo, co, live, odd, me, pc, cv, c, pos, gs);
                 else
-                    home_pairs<S612, false>(p0, pe, pe3, o, rc2s, bandcs, rc2, cv, c, pos, aoff, me, sA, gx, gy, gz);
+                    home_pairs<S612, false>(s_p, b0, b1, o, bo, co, live, odd, me, pc, cv, c, pos, gs);
 #pragma unroll
-                for (int o = 1; o < kLpa; o <<= 1) {
-                    sA += __shfl_xor(sA, o, 64);
-                    gx += __shfl_xor(gx, o, 64);
-                    gy += __shfl_xor(gy, o, 64);
-                    gz += __shfl_xor(gz, o, 64);
+                for (int q = 16; q < 64; q <<= 1) {
+                    gs.s += __shfl_xor(gs.s, q, 64);
+                    gs.x += __shfl_xor(gs.x, q, 64);
+                    gs.y += __shfl_xor(gs.y, q, 64);
+                    gs.z += __shfl_xor(gs.z, q, 64);
                 }
-                if (sub == 0 && live) {
-                    float4 gv = make_float4(gx * gsc, gy * gsc, gz * gsc, 0.f);
+                if (quad == 0 && live) {
+                    float4 gv = make_float4(gs.x * gsc, gs.y * gsc, gs.z * gsc, 0.f);
                     if (r0 > 0) {  // later windows add to the earlier ones (same thread)
                         const float4 pv = J[i];
                         gv.x += pv.x;
@@ -458,7 +593,7 @@ __global__ void __launch_bounds__(kJacBlock, 5) k_cell_jac(CellArgs c, CvSet cs,
                         gv.z += pv.z;
                     }
                     J[i] = gv;
-                    if (sideA) ssum += (double)sA - (r0 == 0 ? (double)self1 : 0.0);
+                    if (sideA) ssum += (double)gs.s - (r0 == 0 ? (double)self1 : 0.0);
                 }
             }
             const bool last = r0 + m >= s_seg[nreg];  // uniform

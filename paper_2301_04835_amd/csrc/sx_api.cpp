@@ -348,6 +348,8 @@ sx_status make_plan(sx_ctx *c)
             cl.nzb = std::max(1, (cl.nc[2] + 5 * cl.rz - 1) / (5 * cl.rz));
             if ((cl.nc[2] + cl.nzb - 1) / cl.nzb > kCzMax) return fail(c, SX_EINVAL, "cell column block too tall");
             cl.nblk = cl.nc[0] * cl.nc[1] * cl.nzb;
+            cl.ext = (float)(std::max({(1 + cl.rxy) * cl.clen[0], (1 + cl.rxy) * cl.clen[1],
+                                       ((cl.nc[2] + cl.nzb - 1) / cl.nzb + cl.rz) * cl.clen[2]}));
             cl.jtotal = 0;
             for (int g = 0; g < cl.G; ++g)
                 for (int u = 0; u < cl.ninv[g]; ++u) {

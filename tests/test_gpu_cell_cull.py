@@ -1,0 +1,90 @@
+"""The pair pass of the cell lists tests 16 home atoms against tiles of 16
+partners before it evaluates pairs.  Sizes around a tile, dense and empty
+regions, several staged windows, both forms of the switch and positions that
+are not numbers, against the FP64 oracle.
+
+  from 15 atoms on   CN values <= 1e-6 relative, VJP <= 1e-5 (inf-norm)
+  below              few pairs, whose FP32 errors do not average: coordinates
+                     of up to 4 cells round by 2^-24 of 8 r0 per operation,
+                     3 operations and 3 coordinates, 4e-6 r0 in a distance of
+                     at least r0 / 2; the switch's slope is at most 12 / r:
+                     1e-4
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import methods
+from paper_2301_04835_amd.api import Sampler
+from gpu_util import dev, rel_inf
+
+pytestmark = pytest.mark.gpu
+
+
+def cell_ctx(cvs, L, n):
+    s = Sampler(0)
+    s.add_cvs(cvs)
+    s.set_box(list(L))
+    s.set_walkers(np.array([0, n], dtype=np.int64), None)
+    s.set_cell_lists(1)
+    s.bind()
+    return s
+
+
+def pair_cvs(na, nb, powers):
+    a, b = list(range(na)), list(range(na, na + nb))
+    n, m = powers
+    base = {"kind": "coordination", "r0": 0.5, "n": n, "m": m, "rcut": 1.2, "normalize": False}
+    return [dict(base, a=a, b=b), dict(base, a=b, b=b)]
+
+
+@pytest.mark.parametrize("powers", [(6, 12), (8, 14)])
+@pytest.mark.parametrize("na,nb", [(1, 2), (2, 15), (15, 17), (16, 16), (17, 65), (33, 127), (129, 1500)])
+@pytest.mark.parametrize("L", [(3.7, 3.7, 3.7), (4.0, 9.9, 17.0)])
+def test_cull_sizes(gpu, na, nb, L, powers):
+    """Half of the atoms in a cluster across the box corner (one cell holds
+    many, some regions exceed a staged window), half anywhere."""
+    g = np.random.default_rng(na * 1000 + nb)
+    n = na + nb
+    L = np.array(L)
+    pos = g.uniform(0.0, 1.0, size=(n, 3)) * L
+    pos[::2] = g.normal(scale=0.55, size=pos[::2].shape)  # around the corner: wraps in every dimension
+    pos[:2] = [[0.1, 0.1, 0.1], [0.5, 0.3, -0.2]]         # at least one pair in the cut
+    pos[na:na + 2] = [[-0.3, 0.2, 0.1], [-0.5, 0.5, 0.4]]
+    pos = pos.astype(np.float32)
+    cvs = pair_cvs(na, nb, powers)
+    s = cell_ctx(cvs, L, n)
+    assert s.cell_list_cvs() == 2
+    P = dev(pos)
+    xi = s.eval_cv(P)[0].cpu().numpy()[0]
+    xb = g.normal(size=(1, 2))
+    pb = torch.zeros_like(P)
+    s.cv_vjp(P, dev(xb), pb)
+    xr, J = methods.cv_eval(pos.astype(np.float64), cvs, L)
+    few = na < 15 or nb < 15
+    assert np.max(np.abs(xi - xr) / np.abs(xr)) <= (1e-4 if few else 1e-6)
+    assert rel_inf(pb.cpu().numpy(), np.tensordot(xb[0], J, axes=1)) <= (1e-4 if few else 1e-5)
+
+
+@pytest.mark.parametrize("who", [5, 40])  # in group a, in group b
+def test_a_position_that_is_no_number_shows(gpu, who):
+    na, nb, L = 20, 30, np.full(3, 4.0)
+    pos = np.random.default_rng(5).uniform(0.0, 1.2, size=(na + nb, 3)).astype(np.float32)
+    cvs = pair_cvs(na, nb, (6, 12))
+    s = cell_ctx(cvs, L, na + nb)
+    pos[who, 1] = -np.nan
+    xi = s.eval_cv(dev(pos))[0].cpu().numpy()[0]
+    assert np.isnan(xi[0]) and np.isnan(xi[1]) == (who >= na)
+
+
+def test_far_outside_the_box(gpu):
+    """FP64 positions 10^7 boxes away: the wrapped positions carry 1e-9 of the
+    box, below the FP32 of the pair terms."""
+    na, nb, L = 40, 90, np.full(3, 4.0)
+    g = np.random.default_rng(6)
+    pos = g.uniform(0.0, 4.0, size=(na + nb, 3))
+    cvs = pair_cvs(na, nb, (6, 12))
+    s = cell_ctx(cvs, L, na + nb)
+    near = s.eval_cv(dev(pos))[0].cpu().numpy()[0]
+    far = s.eval_cv(dev(pos + 4.0 * g.choice([-1e7, 0.0, 1e7], size=pos.shape)))[0].cpu().numpy()[0]
+    np.testing.assert_allclose(far, near, rtol=1e-6)
