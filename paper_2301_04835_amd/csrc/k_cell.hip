@@ -6,8 +6,8 @@
 //
 //   k_cell_build   one workgroup per (walker, group): the cell of every
 //                  member (positions wrapped into the box), LDS counts, an
-//                  exclusive scan, and an in-order placement (stable within
-//                  a cell), so every later sum runs in a fixed order; each
+//                  exclusive scan, and a placement in member order within
+//                  a cell, so every later sum runs in a fixed order; each
 //                  member is stored as (x, y, z) relative to its cell's
 //                  origin (float, ~6e-8 nm) and its atom index, and its
 //                  sorted position is kept in member order.
@@ -33,6 +33,8 @@
 // partners a home atom visits from 27 cut-length cubes to
 // ((2 rxy + 1) / rxy)^2 (2 rz + 1) / rz: 14.1 at rxy = 2, rz = 4 (5.8 cut
 // spheres' worth of volume down to 3.4).
+#include <algorithm>
+
 #include "sx_internal.h"
 #include "dev_cv.h"
 
@@ -40,21 +42,40 @@ namespace sx {
 namespace {
 
 constexpr int kBuildBlock = 1024;
+constexpr int kBuildWords = 20448;  // LDS words of the build: the cells', then a 16-bit slot per member
+static_assert(kBuildWords >= kCellTotal, "every cell has a word");
 
-__device__ __forceinline__ int cell_of(double x, double L, double iL, double clen, int nc, double &rel)
+// The cell of a coordinate and the position within it (iclen = 1 / clen, its
+// rounding made good by the position).
+__device__ __forceinline__ int cell_of(double x, double L, double iL, double clen, double iclen, int nc, double &rel)
 {
     const double xw = x - L * floor(x * iL);  // into [0, L)
-    int c = (int)(xw / clen);
+    int c = (int)(xw * iclen);
     c = c < 0 ? 0 : (c >= nc ? nc - 1 : c);
     rel = xw - c * clen;
+    const int d = rel < 0.0 && c > 0 ? -1 : (rel >= clen && c < nc - 1 ? 1 : 0);
+    if (d != 0) {  // rare
+        c += d;
+        rel = xw - c * clen;
+    }
     return c;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kBuildBlock) k_cell_build(CellArgs c, PosView pos)
+// Members take the slots of their cell in any order (an LDS atomic), then
+// each counts the earlier members among its cell's: the place in member order,
+// whatever the slots were.  Taking turns in member order instead (a wavefront
+// ranks its 64 members by shuffles and 16 wavefronts go one after the other)
+// was a chain of 16 barriers per 1,024 members: 96 groups of 20,000 took
+// 135 us, this way 72: 28 up to the slots, 17 the scattered stores of the
+// records, the rest one compute unit's share of the loads and stores.  (A
+// placement kernel over all compute units, slots in memory: 42 and 55.)
+// SMALL: the slots' members fit in LDS next to the cells' words (80 KB, two
+// workgroups a CU); otherwise they wait where the sorted records go (127 us).
+template <typename T, bool SMALL>
+__global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosView pos)
 {
-    __shared__ int32_t s_off[kCellTotal];
-    __shared__ int32_t s_tot[kBuildBlock];
+    __shared__ int32_t s_off[kBuildWords];  // a cell's count, first slot, end; then (SMALL) the slots' members
+    __shared__ int32_t s_tot[kBuildBlock / 64];
     const int w = blockIdx.x / c.G, g = blockIdx.x % c.G;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t n = c.goff[g + 1] - c.goff[g];
@@ -63,94 +84,126 @@ __global__ void __launch_bounds__(kBuildBlock) k_cell_build(CellArgs c, PosView 
     int32_t *cid = c.cid + (int64_t)w * c.gtotal + c.goff[g];
     int32_t *cst = c.cstart + ((int64_t)w * c.G + g) * (c.ncell + 1);
     float4 *srt = c.sorted + (int64_t)w * c.gtotal + c.goff[g];
+    float4 *tmp = c.jac + (int64_t)w * c.jtotal + c.joff[g][0];  // records the pair pass writes later
+    int32_t *slot = reinterpret_cast<int32_t *>(srt);
+    uint16_t *s_slot = reinterpret_cast<uint16_t *>(s_off + c.ncell);
     for (int i = tid; i < c.ncell; i += kBuildBlock) s_off[i] = 0;
     __syncthreads();
-    // pass 1: cells and counts, four members per thread at a time with their
-    // loads issued together (a member past the group's end reads member b
-    // instead and is dropped)
+    // cells, counts and positions in their cells, four members per thread at a
+    // time with their loads issued together (a member past the group's end is
+    // member b instead and is dropped)
     for (int32_t b = tid; b < n; b += 4 * kBuildBlock) {
+        int32_t a[4];
         double3 r[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int32_t i = b + k * kBuildBlock;
-            r[k] = ld_pos_t<T>(pos, aoff + ga[i < n ? i : b]);
+            a[k] = ga[i < n ? i : b];
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = ld_pos_t<T>(pos, aoff + a[k]);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int32_t i = b + k * kBuildBlock;
             if (i >= n) break;
-            double rel;
-            const int cx = cell_of(r[k].x, c.L[0], c.inv_L[0], c.clen[0], c.nc[0], rel);
-            const int cy = cell_of(r[k].y, c.L[1], c.inv_L[1], c.clen[1], c.nc[1], rel);
-            const int cz = cell_of(r[k].z, c.L[2], c.inv_L[2], c.clen[2], c.nc[2], rel);
+            double rx, ry, rz;
+            const int cx = cell_of(r[k].x, c.L[0], c.inv_L[0], c.clen[0], c.inv_clen[0], c.nc[0], rx);
+            const int cy = cell_of(r[k].y, c.L[1], c.inv_L[1], c.clen[1], c.inv_clen[1], c.nc[1], ry);
+            const int cz = cell_of(r[k].z, c.L[2], c.inv_L[2], c.clen[2], c.inv_clen[2], c.nc[2], rz);
             const int cell = (cx * c.nc[1] + cy) * c.nc[2] + cz;
             cid[i] = cell;
-            atomicAdd(&s_off[cell], 1);  // counts only: the placement below is ordered
+            tmp[i] = make_float4((float)rx, (float)ry, (float)rz, __int_as_float(a[k]));
+            atomicAdd(&s_off[cell], 1);
         }
     }
     __syncthreads();
-    // exclusive scan of the counts: kScanPer cells per thread, then across threads
-    constexpr int kScanPer = kCellTotal / kBuildBlock;
-    int32_t loc[kScanPer], sum = 0;
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q) {
-        const int cc = tid * kScanPer + q;
-        loc[q] = cc < c.ncell ? s_off[cc] : 0;
-        sum += loc[q];
+    // exclusive scan of the counts: consecutive cells per thread, the threads
+    // of a wavefront, the wavefronts in order
+    const int per = (c.ncell + kBuildBlock - 1) / kBuildBlock;
+    const int c0 = min(tid * per, c.ncell), c1 = min(c0 + per, c.ncell);
+    int32_t sum = 0;
+    for (int cc = c0; cc < c1; ++cc) sum += s_off[cc];
+    int32_t run = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(run, o, 64);
+        if (lane >= o) run += y;
     }
-    s_tot[tid] = sum;
+    if (lane == 63) s_tot[wave] = run;
     __syncthreads();
-    for (int o = 1; o < kBuildBlock; o <<= 1) {  // inclusive Hillis-Steele
-        const int32_t add = tid >= o ? s_tot[tid - o] : 0;
-        __syncthreads();
-        s_tot[tid] += add;
-        __syncthreads();
-    }
-    int32_t run = s_tot[tid] - sum;
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q) {
-        const int cc = tid * kScanPer + q;
-        if (cc < c.ncell) {
-            s_off[cc] = run;
-            cst[cc] = run;
-        }
-        run += loc[q];
+    run -= sum;
+    for (int k = 0; k < wave; ++k) run += s_tot[k];
+    for (int cc = c0; cc < c1; ++cc) {
+        const int32_t m = s_off[cc];
+        s_off[cc] = run;
+        cst[cc] = run;
+        run += m;
     }
     if (tid == 0) cst[c.ncell] = n;
     __syncthreads();
-    // pass 2: placement in member order; within a chunk of 1024 members the
-    // rank among same-cell members comes from shuffles inside a wavefront
-    // and from the wavefronts taking turns
-    for (int32_t base = 0; base < n; base += kBuildBlock) {
-        const int32_t i = base + tid;
-        const bool valid = i < n;
-        const int cell = valid ? cid[i] : -1;
-        const int32_t atom = ga[valid ? i : base];  // in flight during the ranking
-        const double3 r = ld_pos_t<T>(pos, aoff + atom);
-        int rank = 0, cnt = 0;
-        for (int k = 0; k < 64; ++k) {
-            const int ck = __shfl(cell, k, 64);
-            cnt += ck == cell ? 1 : 0;
-            rank += (ck == cell && k < lane) ? 1 : 0;
+    for (int32_t b = tid; b < n; b += 4 * kBuildBlock) {
+        int32_t cell[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) cell[k] = cid[b + k * kBuildBlock < n ? b + k * kBuildBlock : b];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int32_t i = b + k * kBuildBlock;
+            if (i >= n) break;
+            const int32_t e = atomicAdd(&s_off[cell[k]], 1);
+            if (SMALL)
+                s_slot[e] = (uint16_t)i;
+            else
+                slot[e] = i;
         }
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (valid) {
-            double rx, ry, rz;
-            cell_of(r.x, c.L[0], c.inv_L[0], c.clen[0], c.nc[0], rx);
-            cell_of(r.y, c.L[1], c.inv_L[1], c.clen[1], c.nc[1], ry);
-            cell_of(r.z, c.L[2], c.inv_L[2], c.clen[2], c.nc[2], rz);
-            v = make_float4((float)rx, (float)ry, (float)rz, __int_as_float(atom));
+    }
+    __syncthreads();
+    // four members' counts side by side.  SMALL: in member order, two slots a
+    // word: all of the cell's words, less what its first and last hold of the
+    // neighbour cells; otherwise in slot order, where lanes share cells.
+    // A member that is not there (past the group's end) is the thread's first:
+    // no other thread's, which may be done with it.
+    const uint32_t *s_two = reinterpret_cast<const uint32_t *>(s_slot);
+    for (int32_t b = tid; b < n; b += 4 * kBuildBlock) {
+        int32_t m[4], lo[4], hi[4], dst[4], len = 0;
+        float4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int32_t e = b + k * kBuildBlock < n ? b + k * kBuildBlock : b;
+            m[k] = SMALL ? e : slot[e];
+            lo[k] = cid[m[k]];
+            if (SMALL) v[k] = tmp[m[k]];
         }
-        for (int t = 0; t < kBuildBlock / 64; ++t) {
-            __syncthreads();
-            if (wave == t && valid) {
-                const int dst = s_off[cell] + rank;
-                srt[dst] = v;
-                cid[i] = dst;  // from here on: the member's sorted position
-                if (rank == cnt - 1) s_off[cell] += cnt;  // after every lane of the wave read it
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            hi[k] = s_off[lo[k]];
+            dst[k] = lo[k] = lo[k] > 0 ? s_off[lo[k] - 1] : 0;
+            len = max(len, SMALL ? ((hi[k] + 1) >> 1) - (lo[k] >> 1) : hi[k] - lo[k]);
+            if (SMALL) {
+                dst[k] -= (lo[k] & 1) && s_slot[lo[k] - 1] < m[k] ? 1 : 0;
+                dst[k] -= (hi[k] & 1) && s_slot[hi[k]] < m[k] ? 1 : 0;
             }
         }
-        __syncthreads();
+        for (int32_t q = 0; q < len; ++q)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (SMALL) {
+                    const int32_t e = (lo[k] >> 1) + q, last = (hi[k] - 1) >> 1;
+                    const uint32_t two = s_two[min(e, last)] | (e > last ? ~0u : 0u);
+                    dst[k] += ((two & 0xffffu) < (uint32_t)m[k] ? 1 : 0) + ((two >> 16) < (uint32_t)m[k] ? 1 : 0);
+                } else {
+                    const int32_t e = lo[k] + q;
+                    dst[k] += e < hi[k] && slot[min(e, hi[k] - 1)] < m[k] ? 1 : 0;
+                }
+            }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (b + k * kBuildBlock >= n) break;
+            if (SMALL) srt[dst[k]] = v[k];
+            cid[m[k]] = dst[k];  // from here on: the member's sorted position
+        }
+    }
+    if (!SMALL) {
+        __syncthreads();  // the slots lie in srt
+        for (int32_t i = tid; i < n; i += kBuildBlock) srt[cid[i]] = tmp[i];
     }
 }
 
@@ -674,10 +727,19 @@ hipError_t launch_cell_cv(const CellArgs &c, const CvSet &cs, const PosView &pos
     if (c.ncn == 0) return hipSuccess;
     hipError_t e = hipSuccess;
     if (which & 1) {
-        if (pos.f64)
-            hipLaunchKernelGGL(k_cell_build<double>, dim3(c.W * c.G), dim3(kBuildBlock), 0, s, c, pos);
+        int32_t nmax = 0;
+        for (int g = 0; g < c.G; ++g) nmax = std::max(nmax, c.goff[g + 1] - c.goff[g]);
+        // every member's 16-bit number behind the cells' words
+        const bool small = nmax <= 65536 && (int64_t)c.ncell + (nmax + 1) / 2 <= kBuildWords;
+        const dim3 grid(c.W * c.G), block(kBuildBlock);
+        if (pos.f64 && small)
+            hipLaunchKernelGGL((k_cell_build<double, true>), grid, block, 0, s, c, pos);
+        else if (pos.f64)
+            hipLaunchKernelGGL((k_cell_build<double, false>), grid, block, 0, s, c, pos);
+        else if (small)
+            hipLaunchKernelGGL((k_cell_build<float, true>), grid, block, 0, s, c, pos);
         else
-            hipLaunchKernelGGL(k_cell_build<float>, dim3(c.W * c.G), dim3(kBuildBlock), 0, s, c, pos);
+            hipLaunchKernelGGL((k_cell_build<float, false>), grid, block, 0, s, c, pos);
         e = hipGetLastError();
         if (e != hipSuccess || !(which & 2)) return e;
     }

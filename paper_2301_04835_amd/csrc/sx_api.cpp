@@ -325,7 +325,10 @@ sx_status make_plan(sx_ctx *c)
             cl.nc[1] *= cl.rxy;
             cl.nc[2] *= cl.rz;
             cl.ncell = cl.nc[0] * cl.nc[1] * cl.nc[2];
-            for (int k = 0; k < 3; ++k) cl.clen[k] = c->box[k] / cl.nc[k];
+            for (int k = 0; k < 3; ++k) {
+                cl.clen[k] = c->box[k] / cl.nc[k];
+                cl.inv_clen[k] = cl.nc[k] / c->box[k];
+            }
             cl.goff[0] = 0;
             for (int g = 0; g < cl.G; ++g) {
                 for (int32_t i : groups[g]) p.gatoms.push_back(i);

@@ -353,7 +353,8 @@ struct CellArgs {
     int32_t W, G, ncn;                 // walkers, distinct groups, cell-list CVs
     int32_t nc[3], ncell;              // cells per dimension, total
     int32_t rxy, rz;                   // reach in x and y, and in z, in sub-cells
-    double L[3], inv_L[3], clen[3];    // box edges, cell edges
+    double L[3], inv_L[3];             // box edges
+    double clen[3], inv_clen[3];       // cell edges
     float ext;                         // largest coordinate of a column block's region from its origin
     const int64_t *atom_off;           // W + 1
     const int32_t *gatoms;             // walker-relative atoms of all groups, group after group

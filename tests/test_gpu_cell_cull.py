@@ -66,6 +66,28 @@ def test_cull_sizes(gpu, na, nb, L, powers):
     assert rel_inf(pb.cpu().numpy(), np.tensordot(xb[0], J, axes=1)) <= (1e-4 if few else 1e-5)
 
 
+@pytest.mark.parametrize("na,L", [(34800, (3.7, 3.7, 3.7)), (41000, (3.7, 3.7, 3.7)), (9000, (19.3, 19.3, 19.3))])
+def test_build_of_large_groups(gpu, na, L):
+    """The members of the cells' slots in LDS, just (34,800 in 432 cells), and
+    in memory (41,000; 9,000 in 16,384 cells); the first CV's value and VJP
+    against the oracle, and bitwise the same again."""
+    g = np.random.default_rng(na)
+    nb, L = 30, np.array(L)
+    n = na + nb
+    pos = (g.uniform(0.0, 1.0, size=(n, 3)) * L).astype(np.float32)
+    cvs = pair_cvs(na, nb, (6, 12))[:1]
+    s = cell_ctx(cvs, L, n)
+    assert s.cell_list_cvs() == 1
+    P = dev(pos)
+    xi = s.eval_cv(P)[0].cpu().numpy()[0]
+    pb = torch.zeros_like(P)
+    s.cv_vjp(P, dev(np.ones((1, 1))), pb)
+    xr, J = methods.cv_eval(pos.astype(np.float64), cvs, L)
+    assert abs(xi[0] - xr[0]) <= 1e-6 * abs(xr[0])
+    assert rel_inf(pb.cpu().numpy(), J[0]) <= 1e-5
+    assert np.array_equal(s.eval_cv(P)[0].cpu().numpy()[0], xi)
+
+
 @pytest.mark.parametrize("who", [5, 40])  # in group a, in group b
 def test_a_position_that_is_no_number_shows(gpu, who):
     na, nb, L = 20, 30, np.full(3, 4.0)
