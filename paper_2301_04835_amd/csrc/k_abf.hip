@@ -24,28 +24,31 @@
 namespace sx {
 namespace {
 
-constexpr int MD = kMaxBiasDim;
-constexpr int NA = MD * MD + MD;  // G (MD x MD) then u (MD)
+// Every function below is instantiated for its number of CVs D, so that the
+// loops, the sums to reduce and the array indices are compile-time constants
+// (registers, no scratch).
+constexpr int terms_of(int D) { return D * D + D; }  // G (D x D) then u (D)
 
 // touched atom u of walker w: its Jacobian rows j_d (slots of one CV summed)
 // and its terms m^-1 j_d . j_e and m^-1 j_d . q added to acc
-__device__ __forceinline__ void abf_atom_terms(const AbfArgs &a, int32_t w, int u, double (&acc)[NA])
+template <int D>
+__device__ __forceinline__ void abf_atom_terms(const AbfArgs &a, int32_t w, int u, double (&acc)[terms_of(D)])
 {
     const WalkerTabs &t = a.tabs;
     const int64_t jb = (int64_t)w * a.nslots, ab = t.atom_off[w];
-    double jv[MD][3];
+    double jv[D][3];
 #pragma unroll
-    for (int d = 0; d < MD; ++d) jv[d][0] = jv[d][1] = jv[d][2] = 0.0;
+    for (int d = 0; d < D; ++d) jv[d][0] = jv[d][1] = jv[d][2] = 0.0;
     for (int q = t.inv_ptr[u]; q < t.inv_ptr[u + 1]; ++q) {
         const int32_t s = t.inv_slot[q];
         const int d = t.slot_cv[s];
-        const double *js = a.J + (jb + s) * 3;
+        const double *js = a.J + (jb + s) * 3, x = js[0], y = js[1], z = js[2];  // beside slot_cv's load
 #pragma unroll
-        for (int dd = 0; dd < MD; ++dd)
+        for (int dd = 0; dd < D; ++dd)
             if (dd == d) {
-                jv[dd][0] += js[0];
-                jv[dd][1] += js[1];
-                jv[dd][2] += js[2];
+                jv[dd][0] += x;
+                jv[dd][1] += y;
+                jv[dd][2] += z;
             }
     }
     const int64_t atom = ab + t.touched[u];
@@ -53,32 +56,29 @@ __device__ __forceinline__ void abf_atom_terms(const AbfArgs &a, int32_t w, int 
     const double f[3] = {fp[0], fp[a.Fsys.sk], fp[2 * a.Fsys.sk]};
     const double im = a.estimator == 1 ? a.inv_mass[atom] : 1.0;
 #pragma unroll
-    for (int d = 0; d < MD; ++d) {
+    for (int d = 0; d < D; ++d) {
 #pragma unroll
-        for (int e = 0; e < MD; ++e)
-            acc[d * MD + e] += im * (jv[d][0] * jv[e][0] + jv[d][1] * jv[e][1] + jv[d][2] * jv[e][2]);
-        acc[MD * MD + d] += im * (jv[d][0] * f[0] + jv[d][1] * f[1] + jv[d][2] * f[2]);
+        for (int e = 0; e < D; ++e)
+            acc[d * D + e] += im * (jv[d][0] * jv[e][0] + jv[d][1] * jv[e][1] + jv[d][2] * jv[e][2]);
+        acc[D * D + d] += im * (jv[d][0] * f[0] + jv[d][1] * f[1] + jv[d][2] * f[2]);
     }
 }
 
-// What the update reads that does not depend on the sums (AbfPre): xi, its
+// What the update reads that does not depend on the sums (AbfPre), from xi: its
 // bin (row major, first CV slowest), the bin's count and force sums (the
 // samples before this step), FUNN's bias, the momentum estimator's previous
 // values and the device step counter.  Called by every lane of a workgroup,
 // the addresses are uniform, so the loads go through the scalar cache and
 // are in flight while the sums are formed.
-__device__ __forceinline__ AbfPre abf_prefetch(const AbfArgs &a, int32_t w)
+template <int D>
+__device__ __forceinline__ AbfPre abf_prefetch(const AbfArgs &a, int32_t w, const double (&xi)[D])
 {
-    // loops over the largest CV count with run-time guards: every array
-    // index is a compile-time constant, so nothing lives in scratch memory
     AbfPre r{};
-    const int D = a.D;
     r.k = 0;
     r.inr = true;
 #pragma unroll
-    for (int d = 0; d < MD; ++d) {
-        if (d >= D) continue;
-        r.xi[d] = a.xi[(int64_t)w * D + d];
+    for (int d = 0; d < D; ++d) {
+        r.xi[d] = xi[d];
         int64_t i = (int64_t)floor((r.xi[d] - a.lo[d]) / a.delta[d]);
         if (a.periodic[d]) {
             i %= a.nbins[d];
@@ -91,17 +91,15 @@ __device__ __forceinline__ AbfPre abf_prefetch(const AbfArgs &a, int32_t w)
     if (r.inr) {
         r.cnt = a.N[(int64_t)w * a.nbins_total + r.k];
 #pragma unroll
-        for (int d = 0; d < MD; ++d)
-            if (d < D) r.F[d] = a.Fsum[((int64_t)w * a.nbins_total + r.k) * D + d];
+        for (int d = 0; d < D; ++d) r.F[d] = a.Fsum[((int64_t)w * a.nbins_total + r.k) * D + d];
     }
 #pragma unroll
-    for (int d = 0; d < MD; ++d)
-        if (d < D && a.b_ext) r.bext[d] = a.b_ext[(int64_t)w * D + d];
+    for (int d = 0; d < D; ++d)
+        if (a.b_ext) r.bext[d] = a.b_ext[(int64_t)w * D + d];
     if (a.estimator == 1) {
         r.has = a.has_prev[w];
 #pragma unroll
-        for (int d = 0; d < MD; ++d) {
-            if (d >= D) continue;
+        for (int d = 0; d < D; ++d) {
             r.bprev[d] = a.b_prev[(int64_t)w * D + d];
             r.wpprev[d] = a.Wp_prev[(int64_t)w * D + d];
         }
@@ -114,43 +112,40 @@ __device__ __forceinline__ AbfPre abf_prefetch(const AbfArgs &a, int32_t w)
 // form theta, and take the bias of xi's bin (zero outside the grid or when x
 // or theta is not finite).  A pure function of its inputs, so every
 // workgroup that evaluates it gets the same bits.
+template <int D>
 struct AbfOut {
-    double x[MD], theta[MD], b[MD];
+    double x[D], theta[D], b[D];
     bool sample, finite;
 };
 
-__device__ AbfOut abf_solve(const AbfArgs &a, const double (&acc)[NA], const AbfPre &pre)
+template <int D>
+__device__ AbfOut<D> abf_solve(const AbfArgs &a, const double (&acc)[terms_of(D)], const AbfPre &pre)
 {
-    // every loop runs over MD with a run-time guard (d < D), so that all
-    // array indices are compile-time constants (registers, no scratch); the
-    // operations on rows and columns below D are those of plain Gaussian
-    // elimination with partial pivoting on the D x D system, in its order
-    const int D = a.D;
-    AbfOut r{};
-    double G[MD][MD], rhs[MD];
+    // plain Gaussian elimination with partial pivoting
+    AbfOut<D> r{};
+    double G[D][D], rhs[D];
 #pragma unroll
-    for (int d = 0; d < MD; ++d) {
+    for (int d = 0; d < D; ++d) {
 #pragma unroll
-        for (int e = 0; e < MD; ++e) G[d][e] = (d < D && e < D) ? acc[d * MD + e] : 0.0;
-        rhs[d] = d < D ? acc[MD * MD + d] : 0.0;
+        for (int e = 0; e < D; ++e) G[d][e] = acc[d * D + e];
+        rhs[d] = acc[D * D + d];
     }
 #pragma unroll
-    for (int col = 0; col < MD; ++col) {
-        if (col >= D) continue;
+    for (int col = 0; col < D; ++col) {
         // pivot: the first row r >= col with the largest |G[r][col]|
         int piv = col;
         double best = fabs(G[col][col]);
 #pragma unroll
-        for (int q = col + 1; q < MD; ++q)
-            if (q < D && fabs(G[q][col]) > best) {
+        for (int q = col + 1; q < D; ++q)
+            if (fabs(G[q][col]) > best) {
                 best = fabs(G[q][col]);
                 piv = q;
             }
 #pragma unroll
-        for (int q = col + 1; q < MD; ++q)
+        for (int q = col + 1; q < D; ++q)
             if (q == piv) {
 #pragma unroll
-                for (int e = 0; e < MD; ++e) {
+                for (int e = 0; e < D; ++e) {
                     const double tmp = G[col][e];
                     G[col][e] = G[q][e];
                     G[q][e] = tmp;
@@ -160,58 +155,54 @@ __device__ AbfOut abf_solve(const AbfArgs &a, const double (&acc)[NA], const Abf
                 rhs[q] = tmp;
             }
 #pragma unroll
-        for (int q = col + 1; q < MD; ++q) {
-            if (q >= D) continue;
+        for (int q = col + 1; q < D; ++q) {
             const double fct = G[q][col] / G[col][col];
 #pragma unroll
-            for (int e = col; e < MD; ++e)
-                if (e < D) G[q][e] -= fct * G[col][e];
+            for (int e = col; e < D; ++e)
+                G[q][e] -= fct * G[col][e];
             rhs[q] -= fct * rhs[col];
         }
     }
 #pragma unroll
-    for (int d = MD - 1; d >= 0; --d) {
-        if (d >= D) continue;
+    for (int d = D - 1; d >= 0; --d) {
         double sd = rhs[d];
 #pragma unroll
-        for (int e = d + 1; e < MD; ++e)
-            if (e < D) sd -= G[d][e] * r.x[e];
+        for (int e = d + 1; e < D; ++e)
+            sd -= G[d][e] * r.x[e];
         r.x[d] = sd / G[d][d];
     }
     r.sample = true;
     if (a.estimator == 1) r.sample = pre.has != 0;
     r.finite = true;
 #pragma unroll
-    for (int d = 0; d < MD; ++d) {
-        if (d >= D) continue;
+    for (int d = 0; d < D; ++d) {
         r.theta[d] = a.estimator == 1 ? pre.bprev[d] - (r.x[d] - pre.wpprev[d]) / a.dt : -r.x[d];
         r.finite = r.finite && isfinite(r.theta[d]) && isfinite(r.x[d]);
     }
     if (pre.inr && r.finite) {
         const double den = (double)max((int64_t)pre.cnt, (int64_t)a.n_threshold);
 #pragma unroll
-        for (int d = 0; d < MD; ++d)
-            if (d < D) r.b[d] = a.b_ext ? pre.bext[d] : den > 0.0 ? pre.F[d] / den : 0.0;
+        for (int d = 0; d < D; ++d)
+            r.b[d] = a.b_ext ? pre.bext[d] : den > 0.0 ? pre.F[d] / den : 0.0;
     }
     return r;
 }
 
 // Once per walker and step: add the sample to the grid, keep the momentum
 // estimator's state, write the outputs and advance the step counter.
-__device__ void abf_commit(const AbfArgs &a, int32_t w, const AbfPre &pre, const AbfOut &r)
+template <int D>
+__device__ void abf_commit(const AbfArgs &a, int32_t w, const AbfPre &pre, const AbfOut<D> &r)
 {
-    const int D = a.D;
     if (!r.finite) atomicOr(a.flags, kFlagNonFinite);
     if (pre.inr && r.finite && r.sample) {
         a.N[(int64_t)w * a.nbins_total + pre.k] = pre.cnt + 1u;
         double *Fk = a.Fsum + ((int64_t)w * a.nbins_total + pre.k) * D;
 #pragma unroll
-        for (int d = 0; d < MD; ++d)
-            if (d < D) Fk[d] = pre.F[d] + r.theta[d];
+        for (int d = 0; d < D; ++d)
+            Fk[d] = pre.F[d] + r.theta[d];
     }
 #pragma unroll
-    for (int d = 0; d < MD; ++d) {
-        if (d >= D) continue;
+    for (int d = 0; d < D; ++d) {
         if (a.estimator == 1) {  // for the next step: this step's W p and bias
             a.Wp_prev[(int64_t)w * D + d] = r.x[d];
             a.b_prev[(int64_t)w * D + d] = r.b[d];
@@ -224,23 +215,27 @@ __device__ void abf_commit(const AbfArgs &a, int32_t w, const AbfPre &pre, const
     if (w == 0) *a.dstep = a.step >= 0 ? a.step + 1 : pre.dstep + 1;
 }
 
+template <int D>
 __global__ void __launch_bounds__(kBlock) k_abf(AbfArgs a)
 {
+    constexpr int NA = terms_of(D);
     __shared__ double lds[NA * (kBlock / 64)];
     __shared__ double s_coef[kMaxCv];
     const int32_t w = blockIdx.x;
-    const AbfPre pre = abf_prefetch(a, w);
+    double xi[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) xi[d] = a.xi[(int64_t)w * D + d];
+    const AbfPre pre = abf_prefetch<D>(a, w, xi);
     double acc[NA];
 #pragma unroll
     for (int j = 0; j < NA; ++j) acc[j] = 0.0;
-    for (int u = threadIdx.x; u < a.tabs.U; u += blockDim.x) abf_atom_terms(a, w, u, acc);
+    for (int u = threadIdx.x; u < a.tabs.U; u += blockDim.x) abf_atom_terms<D>(a, w, u, acc);
     block_sum0<NA>(acc, lds);
     if (threadIdx.x == 0) {
-        const AbfOut r = abf_solve(a, acc, pre);
-        abf_commit(a, w, pre, r);
+        const AbfOut<D> r = abf_solve<D>(a, acc, pre);
+        abf_commit<D>(a, w, pre, r);
 #pragma unroll
-        for (int d = 0; d < MD; ++d)
-            if (d < a.D) s_coef[d] = r.b[d];
+        for (int d = 0; d < D; ++d) s_coef[d] = r.b[d];
     }
     __syncthreads();
     gather_forces(a.tabs, a.J + (int64_t)w * a.nslots * 3, w, s_coef, a.F);
@@ -248,41 +243,59 @@ __global__ void __launch_bounds__(kBlock) k_abf(AbfArgs a)
 
 // Walkers with many touched atoms, in two launches: (1) one lane per touched
 // atom, the terms reduced per workgroup (fixed tree) into a record per
-// (walker, block), and the first workgroup's first lane keeps the walker's
-// AbfPre in the workspace; (2) per (walker, block of touched atoms): the
-// first wavefront sums the walker's records in a fixed order and its first
-// lane solves from them and the kept AbfPre -- every workgroup the same bits
-// -- the first workgroup alone commits the sample, and every workgroup
-// gathers the forces of its atoms.  The grid is read in (1) and written in
-// (2) by one lane, so no workgroup reads it while it changes.
-// The coordination numbers' values of walker w from their block records:
+// (walker, block), and a workgroup of its own keeps the walker's AbfPre in
+// the workspace; (2) per (walker, block of touched atoms): the first wavefront
+// sums the walker's records in a fixed order and its first lane solves from
+// them and the kept AbfPre -- every workgroup the same bits -- the first
+// workgroup alone commits the sample, and every workgroup gathers the forces
+// of its atoms.  The grid is read in (1) and written in (2) by one lane, so no
+// workgroup reads it while it changes.  Both are chains of dependent loads and
+// shuffles: with AbfPre ahead of the first block's atoms, three CVs' terms
+// reduced for any number of CVs and a slot's row loaded after its CV, the two
+// took 6.4 and 5.1 us on 2,500 touched atoms and two CVs; now 3.9 and 4.7.
+
+// xi of walker w, the coordination numbers' values from their block records:
 // lane-strided sums, a fixed butterfly, times the scale (the value kernel's
-// order, so the same bits); run by one whole wavefront, lane 0 writes.
-__device__ void fold_cn_values(const AbfArgs &a, int32_t w)
+// order, so the same bits); run by one whole wavefront, lane 0 writes them.
+template <int D>
+__device__ __forceinline__ void fold_cn_values(const AbfArgs &a, int32_t w, double (&xi)[D])
 {
     const int lane = threadIdx.x & 63;
-    for (int k = 0; k < a.ncn_fold && k < kMaxBiasDim; ++k) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) xi[d] = a.xi[(int64_t)w * D + d];
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        if (k >= a.ncn_fold) continue;
         const double *p = a.cn_vpart + (int64_t)w * a.vblk_per_walker + a.cn_vblk0[k];
         double v = 0.0;
         for (int b = lane; b < a.cn_nblk[k]; b += 64) v += p[b];
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) a.xi_ws[(int64_t)w * a.D + a.cn_d[k]] = v * a.cn_scale[k];
+        v *= a.cn_scale[k];
+        if (lane == 0) a.xi_ws[(int64_t)w * D + a.cn_d[k]] = v;
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d == a.cn_d[k]) xi[d] = v;
     }
 }
 
+template <int D>
 __global__ void __launch_bounds__(kBlock) k_abf_part(AbfArgs a)
 {
+    constexpr int NA = terms_of(D);
     __shared__ double lds[NA * (kBlock / 64)];
     const int32_t w = blockIdx.y;
-    const int u = blockIdx.x * kBlock + threadIdx.x;
-    if (blockIdx.x == 0 && threadIdx.x < 64) {  // lane 0 reads the values it wrote
-        if (a.ncn_fold > 0) fold_cn_values(a, w);
-        if (threadIdx.x == 0) a.pre[w] = abf_prefetch(a, w);
+    if ((int)blockIdx.x == a.nblk) {  // uniform
+        if (threadIdx.x >= 64) return;
+        double xi[D];
+        fold_cn_values<D>(a, w, xi);
+        if (threadIdx.x == 0) a.pre[w] = abf_prefetch<D>(a, w, xi);
+        return;
     }
+    const int u = blockIdx.x * kBlock + threadIdx.x;
     double acc[NA];
 #pragma unroll
     for (int j = 0; j < NA; ++j) acc[j] = 0.0;
-    if (u < a.tabs.U) abf_atom_terms(a, w, u, acc);
+    if (u < a.tabs.U) abf_atom_terms<D>(a, w, u, acc);
     block_sum0<NA>(acc, lds);
     if (threadIdx.x == 0) {
         double *r = a.part + ((int64_t)w * a.nblk + blockIdx.x) * NA;
@@ -291,8 +304,10 @@ __global__ void __launch_bounds__(kBlock) k_abf_part(AbfArgs a)
     }
 }
 
+template <int D>
 __global__ void __launch_bounds__(kBlock) k_abf_finish(AbfArgs a)
 {
+    constexpr int NA = terms_of(D);
     __shared__ double s_coef[kMaxCv];
     const int32_t w = blockIdx.y;
     // this lane's atom: its rows and force requested before the solve
@@ -314,30 +329,40 @@ __global__ void __launch_bounds__(kBlock) k_abf_finish(AbfArgs a)
         for (int j = 0; j < NA; ++j)
             for (int o = 32; o > 0; o >>= 1) acc[j] += __shfl_xor(acc[j], o, 64);
         if (threadIdx.x == 0) {
-            const AbfOut r = abf_solve(a, acc, pre);
-            if (blockIdx.x == 0) abf_commit(a, w, pre, r);
+            const AbfOut<D> r = abf_solve<D>(a, acc, pre);
+            if (blockIdx.x == 0) abf_commit<D>(a, w, pre, r);
 #pragma unroll
-            for (int d = 0; d < MD; ++d)
-                if (d < a.D) s_coef[d] = r.b[d];
+            for (int d = 0; d < D; ++d) s_coef[d] = r.b[d];
         }
     }
     __syncthreads();
     if (u < a.tabs.U) atom_add(a.tabs, Jw, s_coef, a.F, rows);
 }
 
+template <int D>
+hipError_t launch_abf_d(const AbfArgs &a, hipStream_t s)
+{
+    if (a.nblk == 0) {
+        hipLaunchKernelGGL(k_abf<D>, dim3(a.tabs.W), dim3(kBlock), 0, s, a);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_abf_part<D>, dim3((unsigned)a.nblk + 1, (unsigned)a.tabs.W), dim3(kBlock), 0, s, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_abf_finish<D>, dim3((unsigned)a.nblk, (unsigned)a.tabs.W), dim3(kBlock), 0, s, a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_abf(const AbfArgs &a, hipStream_t s)
 {
-    if (a.nblk == 0) {
-        hipLaunchKernelGGL(k_abf, dim3(a.tabs.W), dim3(kBlock), 0, s, a);
-        return hipGetLastError();
+    switch (a.D) {
+    case 1: return launch_abf_d<1>(a, s);
+    case 2: return launch_abf_d<2>(a, s);
+    case 3: return launch_abf_d<3>(a, s);
+    default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(k_abf_part, dim3((unsigned)a.nblk, (unsigned)a.tabs.W), dim3(kBlock), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_abf_finish, dim3((unsigned)a.nblk, (unsigned)a.tabs.W), dim3(kBlock), 0, s, a);
-    return hipGetLastError();
 }
 
 }  // namespace sx
