@@ -68,10 +68,10 @@ struct Plan {
     // metadynamics bias on a grid: nodes per grid, grids (hill lists), and
     // in the state the node values, gradients and pending-hill counts
     int64_t mg_N = 0;
-    int32_t mg_L = 0, mg_n[kMaxBiasDim] = {0, 0, 0};
+    int32_t mg_L = 0, mg_slices = 1, mg_n[kMaxBiasDim] = {0, 0, 0};
     Sub s_mgV, s_mgG, s_mgPend;
     // harmonic windows: sample counts and sums (state), centres (workspace)
-    Sub s_umN, s_umS1, s_umS2, w_hbXi0, w_mgTick, w_shTick;
+    Sub s_umN, s_umS1, s_umS2, w_hbXi0, w_mgTick, w_mgPart, w_shTick;
     // ABF momentum estimator: previous W p, bias and flag per walker (state),
     // inverse masses per atom (workspace)
     Sub s_abfWp, s_abfB, s_abfHas, w_invm;
@@ -569,6 +569,8 @@ sx_status make_plan(sx_ctx *c)
     p.w_hbXi0 = lw.take(c->method == M_HARMONIC ? sizeof(double) * p.W * p.D : 0);
     p.w_shTick = lw.take(c->method == M_METAD ? sizeof(int32_t) : 0);
     p.w_mgTick = lw.take(c->mg_on ? sizeof(int32_t) * p.mg_L : 0);
+    p.mg_slices = c->mg_on ? grid_slices(p.D, p.mg_n, p.mg_N) : 1;
+    p.w_mgPart = lw.take(p.mg_slices > 1 ? sizeof(double) * p.mg_slices * (1 + p.D) * p.mg_N : 0);
     p.w_invm = lw.take(c->abf_est == 1 ? sizeof(double) * p.total_atoms : 0);
     p.w_slot_atom = lw.take(sizeof(int32_t) * p.nslots);
     p.w_slot_cv = lw.take(sizeof(int32_t) * p.nslots);
@@ -877,6 +879,8 @@ GridArgs grid_args(sx_ctx *c, const double *xi)
     g.G = at<double>(c->state, p.s_mgG);
     g.pend = at<int32_t>(c->state, p.s_mgPend);
     g.tick = at<int32_t>(c->ws, p.w_mgTick);
+    g.slices = p.mg_slices;
+    g.part = at<double>(c->ws, p.w_mgPart);
     for (int d = 0; d < kMaxBiasDim; ++d) g.c[d] = d < p.D ? at<float>(c->state, p.s_c[d]) : nullptr;
     g.h = at<float>(c->state, p.s_h);
     g.count = at<int32_t>(c->state, p.s_count);
@@ -2230,7 +2234,7 @@ sx_status sx_hills_set(sx_ctx *ctx, int32_t walker, const float *centers, const 
     int32_t k32 = (int32_t)K;
     if (e == hipSuccess) e = hipMemcpy(at<int32_t>(ctx->state, p.s_count) + wl, &k32, 4, hipMemcpyHostToDevice);
     if (e == hipSuccess && ctx->mg_on) {  // the list's grid from the new list
-        e = launch_grid_rebuild(grid_args(ctx, nullptr), wl, 1, ctx->stream);
+        e = launch_grid_rebuild(grid_args(ctx, nullptr), wl, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     }
     if (e != hipSuccess) return hip_fail(ctx, e, "hill upload");
