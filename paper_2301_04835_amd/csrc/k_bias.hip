@@ -523,16 +523,16 @@ __global__ void __launch_bounds__(kBlock) k_hill_step_one_tile(HillArgs a, CvSet
     float jr[kSmallPer][3];
     if (small_lane) {
         small_entries(a.small, a.F, wr.aoff, u, sg, nent, ent);
-        if (!FUSE) small_jacobian(a.small, a.J, ent, jr);
+        if (!FUSE) small_jacobian(a.J, ent, jr);
     }
     const int32_t cnt0 = ld_uniform(a.count);  // what the tile sees: only the deposit below changes it
     double acc[1 + D];
     hill_tile<D, U, FUSE, T>(a, cs, pos, 0, lds, s_xi, acc, lds_rows ? s_J : nullptr);
     if (FUSE && small_lane) {
         if (lds_rows)
-            small_jacobian(a.small, &s_J[0][0], ent, jr);
+            small_jacobian(&s_J[0][0], ent, jr);
         else
-            small_jacobian(a.small, a.J, ent, jr);
+            small_jacobian(a.J, ent, jr);
     }
     if (!FUSE) {
         if ((int)threadIdx.x < D) s_xi[threadIdx.x] = a.xi[threadIdx.x];

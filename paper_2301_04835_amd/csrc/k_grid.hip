@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
 #pragma unroll
         for (int d = 0; d < kMaxBiasDim; ++d) xi[d] = __shfl(xd, min(d, g.D - 1), 64);
         __syncthreads();  // s_J written (one wavefront)
-        small_jacobian(g.small, &s_J[0][0], ent, jr);  // slot < 4 D: every CV a dihedral
+        small_jacobian(&s_J[0][0], ent, jr);  // slot < 4 D: every CV a dihedral
     } else {
         // xi over the largest CV count with the index clamped to the last
         // CV (in bounds, the extra entries unused), so the loads are issued

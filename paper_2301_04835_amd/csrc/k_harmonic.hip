@@ -103,7 +103,7 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
         for (int d = 0; d < kMaxBiasDim; ++d)
             if (d < a.D) coef[d] = -(a.k[d] * displacement(a, d, s_xi[d], x0[d]));
         float jr[kSmallPer][3];
-        small_jacobian(a.small, &s_J[0][0], ent, jr);
+        small_jacobian(&s_J[0][0], ent, jr);
         small_forces(a.small, a.F, sg, nent, ent, jr, coef);
     }
     if (threadIdx.x == 0) {
