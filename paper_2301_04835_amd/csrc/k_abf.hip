@@ -252,7 +252,7 @@ __global__ void __launch_bounds__(kBlock) k_abf(AbfArgs a)
 // workgroup reads it while it changes.  Both are chains of dependent loads and
 // shuffles: with AbfPre ahead of the first block's atoms, three CVs' terms
 // reduced for any number of CVs and a slot's row loaded after its CV, the two
-// took 6.4 and 5.1 us on 2,500 touched atoms and two CVs; now 3.9 and 4.7.
+// took 6.4 and 5.1 us on 2,500 touched atoms and two CVs; now 3.6 and 4.3.
 
 // xi of walker w, the coordination numbers' values from their block records:
 // lane-strided sums, a fixed butterfly, times the scale (the value kernel's
@@ -269,8 +269,7 @@ __device__ __forceinline__ void fold_cn_values(const AbfArgs &a, int32_t w, doub
         const double *p = a.cn_vpart + (int64_t)w * a.vblk_per_walker + a.cn_vblk0[k];
         double v = 0.0;
         for (int b = lane; b < a.cn_nblk[k]; b += 64) v += p[b];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        v *= a.cn_scale[k];
+        v = wave_sum(v) * a.cn_scale[k];
         if (lane == 0) a.xi_ws[(int64_t)w * D + a.cn_d[k]] = v;
 #pragma unroll
         for (int d = 0; d < D; ++d)
@@ -326,8 +325,7 @@ __global__ void __launch_bounds__(kBlock) k_abf_finish(AbfArgs a)
             for (int j = 0; j < NA; ++j) acc[j] += r[j];
         }
 #pragma unroll
-        for (int j = 0; j < NA; ++j)
-            for (int o = 32; o > 0; o >>= 1) acc[j] += __shfl_xor(acc[j], o, 64);
+        for (int j = 0; j < NA; ++j) acc[j] = wave_sum(acc[j]);
         if (threadIdx.x == 0) {
             const AbfOut<D> r = abf_solve<D>(a, acc, pre);
             if (blockIdx.x == 0) abf_commit<D>(a, w, pre, r);

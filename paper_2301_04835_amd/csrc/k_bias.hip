@@ -450,14 +450,12 @@ __global__ void __launch_bounds__(64) k_hill_finalize_wave(HillArgs a, CvSet cs,
         for (int j = 0; j <= D; ++j) acc[j] += p[j];
     }
 #pragma unroll
-    for (int j = 0; j <= D; ++j)
-        for (int o = 32; o > 0; o >>= 1) acc[j] += __shfl_xor(acc[j], o, 64);
-    // every lane now holds the sums; take lane 0's bits so all agree
-#pragma unroll
-    for (int j = 0; j <= D; ++j) acc[j] = __shfl(acc[j], 0, 64);
+    for (int j = 0; j <= D; ++j) acc[j] = wave_sum(acc[j]);  // the same bits in every lane
     double coef[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) coef[d] = acc[1 + d] * a.inv_sig2[d];  // -dV/dxi
+    // ahead of lane 0's outputs, whose arithmetic then overlaps these stores
+    if (small_lane) small_forces(a.small, a.F, sg, nent, ent, jr, coef);
     if (lane == 0) {
         const double V = acc[0];
         bool finite = isfinite(V);
@@ -486,7 +484,6 @@ __global__ void __launch_bounds__(64) k_hill_finalize_wave(HillArgs a, CvSet cs,
             }
         }
     }
-    if (small_lane) small_forces(a.small, a.F, sg, nent, ent, jr, coef);
 }
 
 // The whole step in one launch when all the hills are one tile (one walker

@@ -37,6 +37,7 @@
 
 #include "sx_internal.h"
 #include "dev_cv.h"
+#include "dev_reduce.h"
 
 namespace sx {
 namespace {
@@ -654,7 +655,7 @@ __global__ void __launch_bounds__(kJacBlock, 5) k_cell_jac(CellArgs c, CvSet cs,
             if (last) break;
         }
         if (sideA) {  // the CV's partial over this block: fixed butterfly, then waves in order
-            for (int o = 32; o > 0; o >>= 1) ssum += __shfl_xor(ssum, o, 64);
+            ssum = wave_sum(ssum);
             if ((tid & 63) == 0) s_red[wave] = ssum;
             __syncthreads();
             if (tid == 0) {
@@ -675,7 +676,7 @@ __global__ void __launch_bounds__(kBlock) k_cn_cell_fin(CellArgs c, CvSet cs, do
     const double *p = c.part + ((int64_t)w * c.ncn + k) * c.nblk;
     double v = 0.0;
     for (int i = threadIdx.x; i < c.nblk; i += kBlock) v += p[i];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -251,6 +251,13 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
         V = 0.0;
         for (int d = 0; d < kMaxBiasDim; ++d) G[d] = 0.0;
     }
+    // ahead of lane 0's outputs, whose arithmetic then overlaps these stores
+    if (lane < g.small.U) {
+        double coef[kMaxBiasDim];
+#pragma unroll
+        for (int d = 0; d < kMaxBiasDim; ++d) coef[d] = -G[d];
+        small_forces(g.small, g.F, sg, nent, ent, jr, coef);
+    }
     if (lane == 0) {
         bool finite = isfinite(V);
         g.V_ws[w] = V;
@@ -282,12 +289,6 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
                 atomicOr(g.flags, kFlagCapacity);
             }
         }
-    }
-    if (lane < g.small.U) {
-        double coef[kMaxBiasDim];
-#pragma unroll
-        for (int d = 0; d < kMaxBiasDim; ++d) coef[d] = -G[d];
-        small_forces(g.small, g.F, sg, nent, ent, jr, coef);
     }
 }
 

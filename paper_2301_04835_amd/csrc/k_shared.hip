@@ -37,6 +37,7 @@
 // slots/s a loop of multiply-adds reaches (6.24 ms).
 #include "sx_internal.h"
 #include "dev_cv.h"
+#include "dev_reduce.h"
 #include "dev_gather.h"
 
 namespace sx {
@@ -253,8 +254,7 @@ __device__ __forceinline__ void block_sum0(double (&v)[N], double *lds)
 {
     // fixed tree: wave butterfly, then waves in index order; result in thread 0
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-        for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+    for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
         for (int k = 0; k < N; ++k) lds[(threadIdx.x >> 6) * N + k] = v[k];
@@ -436,11 +436,17 @@ __global__ void __launch_bounds__(64) k_hill_shared_finalize_wave(SharedArgs a)
         for (int j = 0; j <= D; ++j) acc[j] += p[j];
     }
 #pragma unroll
-    for (int j = 0; j <= D; ++j)
-        for (int o = 32; o > 0; o >>= 1) acc[j] += __shfl_xor(acc[j], o, 64);
+    for (int j = 0; j <= D; ++j) acc[j] = wave_sum(acc[j]);
     double dv[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) dv[d] = -acc[1 + d] * a.inv_sig2[d];
+    // ahead of lane 0's outputs, whose arithmetic then overlaps these stores
+    if (lane < a.small.U) {
+        double coef[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) coef[d] = -dv[d];
+        small_forces(a.small, a.F, sg, nent, ent, jr, coef);
+    }
     if (lane == 0) {
         const double V = acc[0];
         bool finite = isfinite(V);
@@ -467,12 +473,6 @@ __global__ void __launch_bounds__(64) k_hill_shared_finalize_wave(SharedArgs a)
             }
             shared_count(a, cnt);
         }
-    }
-    if (lane < a.small.U) {
-        double coef[D];
-#pragma unroll
-        for (int d = 0; d < D; ++d) coef[d] = -dv[d];
-        small_forces(a.small, a.F, sg, nent, ent, jr, coef);
     }
 }
 
