@@ -26,6 +26,7 @@
 #include "sx_internal.h"
 #include "dev_cv.h"
 #include "dev_gather.h"
+#include "dev_reduce.h"
 
 #include <cmath>
 
@@ -292,11 +293,9 @@ __global__ void __launch_bounds__(kBlock) k_mlp_fwd(MlpArgs a, const double *xi,
     // reduce over the 16 output lanes of each row group (fixed butterfly)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        for (int m = 1; m < 16; m <<= 1) {
-            yp[r] += __shfl_xor(yp[r], m, 64);
+        yp[r] = row16_sum(yp[r]);
 #pragma unroll
-            for (int d = 0; d < D; ++d) dyp[d][r] += __shfl_xor(dyp[d][r], m, 64);
-        }
+        for (int d = 0; d < D; ++d) dyp[d][r] = row16_sum(dyp[d][r]);
     }
     // CVs of this lane's four output samples (rows kg*4 + r), for the
     // certification lookup and the outputs
@@ -565,11 +564,9 @@ __global__ void __launch_bounds__(kTrainBlock) k_mlp_train(MlpArgs a, const doub
 #pragma unroll
             for (int d = 0; d < D; ++d) dy[d] = fmaf(w, s_x[(d + 1) * S + ls][nt * 16 + r16], dy[d]);
         }
-        for (int m = 1; m < 16; m <<= 1) {
-            y += __shfl_xor(y, m, 64);
+        y = row16_sum(y);
 #pragma unroll
-            for (int d = 0; d < D; ++d) dy[d] += __shfl_xor(dy[d], m, 64);
-        }
+        for (int d = 0; d < D; ++d) dy[d] = row16_sum(dy[d]);
         if (r16 == 0) {
             // targets in network units: (V - out_shift) / out_scale, G / out_scale
             const double inv_sc = 1.0 / a.out_scale;
