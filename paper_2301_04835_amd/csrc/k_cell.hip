@@ -506,10 +506,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Partners [b0, b1) of the staged window (uniform per wavefront) against its
 // 16 home atoms; live: this lane's atom counts.  bo: the lane's word of the
 // home operand, (-2 x, -2 y, -2 z, 1) by lane / 16; co = |o|^2 - R^2.
+// odd: no cull (a position in the window or o is outside its bound).
 template <bool S612, bool SIDEA>
-__device__ __forceinline__ void home_pairs(const Staged &sp, int b0, int b1, float3 o, float bo, float co, bool live, bool odd,
-                                           int32_t me, const PairCtx &k, const CvDesc &cv, const CellArgs &c,
-                                           const PosView &pos, HomeSum &g)
+__device__ __forceinline__ void home_pairs(const Staged &sp, int b0, int b1, float3 o, float bo, float co, bool live,
+                                           bool odd, int32_t me, const PairCtx &k, const CvDesc &cv,
+                                           const CellArgs &c, const PosView &pos, HomeSum &g)
 {
     const int lane = threadIdx.x & 63, quad = lane >> 4;
     // row r of a tile is its partner 4 (r % 4) + r / 4, so that a lane's rows
@@ -517,6 +518,7 @@ __device__ __forceinline__ void home_pairs(const Staged &sp, int b0, int b1, flo
     // fourth partner and keep about as many each
     const float *const pa = &sp.c[quad][kFar + 4 * (lane & 3) + ((lane & 15) >> 2)];
     const f32x4 cc = {co, co, co, co};
+    if (b0 >= b1) return;  // none of the atoms' ranges in this window (uniform): b0 may lie past its end
     uint32_t m0 = 0, m1 = 0;  // kept partners of the lane's current word and of the next
     int e0 = 0;               // byte offset of bit 0 of m0 in a staged array
     float a[kTiles];
