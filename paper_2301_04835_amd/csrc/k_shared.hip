@@ -249,25 +249,6 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared_cv(SharedArgs a, SharedC
     hill_shared<D, Q, kPerAll, true>(a, &fc);
 }
 
-template <int N>
-__device__ __forceinline__ void block_sum0(double (&v)[N], double *lds)
-{
-    // fixed tree: wave butterfly, then waves in index order; result in thread 0
-#pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int k = 0; k < N; ++k) lds[(threadIdx.x >> 6) * N + k] = v[k];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            double s = lds[k];
-            for (int q = 1; q < kBlock / 64; ++q) s += lds[q * N + k];
-            v[k] = s;
-        }
-}
-
 // does this launch append hills?  (the step counter was moved by the sum)
 __device__ __forceinline__ bool deposits(const SharedArgs &a)
 {
