@@ -46,7 +46,22 @@ namespace {
 constexpr int kStage = kBlock;  // hills staged in LDS at a time (one per lane)
 constexpr int64_t kMaxRecords = 8 * 65536;  // partial records of a sum at arbitrary points
 
-enum { kPerNone = 0, kPerAll = 1, kPerMixed = 2 };
+// kPerNarrow: any CVs, a periodic one narrower than kNarrow among them
+enum { kPerNone = 0, kPerAll = 1, kPerMixed = 2, kPerNarrow = 3 };
+
+// The exponent as w f (f - 1) + w / 4 cancels near a hill's centre: its error
+// is that of w / 4, 7.1 / sigma^2, in FP64, about 1e-14 / sigma^2 for three
+// CVs.  Narrower than kNarrow that would pass 2^-31 (the Gaussian's own float32
+// rounding is 2^-24; at 1e-5 rad sums came out up to 1.4e-5 off), so such sums keep the
+// square of a displacement in units of the width, two issue slots more.
+constexpr double kNarrow = 0.005;
+
+bool narrow(const SharedArgs &a)
+{
+    for (int d = 0; d < a.D; ++d)
+        if (a.period[d] > 0.0 && a.inv_sig2[d] * (kNarrow * kNarrow) > 1.0) return true;
+    return false;
+}
 
 // Queries per lane (Q) and lanes that hold queries (ql) of a sum over nq
 // queries.  More queries per lane amortise the staged hills' LDS reads; they
@@ -137,7 +152,9 @@ __device__ __forceinline__ void hill_shared(const SharedArgs &a, const SharedCv 
     // scale of CV d: turns (periodic), or units in which the quadratic form
     // is the square; wt: the periodic CV's weight of f (f - 1) + 1/4
     constexpr double kInvTurn = 0.15915494309189533577, kTurn = 6.2831853071795864769;
-    double sc[D], wt[D], q0 = 0.0;
+    // (kPerNarrow: the period and its inverse in the scaled units)
+    constexpr bool kScaled = PER == kPerNarrow;
+    double sc[D], wt[D], per[D], iper[D], q0 = 0.0;
     bool wrap[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -145,6 +162,8 @@ __device__ __forceinline__ void hill_shared(const SharedArgs &a, const SharedCv 
         wrap[d] = PER == kPerAll || (PER == kPerMixed && a.period[d] > 0.0);
         wt[d] = wrap[d] ? s2 * (kTurn * kTurn) : 0.0;
         sc[d] = wrap[d] ? kInvTurn : sqrt(s2);
+        per[d] = kScaled ? a.period[d] * sc[d] : 0.0;
+        iper[d] = kScaled ? a.inv_period[d] / sc[d] : 0.0;
         q0 += 0.25 * wt[d];
     }
     double xs[Q][D];
@@ -194,6 +213,7 @@ __device__ __forceinline__ void hill_shared(const SharedArgs &a, const SharedCv 
                             x[d] = __builtin_amdgcn_fract(x[d]);
                             qd = fma(x[d], fma(wt[d], x[d], -wt[d]), qd);
                         } else {
+                            if (kScaled && per[d] > 0.0) x[d] = fma(-per[d], rint(x[d] * iper[d]), x[d]);
                             qd = fma(x[d], x[d], qd);
                         }
                     }
@@ -634,15 +654,16 @@ hipError_t launch_shared_d(const SharedArgs &a, const SharedCv *cv, hipStream_t 
         any = any || a.period[d] > 0.0;
         all = all && a.period[d] > 0.0;
     }
-    const int per = all ? kPerAll : (any ? kPerMixed : kPerNone);
+    const int per = narrow(a) ? kPerNarrow : all ? kPerAll : (any ? kPerMixed : kPerNone);
 #define SX_SHARED_LAUNCH(QQ)                                                                                       \
     case QQ:                                                                                                       \
         if (cv) hipLaunchKernelGGL((k_hill_shared_cv<D, QQ>), grid, dim3(kBlock), 0, s, b, *cv);                   \
         else if (per == kPerAll) hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerAll>), grid, dim3(kBlock), 0, s, b); \
         else if (per == kPerNone) hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerNone>), grid, dim3(kBlock), 0, s, b); \
+        else if (per == kPerNarrow) hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerNarrow>), grid, dim3(kBlock), 0, s, b); \
         else hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerMixed>), grid, dim3(kBlock), 0, s, b);                   \
         break;
-    if (cv && !all) return hipErrorInvalidValue;  // dihedrals only
+    if (cv && per != kPerAll) return hipErrorInvalidValue;  // shared_sums_cvs
     switch (Q) {
         SX_SHARED_LAUNCH(1)
         SX_SHARED_LAUNCH(2)
@@ -686,6 +707,13 @@ int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target)
             break;
         }
     return (int32_t)std::max<int64_t>(1, std::min(nc, most));
+}
+
+bool shared_sums_cvs(const SharedArgs &a)
+{
+    for (int d = 0; d < a.D; ++d)
+        if (!(a.period[d] > 0.0)) return false;
+    return !narrow(a);
 }
 
 hipError_t launch_hill_shared(const SharedArgs &a, hipStream_t s, const SharedCv *cv)

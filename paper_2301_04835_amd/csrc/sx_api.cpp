@@ -952,8 +952,9 @@ sx_status enqueue_step(sx_ctx *c, const void *pos, int32_t dtype, int32_t layout
                            p.small.U > 0 && forces != nullptr && p.nslots <= 4 * kMaxBiasDim;
     // the harmonic kernel evaluates dihedral CVs itself
     const bool fuse_harmonic = c->method == M_HARMONIC && p.all_dihedral;
-    // the shared sum evaluates dihedral CVs itself
-    const bool fuse_shared = c->method == M_METAD && c->shared && !c->mg_on && !c->sg_on && p.all_dihedral;
+    // the shared sum evaluates dihedral CVs itself (but for narrow hills)
+    const bool fuse_shared = c->method == M_METAD && c->shared && !c->mg_on && !c->sg_on && p.all_dihedral &&
+                             shared_sums_cvs(shared_args(c, 0, xi, p.W));
     if (c->sg_on) return enqueue_surrogate_step(c, pv, step, xi, J, xi_out, V_out, dVdxi_out, forces, layout);
     double *J64 = c->method == M_ABF ? at<double>(c->ws, p.w_J64) : nullptr;
     // ABF in two launches (without FUNN, which reads xi first) sums the

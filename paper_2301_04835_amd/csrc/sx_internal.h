@@ -418,6 +418,8 @@ hipError_t launch_grid_eval(const GridArgs &g, int32_t l, const double *xi, int6
 // and at most 8 x 65536 (chunk, query) records unless one chunk has more
 int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target = 0);
 hipError_t launch_hill_shared(const SharedArgs &a, hipStream_t s, const SharedCv *cv = nullptr);
+// whether that launch takes `cv` when every CV is a dihedral (not with narrow hills)
+bool shared_sums_cvs(const SharedArgs &a);
 // cell lists (which & 1), then every cell-list coordination number's value
 // into xi and the gradients of its members (which & 2)
 hipError_t launch_cell_cv(const CellArgs &c, const CvSet &cs, const PosView &pos, double *xi, hipStream_t s,
