@@ -22,7 +22,9 @@
 //     x - P rint(x / P)).  The sum of e (f - 1/2) is formed once per chunk.
 //     Summing the products in FP32 would lose digits where the terms of
 //     dV/dxi cancel;
-//   * periodicity is a template parameter (all, none, or per CV);
+//   * which CVs are periodic is a template parameter, a bit per CV (8,191
+//     points on 200,000 hills, an angle and a distance: 680 us; with a test of
+//     the period in the pair loop 1,149);
 //   * when every CV is a dihedral a step's workgroups evaluate their queries'
 //     CVs themselves (FP64) while their first hills are in flight, which
 //     saves the CV kernel's launch; the first chunk's workgroups store xi and
@@ -46,21 +48,28 @@ namespace {
 constexpr int kStage = kBlock;  // hills staged in LDS at a time (one per lane)
 constexpr int64_t kMaxRecords = 8 * 65536;  // partial records of a sum at arbitrary points
 
-// kPerNarrow: any CVs, a periodic one narrower than kNarrow among them
-enum { kPerNone = 0, kPerAll = 1, kPerMixed = 2, kPerNarrow = 3 };
+// Periodic CVs of a shared sum: bit d for CV d, or kNarrowForm where one of
+// them is narrower than kNarrow; of the fallback sums, one of the three.
+constexpr int kNarrowForm = -1;
+constexpr int all_periodic(int D) { return (1 << D) - 1; }
+enum { kPerNone = 0, kPerAll = 1, kPerMixed = 2 };
 
 // The exponent as w f (f - 1) + w / 4 cancels near a hill's centre: its error
 // is that of w / 4, 7.1 / sigma^2, in FP64, about 1e-14 / sigma^2 for three
 // CVs.  Narrower than kNarrow that would pass 2^-31 (the Gaussian's own float32
-// rounding is 2^-24; at 1e-5 rad sums came out up to 1.4e-5 off), so such sums keep the
-// square of a displacement in units of the width, two issue slots more.
+// rounding is 2^-24; at 1e-5 rad sums came out up to 1.4e-5 off), so such sums
+// keep the square of a displacement in units of the width, two issue slots more.
 constexpr double kNarrow = 0.005;
 
-bool narrow(const SharedArgs &a)
+int periodic_form(const SharedArgs &a)
 {
+    int m = 0;
     for (int d = 0; d < a.D; ++d)
-        if (a.period[d] > 0.0 && a.inv_sig2[d] * (kNarrow * kNarrow) > 1.0) return true;
-    return false;
+        if (a.period[d] > 0.0) {
+            if (a.inv_sig2[d] * (kNarrow * kNarrow) > 1.0) return kNarrowForm;
+            m |= 1 << d;
+        }
+    return m;
 }
 
 // Queries per lane (Q) and lanes that hold queries (ql) of a sum over nq
@@ -152,14 +161,14 @@ __device__ __forceinline__ void hill_shared(const SharedArgs &a, const SharedCv 
     // scale of CV d: turns (periodic), or units in which the quadratic form
     // is the square; wt: the periodic CV's weight of f (f - 1) + 1/4
     constexpr double kInvTurn = 0.15915494309189533577, kTurn = 6.2831853071795864769;
-    // (kPerNarrow: the period and its inverse in the scaled units)
-    constexpr bool kScaled = PER == kPerNarrow;
+    // (kNarrowForm: all of them scaled, and the periods with them)
+    constexpr bool kScaled = PER == kNarrowForm;
     double sc[D], wt[D], per[D], iper[D], q0 = 0.0;
     bool wrap[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         const double s2 = 0.72134752044448170368 * a.inv_sig2[d];  // log2(e) / (2 sigma^2)
-        wrap[d] = PER == kPerAll || (PER == kPerMixed && a.period[d] > 0.0);
+        wrap[d] = !kScaled && (PER >> d & 1);
         wt[d] = wrap[d] ? s2 * (kTurn * kTurn) : 0.0;
         sc[d] = wrap[d] ? kInvTurn : sqrt(s2);
         per[d] = kScaled ? a.period[d] * sc[d] : 0.0;
@@ -266,7 +275,7 @@ __global__ void __launch_bounds__(kBlock) k_hill_shared(SharedArgs a)
 template <int D, int Q>
 __global__ void __launch_bounds__(kBlock) k_hill_shared_cv(SharedArgs a, SharedCv fc)
 {
-    hill_shared<D, Q, kPerAll, true>(a, &fc);
+    hill_shared<D, Q, all_periodic(D), true>(a, &fc);
 }
 
 // does this launch append hills?  (the step counter was moved by the sum)
@@ -606,6 +615,17 @@ bool small_finalize(const SharedArgs &a)
     return a.do_forces && a.small.on && a.small.U > 0 && a.nchunk >= 1 && a.tabs.W == a.nq;
 }
 
+template <int D, int Q, int PER = kNarrowForm>
+void launch_sum(const SharedArgs &a, const SharedCv *cv, dim3 grid, hipStream_t s)
+{
+    if (cv)
+        hipLaunchKernelGGL((k_hill_shared_cv<D, Q>), grid, dim3(kBlock), 0, s, a, *cv);
+    else if (periodic_form(a) == PER)
+        hipLaunchKernelGGL((k_hill_shared<D, Q, PER>), grid, dim3(kBlock), 0, s, a);
+    else if constexpr (PER < all_periodic(D))
+        launch_sum<D, Q, PER + 1>(a, cv, grid, s);
+}
+
 template <int D>
 hipError_t launch_shared_d(const SharedArgs &a, const SharedCv *cv, hipStream_t s)
 {
@@ -649,28 +669,13 @@ hipError_t launch_shared_d(const SharedArgs &a, const SharedCv *cv, hipStream_t 
     b.rec_ch = per_query ? 1 : a.nq;
     b.rec_q = per_query ? a.nchunk : 1;
     const dim3 grid(a.nchunk, (unsigned)((a.nq + ql * Q - 1) / (ql * Q)));
-    bool any = false, all = true;
-    for (int d = 0; d < D; ++d) {
-        any = any || a.period[d] > 0.0;
-        all = all && a.period[d] > 0.0;
-    }
-    const int per = narrow(a) ? kPerNarrow : all ? kPerAll : (any ? kPerMixed : kPerNone);
-#define SX_SHARED_LAUNCH(QQ)                                                                                       \
-    case QQ:                                                                                                       \
-        if (cv) hipLaunchKernelGGL((k_hill_shared_cv<D, QQ>), grid, dim3(kBlock), 0, s, b, *cv);                   \
-        else if (per == kPerAll) hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerAll>), grid, dim3(kBlock), 0, s, b); \
-        else if (per == kPerNone) hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerNone>), grid, dim3(kBlock), 0, s, b); \
-        else if (per == kPerNarrow) hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerNarrow>), grid, dim3(kBlock), 0, s, b); \
-        else hipLaunchKernelGGL((k_hill_shared<D, QQ, kPerMixed>), grid, dim3(kBlock), 0, s, b);                   \
-        break;
-    if (cv && per != kPerAll) return hipErrorInvalidValue;  // shared_sums_cvs
+    if (cv && !shared_sums_cvs(a)) return hipErrorInvalidValue;
     switch (Q) {
-        SX_SHARED_LAUNCH(1)
-        SX_SHARED_LAUNCH(2)
-        SX_SHARED_LAUNCH(4)
+    case 1: launch_sum<D, 1>(b, cv, grid, s); break;
+    case 2: launch_sum<D, 2>(b, cv, grid, s); break;
+    case 4: launch_sum<D, 4>(b, cv, grid, s); break;
     default: return hipErrorInvalidValue;
     }
-#undef SX_SHARED_LAUNCH
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (per_query && small_finalize(b))
@@ -709,12 +714,7 @@ int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target)
     return (int32_t)std::max<int64_t>(1, std::min(nc, most));
 }
 
-bool shared_sums_cvs(const SharedArgs &a)
-{
-    for (int d = 0; d < a.D; ++d)
-        if (!(a.period[d] > 0.0)) return false;
-    return !narrow(a);
-}
+bool shared_sums_cvs(const SharedArgs &a) { return periodic_form(a) == all_periodic(a.D); }
 
 hipError_t launch_hill_shared(const SharedArgs &a, hipStream_t s, const SharedCv *cv)
 {

@@ -1,0 +1,54 @@
+"""Times of calls next to those of their neighbours: a form of a call may not
+cost a multiple of another that does the same work.  Each bound lies midway
+between what was measured and the fault it stands against; times are the best
+of several rounds in one process.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2301_04835_amd import Sampler
+
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+RG = {"kind": "gyration", "idx": [0, 1, 2, 3, 4, 5]}
+
+
+def best_us(call, reps, rounds=7):
+    call()
+    torch.cuda.synchronize()
+    t = []
+    for _ in range(rounds):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        t.append(a.elapsed_time(b) * 1e3 / reps)
+    return min(t)
+
+
+def eval_us(per, n, K):
+    g = np.random.default_rng(n)
+    s = Sampler(0)
+    s.add_cvs([{"kind": "dihedral", "idx": [d, d + 1, d + 2, d + 3]} if p else RG for d, p in enumerate(per)])
+    s.metad([0.35 if p else 0.03 for p in per], 1.0, 300.0, 6.0, 500, K)
+    s.bind()
+    draw = lambda m: np.stack([g.uniform(-np.pi, np.pi, m) if p else g.normal(0.25, 0.05, m) for p in per], 1)
+    s.hills_set(0, draw(K).astype(np.float32), np.ones(K, np.float32))
+    x = dev(draw(n))
+    V = torch.empty(n, dtype=torch.float64, device=x.device)
+    dV = torch.empty((n, len(per)), dtype=torch.float64, device=x.device)
+    return best_us(lambda: s.bias_eval_noalloc(x, V, dV), 3)
+
+
+@pytest.mark.parametrize("n", [700, 8191, 20000])
+@pytest.mark.parametrize("per", [[True, False], [False, True], [True, False, True], [False, True, False]])
+def test_mixed_sets_sum_as_fast_as_angles(gpu, per, n):
+    """A CV without a period takes two operations a pair, an angle four."""
+    mixed, angles = eval_us(per, n, 200000), eval_us([True] * len(per), n, 200000)
+    print(per, n, round(mixed, 1), round(angles, 1))
+    assert mixed <= 1.15 * angles
