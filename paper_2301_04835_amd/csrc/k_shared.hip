@@ -73,12 +73,24 @@ int periodic_form(const SharedArgs &a)
 }
 
 // Queries per lane (Q) and lanes that hold queries (ql) of a sum over nq
-// queries.  More queries per lane amortise the staged hills' LDS reads; they
-// need enough query blocks left to fill the chip: 4 from 8,192 points on, 2
-// from 1,024, else 1.
-void shared_shape(int64_t nq, int &Q, int &ql)
+// queries of a list with room for cap hills.  More queries per lane amortise
+// the staged hills' LDS reads, but a lane's queries are one chain: their start
+// and their sums at the end are paid by fewer wavefronts.  So Q rises with the
+// pairs a launch has (by the capacity: the count is on the device).  Two
+// angles, us with Q = 1, 2, 4:
+//     1,000 hills x  8,192 points   11.1  11.5  14.9
+//    10,000 hills x  4,096          27.5  28.8  29.6
+//    10,000 hills x 16,384          84.5  80.6  81.8
+//   100,000 hills x  1,024          56.3  54.0  56.2
+//    30,000 hills x 16,384         241.2 224.3 220.2
+//   100,000 hills x 16,384         784.2 729.1 712.5
+// and a list with spare capacity (1,000 hills in room for 300,000) pays up to
+// 1.3 times its best at 1,024 points.  More than 65,536 queries are walkers:
+// 4, so that their blocks fit a grid.
+void shared_shape(int64_t nq, int64_t cap, int &Q, int &ql)
 {
-    Q = nq >= 8192 ? 4 : nq >= 1024 ? 2 : 1;
+    const double pairs = (double)cap * (double)nq;
+    Q = nq > 65536 || (nq >= 8192 && pairs >= 0x1p29) ? 4 : nq >= 1024 && pairs >= 0x1p26 ? 2 : 1;
     ql = 64;
     while (ql > 4 && nq <= ql / 2) ql /= 2;
 }
@@ -661,7 +673,7 @@ hipError_t launch_shared_d(const SharedArgs &a, const SharedCv *cv, hipStream_t 
     }
     SharedArgs b = a;
     int Q, ql;
-    shared_shape(a.nq, Q, ql);
+    shared_shape(a.nq, a.cap, Q, ql);
     for (b.lg = 0; (ql << b.lg) < 64;) ++b.lg;
     // many chunks: one wavefront (or workgroup) reads a query's records, kept
     // next to each other; few: a lane per query reads them chunk after chunk
@@ -690,21 +702,31 @@ hipError_t launch_shared_d(const SharedArgs &a, const SharedCv *cv, hipStream_t 
 
 }  // namespace
 
+// one chunk per stage of the capacity, and no more than the partial records hold
+int64_t most_chunks(int64_t cap, int64_t nq)
+{
+    return std::min<int64_t>((cap + kStage - 1) / kStage, kMaxRecords / std::max<int64_t>(1, nq));
+}
+
+int64_t shared_records(int64_t cap, int64_t nq) { return std::max<int64_t>(1, most_chunks(cap, nq)) * nq; }
+
 // Every workgroup has an equal share of the hills and the queries, so the
 // chunks are chosen to give each of the 256 CUs the same number of
-// workgroups: k = 4 by default (8 with 4 queries per lane, whose workgroups
-// run for milliseconds), fewer where the capacity has too few stages.  256
+// workgroups: k = 4 by default (8 with 4 queries per lane, the longest
+// sums), fewer where the capacity has too few stages.  256
 // walkers on 100,000 hills, us per step: 27.6 (k = 1), 23.7 (2), 22.6 (3),
 // 22.8 (4), 24.3 (6), 25.1 (8); 100 walkers on 50,000 hills in three CVs:
-// 14.9 at 2 x 256 workgroups, 16.7 at 548.
+// 14.9 at 2 x 256 workgroups, 16.7 at 548.  8,192 points on 100,000 hills with
+// Q = 4: 365.6 (k = 4), 357.6 (8); with Q = 2 369.9 and 363.6, but 28.8 and
+// 30.3 for 4,096 points on 10,000.
 int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target)
 {
     constexpr int kCus = 256;
     int Q, ql;
-    shared_shape(nq, Q, ql);
+    shared_shape(nq, cap, Q, ql);
     if (target <= 0) target = (Q == 4 ? 8 : 4) * kCus;
     const int64_t nqb = std::max<int64_t>(1, (nq + (int64_t)ql * Q - 1) / ((int64_t)ql * Q));
-    const int64_t most = std::min<int64_t>((cap + kStage - 1) / kStage, kMaxRecords / std::max<int64_t>(1, nq));
+    const int64_t most = most_chunks(cap, nq);
     int64_t nc = target < kCus ? target / nqb : most;
     for (int64_t k = target / kCus; k >= 1; --k)
         if (k * kCus / nqb <= most) {

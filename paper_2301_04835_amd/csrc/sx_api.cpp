@@ -476,7 +476,7 @@ sx_status make_plan(sx_ctx *c)
     for (int w = 0; w < nlists; ++w) maxcap = std::max<int64_t>(maxcap, p.hill_cap[w]);
     p.shared_records = 0;
     if (c->method == M_METAD) {
-        p.shared_records = (int64_t)shared_chunks(maxcap, kEvalBatch) * kEvalBatch;
+        p.shared_records = shared_records(maxcap, kEvalBatch);
         if (c->shared)  // the step's sum at any tuning: at most one chunk per 256-hill stage
             p.shared_records = std::max<int64_t>(p.shared_records, (maxcap + 255) / 256 * (int64_t)p.W);
     }

@@ -417,6 +417,8 @@ hipError_t launch_grid_eval(const GridArgs &g, int32_t l, const double *xi, int6
 // workgroups (0: the default), at most one chunk per 256 hills of capacity
 // and at most 8 x 65536 (chunk, query) records unless one chunk has more
 int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target = 0);
+// records that such sums over at most nq <= 65536 queries need at the default
+int64_t shared_records(int64_t cap, int64_t nq);
 hipError_t launch_hill_shared(const SharedArgs &a, hipStream_t s, const SharedCv *cv = nullptr);
 // whether that launch takes `cv` when every CV is a dihedral (not with narrow hills)
 bool shared_sums_cvs(const SharedArgs &a);
