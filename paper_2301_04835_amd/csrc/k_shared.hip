@@ -724,11 +724,12 @@ int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target)
     constexpr int kCus = 256;
     int Q, ql;
     shared_shape(nq, cap, Q, ql);
-    if (target <= 0) target = (Q == 4 ? 8 : 4) * kCus;
     const int64_t nqb = std::max<int64_t>(1, (nq + (int64_t)ql * Q - 1) / ((int64_t)ql * Q));
+    if (target > 0)  // the caller's number, rounded up to whole chunks
+        return (int32_t)std::max<int64_t>(1, std::min((cap + kStage - 1) / kStage, (target + nqb - 1) / nqb));
     const int64_t most = most_chunks(cap, nq);
-    int64_t nc = target < kCus ? target / nqb : most;
-    for (int64_t k = target / kCus; k >= 1; --k)
+    int64_t nc = most;
+    for (int64_t k = Q == 4 ? 8 : 4; k >= 1; --k)
         if (k * kCus / nqb <= most) {
             nc = k * kCus / nqb;
             break;

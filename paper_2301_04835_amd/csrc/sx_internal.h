@@ -413,9 +413,9 @@ int32_t grid_slices(int32_t D, const int32_t *n, int64_t N);
 hipError_t launch_grid_rebuild(const GridArgs &g, int32_t l, hipStream_t s);
 hipError_t launch_grid_eval(const GridArgs &g, int32_t l, const double *xi, int64_t n, double *V, double *dV,
                             hipStream_t s);
-// hill chunks of a shared-list sum over nq queries: about `target`
-// workgroups (0: the default), at most one chunk per 256 hills of capacity
-// and at most 8 x 65536 (chunk, query) records unless one chunk has more
+// hill chunks of a shared-list sum over nq queries: `target` workgroups (0:
+// the default), at most one chunk per 256 hills of capacity; by default also
+// at most 8 x 65536 (chunk, query) records unless one chunk has more
 int32_t shared_chunks(int64_t cap, int64_t nq, int32_t target = 0);
 // records that such sums over at most nq <= 65536 queries need at the default
 int64_t shared_records(int64_t cap, int64_t nq);
