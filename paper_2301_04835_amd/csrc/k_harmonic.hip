@@ -12,6 +12,8 @@
 namespace sx {
 namespace {
 
+constexpr int kFuseBlock = 128;  // the dihedrals' wavefront and the force table's
+
 // xi - xi0 of CV d, minimum image where it is periodic
 __device__ __forceinline__ double displacement(const HarmonicArgs &a, int d, double x, double x0)
 {
@@ -21,25 +23,27 @@ __device__ __forceinline__ double displacement(const HarmonicArgs &a, int d, dou
 }
 
 // one workgroup per walker; thread 0 owns the window's bookkeeping and
-// requests its centre and running sums before anything waits.  With fuse_cv
-// thread d < D first evaluates dihedral d (FP64) from the positions: its
-// value into LDS and the workspace, its gradient rows into the workspace's
-// Jacobian, which the gather below reads after the barrier.  When the force
-// table fits the kernel arguments too, the second wavefront requests its rows
-// and the atoms' forces and forms the coefficients itself, and takes the
-// gradient rows from LDS: after the dihedrals' barrier it only multiplies and
-// stores (four dependent table loads, another barrier behind thread 0's
-// stores and a trip of the gradients through L2 before: 256 windows 5.93 us,
-// now 5.66).
-__global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
+// requests its centre and running sums before anything waits.  With FUSE
+// (dihedrals, whose force table always fits the kernel arguments) thread d < D
+// first evaluates dihedral d (FP64) from the positions: its value into LDS and
+// the workspace, its gradient rows into LDS and the workspace's Jacobian.  The
+// second wavefront requests the table's rows and the atoms' forces and forms
+// the coefficients itself: after the dihedrals' barrier it only multiplies and
+// stores (four dependent table loads, another barrier behind thread 0's stores
+// and a trip of the gradients through L2 before: a replayed step of 256
+// windows in two angles 5.8 us, now 4.7).  A kernel of two wavefronts for it
+// and one of four for the others: as branches of one kernel of four, its
+// registers left room for 7 of 8 wavefronts a SIMD and 2,048 windows took a
+// second round (8.7 us a step; 6.6 now, 1,700 windows 6.6).
+template <bool FUSE>
+__global__ void __launch_bounds__(FUSE ? kFuseBlock : kBlock) k_harmonic(HarmonicArgs a)
 {
     __shared__ double s_coef[kMaxCv];
     __shared__ double s_xi[kMaxBiasDim];
     __shared__ float s_J[kLdsRows][3];
     const int32_t w = blockIdx.x;
-    const bool small = a.fuse_cv && a.do_forces && a.small.on && a.nslots <= kLdsRows;  // uniform
     const int u = (int)threadIdx.x - 64;
-    const bool small_lane = small && u >= 0 && u < a.small.U;
+    const bool small_lane = FUSE && a.do_forces && u >= 0 && u < a.small.U;
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
     int32_t ent[kSmallPer];
@@ -61,7 +65,7 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
         }
         if (a.accumulate) np0 = a.n[w];
     }
-    if (a.fuse_cv) {
+    if (FUSE) {
         if ((int)threadIdx.x < a.D) {
             // atom indices and slot selected by value from the kernel
             // arguments: no load between them and the positions
@@ -88,14 +92,12 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
                 js[3 * q] = (float)gr[q].x;
                 js[3 * q + 1] = (float)gr[q].y;
                 js[3 * q + 2] = (float)gr[q].z;
-                if (small) {
-                    s_J[slot0 + q][0] = (float)gr[q].x;
-                    s_J[slot0 + q][1] = (float)gr[q].y;
-                    s_J[slot0 + q][2] = (float)gr[q].z;
-                }
+                s_J[slot0 + q][0] = (float)gr[q].x;
+                s_J[slot0 + q][1] = (float)gr[q].y;
+                s_J[slot0 + q][2] = (float)gr[q].z;
             }
         }
-        __syncthreads();  // s_xi, and the Jacobian rows the gather reads
+        __syncthreads();  // s_xi and s_J
     }
     if (small_lane) {
         double coef[kMaxBiasDim] = {0.0, 0.0, 0.0};
@@ -112,7 +114,7 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
 #pragma unroll
         for (int d = 0; d < kMaxBiasDim; ++d) {
             if (d >= a.D) break;
-            const double x = a.fuse_cv ? s_xi[d] : a.xi[(int64_t)w * a.D + d];
+            const double x = FUSE ? s_xi[d] : a.xi[(int64_t)w * a.D + d];
             const double t = displacement(a, d, x, x0[d]);
             Dv[d] = t;
             const double g = a.k[d] * t;
@@ -139,7 +141,7 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
         }
         if (w == 0 && a.count_step) *a.dstep = a.step >= 0 ? a.step + 1 : *a.dstep + 1;
     }
-    if (small) return;  // uniform
+    if (FUSE) return;
     __syncthreads();
     if (a.do_forces) gather_forces(a.tabs, a.J + (int64_t)w * a.nslots * 3, w, s_coef, a.F);
 }
@@ -149,7 +151,11 @@ __global__ void __launch_bounds__(kBlock) k_harmonic(HarmonicArgs a)
 hipError_t launch_harmonic(const HarmonicArgs &a, hipStream_t s)
 {
     if (a.tabs.W < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_harmonic, dim3(a.tabs.W), dim3(kBlock), 0, s, a);
+    if (a.fuse_cv && (!a.small.on || a.nslots > kLdsRows)) return hipErrorInvalidValue;
+    if (a.fuse_cv)
+        hipLaunchKernelGGL(k_harmonic<true>, dim3(a.tabs.W), dim3(kFuseBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_harmonic<false>, dim3(a.tabs.W), dim3(kBlock), 0, s, a);
     return hipGetLastError();
 }
 

@@ -951,7 +951,8 @@ sx_status enqueue_step(sx_ctx *c, const void *pos, int32_t dtype, int32_t layout
     const bool fuse_grid = c->method == M_METAD && c->mg_on && !c->sg_on && p.all_dihedral && p.small.on &&
                            p.small.U > 0 && forces != nullptr && p.nslots <= 4 * kMaxBiasDim;
     // the harmonic kernel evaluates dihedral CVs itself
-    const bool fuse_harmonic = c->method == M_HARMONIC && p.all_dihedral;
+    const bool fuse_harmonic = c->method == M_HARMONIC && p.all_dihedral && p.small.on &&
+                               p.nslots <= 4 * kMaxBiasDim;
     // the shared sum evaluates dihedral CVs itself (but for narrow hills)
     const bool fuse_shared = c->method == M_METAD && c->shared && !c->mg_on && !c->sg_on && p.all_dihedral &&
                              shared_sums_cvs(shared_args(c, 0, xi, p.W));

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2301_04835_amd import Sampler
+from paper_2301_04835_amd import Sampler, synth
 
 from gpu_util import dev
 
@@ -61,3 +61,22 @@ def test_short_lists_stay_fast_with_many_points(gpu, D):
     below, above = eval_us([True] * D, 8191, 1000), eval_us([True] * D, 8192, 1000)
     print(D, round(below, 1), round(above, 1))
     assert above <= 1.2 * below
+
+
+@pytest.mark.parametrize("D", [1, 2, 3])
+def test_windows_take_no_second_round(gpu, D):
+    """2,048 windows fit the chip at once, as 1,700 do (1.3 times otherwise)."""
+    t = []
+    for W in (1700, 2048):
+        pos = np.concatenate([synth.chain_template(22, 60 + w % 64) for w in range(W)]).astype(np.float32)
+        s = Sampler(0)
+        s.add_cvs([{"kind": "dihedral", "idx": [d, d + 1, d + 2, d + 3]} for d in range(D)])
+        s.set_walkers(np.arange(W + 1) * 22)
+        s.harmonic([100.0] * D, np.zeros((W, D)))
+        s.bind()
+        P = dev(pos)
+        F = torch.zeros_like(P)
+        s.graph_capture(20, P, forces=F)
+        t.append(best_us(s.graph_launch, 5) / 20)
+    print(D, [round(x, 2) for x in t])
+    assert t[1] <= 1.12 * t[0]
