@@ -87,37 +87,36 @@ __device__ __forceinline__ void block_sum(double (&v)[N], double *lds /* N * kBl
 // ------------------------------------------------------- radius of gyration
 // Rg = sqrt((1/n) sum |r_i - c|^2), c = (1/n) sum r_i; dRg/dr_i = (r_i - c)/(n Rg).
 // One workgroup per (walker w, gyration CV j); lds: 4 * kBlock / 64 doubles.
-// A thread's first kGyrKeep members stay in registers, their loads in flight
-// together; members beyond are read again in each pass.  With the same for
-// the partners' staging below, the CVs of a 50,000-atom box (Rg of 500, CN of
+// A thread's first KEEP members stay in registers, their loads in flight
+// together; members beyond are read again in each pass.  One member a thread
+// while that is all of them, else kGyrKeep: a step with the Rg of 6 atoms of
+// 4,096 walkers takes 21.2 us with one, 23.7 with four (22.0 with the loads in
+// each pass), of 500 atoms 37.2 with four (42.6).  With the same for the
+// partners' staging below, the CVs of a 50,000-atom box (Rg of 500, CN of
 // 1,000 x 1,000, FP64) take 10.1 us, 10.9 before: the pair terms bound it.
 constexpr int kGyrKeep = 4;
 
-template <typename T, typename JT>
-__device__ __forceinline__ void gyration_block(const CvSet &cs, const WalkerTabs &t, const PosView &pos, double *xi,
-                                               JT *J, int32_t w, int j, double *lds)
+template <int KEEP, typename T, typename JT>
+__device__ __forceinline__ void gyration_of(const CvSet &cs, const CvDesc &cv, const WalkerTabs &t, const PosView &pos,
+                                            double *xi, JT *J, int32_t w, double *lds)
 {
-    int c = 0, seen = 0;
-    for (; c < cs.ncv; ++c)
-        if (cs.cv[c].kind == CV_GYRATION && seen++ == j) break;
-    const CvDesc cv = cs.cv[c];
     const int64_t base = t.atom_off[w];
     const int n = cv.na;
     const int32_t *const atoms = t.slot_atom + cv.slot0;
-    int32_t a[kGyrKeep];
-    double3 p[kGyrKeep];
+    int32_t a[KEEP];
+    double3 p[KEEP];
 #pragma unroll
-    for (int k = 0; k < kGyrKeep; ++k) a[k] = atoms[min((int)threadIdx.x + k * kBlock, n - 1)];
+    for (int k = 0; k < KEEP; ++k) a[k] = atoms[min((int)threadIdx.x + k * kBlock, n - 1)];
 #pragma unroll
-    for (int k = 0; k < kGyrKeep; ++k) p[k] = ld_pos_t<T>(pos, base + a[k]);
+    for (int k = 0; k < KEEP; ++k) p[k] = ld_pos_t<T>(pos, base + a[k]);
     // f(i, r_i) over the thread's members in order
     auto members = [&](auto f) {
 #pragma unroll
-        for (int k = 0; k < kGyrKeep; ++k) {
+        for (int k = 0; k < KEEP; ++k) {
             const int i = threadIdx.x + k * kBlock;
             if (i < n) f(i, p[k]);
         }
-        for (int i = threadIdx.x + kGyrKeep * kBlock; i < n; i += kBlock) f(i, ld_pos_t<T>(pos, base + atoms[i]));
+        for (int i = threadIdx.x + KEEP * kBlock; i < n; i += kBlock) f(i, ld_pos_t<T>(pos, base + atoms[i]));
     };
     double s[3] = {0.0, 0.0, 0.0};
     members([&](int, double3 r) {
@@ -140,6 +139,20 @@ __device__ __forceinline__ void gyration_block(const CvSet &cs, const WalkerTabs
         const int64_t sb = (int64_t)w * cs.nslots + cv.slot0;
         members([&](int i, double3 r) { st_slot(J, sb + i, d3scale(d3sub(r, cen), inv)); });
     }
+}
+
+template <typename T, typename JT>
+__device__ __forceinline__ void gyration_block(const CvSet &cs, const WalkerTabs &t, const PosView &pos, double *xi,
+                                               JT *J, int32_t w, int j, double *lds)
+{
+    int c = 0, seen = 0;
+    for (; c < cs.ncv; ++c)
+        if (cs.cv[c].kind == CV_GYRATION && seen++ == j) break;
+    const CvDesc cv = cs.cv[c];
+    if (cv.na <= kBlock)
+        gyration_of<1, T>(cs, cv, t, pos, xi, J, w, lds);
+    else
+        gyration_of<kGyrKeep, T>(cs, cv, t, pos, xi, J, w, lds);
 }
 
 // ---------------------------------------------- coordination number, all pairs
