@@ -10,7 +10,7 @@
 //                   the read-back V) and the force gather; k_grid_step_wave
 //                   is the same in one wavefront when forces go through the
 //                   table in kernel-argument form.
-//   k_grid_tiles, k_grid_line, k_grid_fill
+//   k_grid_tiles, k_grid_line, k_grid_fill, k_grid_few
 //                   the hills the step appended, or a whole list (rebuild, in
 //                   slices that k_grid_join adds up), onto every node; after
 //                   a step the list's count and the device step counter
@@ -358,10 +358,10 @@ __device__ __forceinline__ double exp2_neg(double y)
     return ldexp(p, (int)n);
 }
 
-// The factor e of CV d at displacement x - c, and g = -u / sigma^2.  The
-// image is that of rint(u / period): where the product with the reciprocal is
-// too near half a period to tell, the quotient decides.
-__device__ __forceinline__ void axis_factor(const GridArgs &g, int d, double x, double c, double &e, double &gd)
+// The displacement u = x - c of CV d.  Its image is that of rint(u / period):
+// where the product with the reciprocal is too near half a period to tell, the
+// quotient decides.  In the units of exp2_neg: y = -u^2 / (2 sigma^2 ln 2).
+__device__ __forceinline__ double axis_offset(const GridArgs &g, int d, double x, double c, double &y)
 {
     double u = x - c;
     if (g.period[d] > 0.0) {
@@ -369,8 +369,16 @@ __device__ __forceinline__ void axis_factor(const GridArgs &g, int d, double x, 
         if (__builtin_expect(fabs(v) > 0.499999999 * g.period[d], 0)) v = fma(-g.period[d], rint(u / g.period[d]), u);
         u = v;
     }
-    e = exp2_neg(-(u * u) * (0.72134752044448170368 * g.inv_sig2[d]));  // log2(e) / 2
-    gd = -u * g.inv_sig2[d];
+    y = -(u * u) * (0.72134752044448170368 * g.inv_sig2[d]);  // log2(e) / 2
+    return u;
+}
+
+// the factor e of CV d at displacement u, and g = -u / sigma^2
+__device__ __forceinline__ void axis_factor(const GridArgs &g, int d, double x, double c, double &e, double &gd)
+{
+    double y;
+    gd = -axis_offset(g, d, x, c, y) * g.inv_sig2[d];
+    e = exp2_neg(y);
 }
 
 // The hills [k0, k1) of grid l that a workgroup sums: after k_grid_step the
@@ -704,6 +712,85 @@ __global__ void __launch_bounds__(1024) k_grid_fill(GridArgs g, int32_t l, int32
     }
 }
 
+// Few hills (a list's own hill of a step, a short list): nothing to share
+// over hills, so the nodes are shared out alone.  A workgroup takes 2^shift
+// columns and as many rows as make four nodes a thread (one in one CV); a
+// thread's nodes share their column's Gaussian, and the CVs of a row are one
+// exponent.  One hill is a chain of its loads, one exponential and the nodes'
+// update; each further one adds 0.6 us (0.2 in one CV).
+constexpr int kFewRows = 4;  // nodes of a thread, D > 1
+
+template <int D, bool REBUILD>
+__global__ void __launch_bounds__(kBlock) k_grid_few(GridArgs g, int32_t l0, int32_t per, int32_t nr,
+                                                     int32_t shift)
+{
+    constexpr int R = D == 1 ? 1 : kFewRows, DR = D == 1 ? 1 : D - 1;  // (one CV: no rows, DR unused)
+    if (!REBUILD) advance_step(g);
+    const int32_t l = REBUILD ? l0 : (int32_t)blockIdx.x / per, wg = (int32_t)blockIdx.x % per;
+    int32_t k0, k1;
+    hill_range<REBUILD>(g, l, 0, k0, k1);
+    if (!REBUILD && k1 == k0) return;  // uniform
+    const int64_t hb = (int64_t)g.wrec[l].hb4 * 4;
+    const int32_t nc = g.n[D - 1];
+    const int32_t side = 1 << shift, down = kBlock >> shift;  // columns of a tile, threads down it
+    const int32_t tc = (nc + side - 1) >> shift, tiles = tc * ((nr + down * R - 1) / (down * R));
+    double *const Vg = g.V + (int64_t)l * g.N, *const Gg = g.G + (int64_t)l * D * g.N;
+    for (int32_t tile = wg; tile < tiles; tile += per) {
+        const int32_t c = tile % tc * side + ((int32_t)threadIdx.x & (side - 1));
+        const int32_t r0 = tile / tc * (down * R) + ((int32_t)threadIdx.x >> shift);
+        const double xc = g.lo[D - 1] + (double)c * g.delta[D - 1];
+        double xr[R][DR], acc[R][1 + D];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            int32_t r = r0 + q * down;
+#pragma unroll
+            for (int d = D - 2; d >= 0; --d) {
+                xr[q][d] = g.lo[d] + (double)(r % g.n[d]) * g.delta[d];
+                r /= g.n[d];
+            }
+#pragma unroll
+            for (int j = 0; j <= D; ++j) acc[q][j] = 0.0;
+        }
+        for (int32_t k = k0; k < k1; ++k) {
+            double hc[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) hc[d] = (double)g.c[d][hb + k];
+            double ec, gc;
+            axis_factor(g, D - 1, xc, hc[D - 1], ec, gc);
+            ec *= (double)g.h[hb + k];
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                double y = 0.0, gr[DR], yd;
+#pragma unroll
+                for (int d = 0; d < D - 1; ++d) {
+                    gr[d] = -axis_offset(g, d, xr[q][d], hc[d], yd) * g.inv_sig2[d];
+                    y += yd;
+                }
+                const double e = D == 1 ? ec : ec * exp2_neg(y);
+                acc[q][0] += e;
+#pragma unroll
+                for (int d = 0; d < D - 1; ++d) acc[q][1 + d] = fma(e, gr[d], acc[q][1 + d]);
+                acc[q][D] = fma(e, gc, acc[q][D]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int32_t r = r0 + q * down;
+            if (r >= nr || c >= nc) continue;
+            const int64_t node = (int64_t)r * nc + c;
+            Vg[node] = REBUILD ? acc[q][0] : Vg[node] + acc[q][0];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                double *p = Gg + (int64_t)d * g.N + node;
+                *p = REBUILD ? acc[q][1 + d] : *p + acc[q][1 + d];
+            }
+        }
+    }
+    if (REBUILD) return;
+    __syncthreads();  // every wavefront has read the count
+    finish_add(g, l, k1, per);
+}
+
 // a rebuild's slices joined in order
 __global__ void __launch_bounds__(kBlock) k_grid_join(GridArgs g, int32_t l)
 {
@@ -754,6 +841,29 @@ hipError_t launch_tiles(const GridArgs &g, int32_t l0, int64_t per, int64_t nz, 
     return hipGetLastError();
 }
 
+// k_grid_few (the plan holds N to 2^30) on grids l0 .. l0 + nl - 1, at most `most` workgroups
+// each: tiles of 64 columns, fewer where there are fewer, more where the rows
+// would not fill them
+template <bool REBUILD>
+hipError_t launch_few(const GridArgs &g, int32_t l0, int64_t most, int64_t nl, hipStream_t s)
+{
+    const int32_t nc = g.n[g.D - 1], nr = (int32_t)(g.N / nc), rows = g.D == 1 ? 1 : kFewRows;
+    int32_t shift = 0;
+    while ((1 << shift) < nc && (shift < 6 || (shift < 8 && (kBlock >> (shift + 1)) * rows >= nr))) ++shift;
+    if (g.D == 1) shift = 8;
+    const int32_t side = 1 << shift, down = (kBlock >> shift) * rows;
+    const int64_t per = std::min(most, (int64_t)((nc + side - 1) / side) * ((nr + down - 1) / down));
+    if (per * nl > INT32_MAX) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(per * nl));
+    switch (g.D) {
+    case 1: hipLaunchKernelGGL((k_grid_few<1, REBUILD>), grid, dim3(kBlock), 0, s, g, l0, (int32_t)per, nr, shift); break;
+    case 2: hipLaunchKernelGGL((k_grid_few<2, REBUILD>), grid, dim3(kBlock), 0, s, g, l0, (int32_t)per, nr, shift); break;
+    case 3: hipLaunchKernelGGL((k_grid_few<3, REBUILD>), grid, dim3(kBlock), 0, s, g, l0, (int32_t)per, nr, shift); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 __global__ void __launch_bounds__(kBlock) k_grid_eval(GridArgs g, int32_t l, const double *xi, int64_t n, double *V,
                                                         double *dV)
 {
@@ -781,6 +891,32 @@ hipError_t launch_scale_f64(double *x, int64_t n, double a, hipStream_t s)
     return hipGetLastError();
 }
 
+// Does k_grid_few take a step's hills?  One a list (private lists) always, one
+// or two walkers of a shared list about even; in one CV up to 64 where the
+// grid is more than one round of k_grid_line's workgroups.  A step that
+// deposits, us with the tiles and with k_grid_few:
+//   32 lists of 4,096 nodes in one CV          22.4  12.4
+//   32 lists of 1,000 x 2 nodes                23.0  12.1
+//   32 lists of 100 x 100 x 3                 136.2  30.9
+//   a list of 512 x 512, 1 hill / 2 / 4        15.0  14.6 / 15.6  15.9 / 15.7  16.8
+//   a list of 100,000 in one CV, 4 / 64        21.8  14.0 / 26.1  24.4
+// A rebuild of up to 8 hills, 32 where padding is most of the tiles:
+//   512 x 512, 4 hills / 16                    72.5  71.8 / 72.2  78.3
+//   100 x 100 x 3, 16 / 64                    124.4  92.4 / 179   124
+//   100,000 in one CV, 16 / 256                75.6  59.3 / 104   110
+bool few_hills(const GridArgs &g, int64_t tiles)
+{
+    const int32_t hills = g.shared ? g.tabs.W : 1;
+    return hills <= 2 || (g.D == 1 && tiles > 512 && hills <= 64);
+}
+
+bool few_rebuild(const GridArgs &g, int64_t hills)
+{
+    const int64_t tiles = tiles_of(g.D, g.n, g.N, kTileSide);
+    if (g.D == 1) return hills <= (tiles > 512 ? 64 : 8);
+    return hills <= (tiles * kTileSide * kTileSide >= 4 * g.N ? 32 : 8);
+}
+
 // A configuration that never deposits (deposit off, or on a stride of 0)
 // has nothing for the add kernel but the step counter: the step kernel then
 // advances it and the add kernel is not launched.
@@ -798,10 +934,13 @@ hipError_t launch_grid_step(const GridArgs &g0, hipStream_t s)
         hipLaunchKernelGGL(k_grid_step, dim3(g.tabs.W), dim3(kBlock), 0, s, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !add) return e;
-    // about 1024 workgroups in all: on a step that deposits nothing each of
-    // them only reads its list's count of new hills
-    const int64_t most = (1024 + g.L - 1) / g.L;
-    return launch_tiles<false>(g, 0, std::min(tiles_of(g.D, g.n, g.N, kTileSide), most), g.L, s);
+    // about 1024 workgroups in all (512 of k_grid_line's 16 wavefronts): on a
+    // step that deposits nothing each of them only reads its list's count of
+    // new hills
+    const int64_t tiles = tiles_of(g.D, g.n, g.N, kTileSide), room = g.D == 1 ? 512 : 1024;
+    const int64_t most = (room + g.L - 1) / g.L;
+    if (few_hills(g, tiles)) return launch_few<false>(g, 0, (1024 + g.L - 1) / g.L, g.L, s);
+    return launch_tiles<false>(g, 0, std::min(tiles, most), g.L, s);
 }
 
 // A workgroup fills a compute unit, so the tiles of most grids leave the chip
@@ -821,9 +960,15 @@ int32_t grid_slices(int32_t D, const int32_t *n, int64_t N)
     return best;
 }
 
-hipError_t launch_grid_rebuild(const GridArgs &g, int32_t l, hipStream_t s)
+hipError_t launch_grid_rebuild(const GridArgs &g0, int32_t l, int64_t hills, hipStream_t s)
 {
+    GridArgs g = g0;
     if (l < 0 || l >= g.L || g.slices < 1 || (g.slices > 1 && !g.part)) return hipErrorInvalidValue;
+    if (few_rebuild(g, hills)) {
+        g.slices = 1;
+        return launch_few<true>(g, l, 4096, 1, s);
+    }
+    g.slices = (int32_t)std::min<int64_t>(g.slices, (hills + kTileHills - 1) / kTileHills);  // none of them empty
     hipError_t e;
     if (fill_tiles(g.D, g.n, g.N)) {
         const int64_t tiles = tiles_of(g.D, g.n, g.N, kFillSide);

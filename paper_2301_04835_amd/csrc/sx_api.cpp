@@ -2236,7 +2236,7 @@ sx_status sx_hills_set(sx_ctx *ctx, int32_t walker, const float *centers, const 
     int32_t k32 = (int32_t)K;
     if (e == hipSuccess) e = hipMemcpy(at<int32_t>(ctx->state, p.s_count) + wl, &k32, 4, hipMemcpyHostToDevice);
     if (e == hipSuccess && ctx->mg_on) {  // the list's grid from the new list
-        e = launch_grid_rebuild(grid_args(ctx, nullptr), wl, ctx->stream);
+        e = launch_grid_rebuild(grid_args(ctx, nullptr), wl, K, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     }
     if (e != hipSuccess) return hip_fail(ctx, e, "hill upload");

@@ -403,14 +403,15 @@ hipError_t launch_hill_private(const HillArgs &a, const CvSet &cs, const PosView
                                int which = 3);
 hipError_t launch_abf(const AbfArgs &a, hipStream_t s);
 // grid bias: a step (read-back, outputs, deposit, forces, then the step's
-// hills onto the grids); rebuilding grid l from its whole list, in as many
-// parts as grid_slices says for its nodes; read-back at n points of grid l
+// hills onto the grids); rebuilding grid l from its whole list of `hills`, in
+// at most as many parts as grid_slices says for its nodes; read-back at n
+// points of grid l
 hipError_t launch_harmonic(const HarmonicArgs &a, hipStream_t s);
 hipError_t launch_grid_step(const GridArgs &g, hipStream_t s);
 // x[i] *= a for i < n (device FP64)
 hipError_t launch_scale_f64(double *x, int64_t n, double a, hipStream_t s);
 int32_t grid_slices(int32_t D, const int32_t *n, int64_t N);
-hipError_t launch_grid_rebuild(const GridArgs &g, int32_t l, hipStream_t s);
+hipError_t launch_grid_rebuild(const GridArgs &g, int32_t l, int64_t hills, hipStream_t s);
 hipError_t launch_grid_eval(const GridArgs &g, int32_t l, const double *xi, int64_t n, double *V, double *dV,
                             hipStream_t s);
 // hill chunks of a shared-list sum over nq queries: `target` workgroups (0:

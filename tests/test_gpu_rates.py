@@ -80,3 +80,26 @@ def test_windows_take_no_second_round(gpu, D):
         t.append(best_us(s.graph_launch, 5) / 20)
     print(D, [round(x, 2) for x in t])
     assert t[1] <= 1.12 * t[0]
+
+
+@pytest.mark.parametrize("nb", [[4096], [1000, 2], [2, 1000]])
+def test_private_grids_take_their_hill_side_by_side(gpu, nb):
+    """A step in which each of 32 walkers puts one hill onto its own grid, next
+    to one walker's (1.8 times and more with tiles of matrix products)."""
+    t = []
+    for W in (1, 32):
+        D = len(nb)
+        s = Sampler(0)
+        for d in range(D):
+            s.add_dihedral([d, d + 1, d + 2, d + 3])
+        s.set_walkers(np.arange(W + 1) * 22, hill_capacity=[20000] * W)
+        s.metad([0.35] * D, 1.2, 300.0, 6.0, 1)
+        s.metad_grid([-np.pi] * D, [np.pi] * D, nb)
+        s.bind()
+        P = dev(np.concatenate([synth.chain_template(22, 40 + w) for w in range(W)]).astype(np.float32))
+        F = torch.zeros_like(P)
+        s.graph_capture(20, P, forces=F)
+        t.append(best_us(s.graph_launch, 5) / 20)
+        s.check()
+    print(nb, [round(x, 2) for x in t])
+    assert t[1] <= 1.6 * t[0]
