@@ -72,11 +72,24 @@ __device__ __forceinline__ int cell_of(double x, double L, double iL, double cle
 // placement kernel over all compute units, slots in memory: 42 and 55.)
 // SMALL: the slots' members fit in LDS next to the cells' words (80 KB, two
 // workgroups a CU); otherwise they wait where the sorted records go (127 us).
+// Counting costs a cell the square of its members, so where the squares of a
+// group's cells add up to more than crowded() per member (a dense droplet in a
+// large box, whose cells are capped at 16 a side) its members take the turns.
+// Counting and turns, us, of a group in 16,384 cells (slots in memory):
+//   20,000 members, squares of 10 / 18 / 55 / 388   111 135 214 967   129
+//   of 32 walkers                                   147 171 259 1,023 137
+//   60,000, squares of 10 / 19 / 58 / 403           311 379 642 2,755 346
+// in 432 (slots in LDS): 20,000, squares of 186, 178 and 118; 5,000, of 47, 34
+// and 35; in 16,384: 5,000, of 32 / 48 / 145, 41 49 82 and 46; 2,000, of 22 /
+// 50, 28 33 and 29.
+__device__ __forceinline__ float crowded(bool in_lds, int32_t n) { return !in_lds ? 12.f : n > 8192 ? 90.f : 40.f; }
+
 template <typename T, bool SMALL>
 __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosView pos)
 {
     __shared__ int32_t s_off[kBuildWords];  // a cell's count, first slot, end; then (SMALL) the slots' members
     __shared__ int32_t s_tot[kBuildBlock / 64];
+    __shared__ float s_sq[kBuildBlock / 64];
     const int w = blockIdx.x / c.G, g = blockIdx.x % c.G;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t n = c.goff[g + 1] - c.goff[g];
@@ -123,16 +136,29 @@ __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosVi
     const int per = (c.ncell + kBuildBlock - 1) / kBuildBlock;
     const int c0 = min(tid * per, c.ncell), c1 = min(c0 + per, c.ncell);
     int32_t sum = 0;
-    for (int cc = c0; cc < c1; ++cc) sum += s_off[cc];
+    float sq = 0.f;  // the sum of the counts' squares, the same in every thread below
+    for (int cc = c0; cc < c1; ++cc) {
+        const int32_t m = s_off[cc];
+        sum += m;
+        sq += (float)m * (float)m;
+    }
     int32_t run = sum;
     for (int o = 1; o < 64; o <<= 1) {
         const int32_t y = __shfl_up(run, o, 64);
         if (lane >= o) run += y;
+        sq += __shfl_xor(sq, o, 64);
     }
-    if (lane == 63) s_tot[wave] = run;
+    if (lane == 63) {
+        s_tot[wave] = run;
+        s_sq[wave] = sq;
+    }
     __syncthreads();
     run -= sum;
-    for (int k = 0; k < wave; ++k) run += s_tot[k];
+    sq = 0.f;
+    for (int k = 0; k < kBuildBlock / 64; ++k) {
+        run += k < wave ? s_tot[k] : 0;
+        sq += s_sq[k];
+    }
     for (int cc = c0; cc < c1; ++cc) {
         const int32_t m = s_off[cc];
         s_off[cc] = run;
@@ -141,6 +167,31 @@ __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosVi
     }
     if (tid == 0) cst[c.ncell] = n;
     __syncthreads();
+    if (sq > crowded(SMALL, n) * (float)n) {  // uniform
+        for (int32_t base = 0; base < n; base += kBuildBlock) {
+            const int32_t i = base + tid;
+            const bool valid = i < n;
+            const int cell = valid ? cid[i] : -1;
+            const float4 v = tmp[valid ? i : base];  // in flight during the ranking
+            int rank = 0, cnt = 0;
+            for (int k = 0; k < 64; ++k) {
+                const int ck = __shfl(cell, k, 64);
+                cnt += ck == cell ? 1 : 0;
+                rank += (ck == cell && k < lane) ? 1 : 0;
+            }
+            for (int t = 0; t < kBuildBlock / 64; ++t) {
+                __syncthreads();
+                if (wave == t && valid) {
+                    const int dst = s_off[cell] + rank;
+                    srt[dst] = v;
+                    cid[i] = dst;  // from here on: the member's sorted position
+                    if (rank == cnt - 1) s_off[cell] += cnt;  // after every lane of the wavefront read it
+                }
+            }
+            __syncthreads();
+        }
+        return;
+    }
     for (int32_t b = tid; b < n; b += 4 * kBuildBlock) {
         int32_t cell[4];
 #pragma unroll

@@ -103,3 +103,32 @@ def test_private_grids_take_their_hill_side_by_side(gpu, nb):
         s.check()
     print(nb, [round(x, 2) for x in t])
     assert t[1] <= 1.6 * t[0]
+
+
+@pytest.mark.parametrize("n,box", [(20000, 40.0), (20000, 80.0), (41000, 60.0)])
+def test_crowded_cells_sort_in_linear_time(gpu, n, box):
+    """A droplet at water's density in a large box, whose cells hold hundreds of
+    members, next to the same atoms all over a box of the usual density (3.9 and
+    17 times with every member counting its cell's)."""
+    t = []
+    g = np.random.default_rng(n)
+    for L in ((2 * n / 23.0) ** (1 / 3), box):
+        x = g.random((2 * n, 3)) * L
+        if L == box:
+            v = g.normal(size=(2 * n, 3))
+            r = (2 * n / 33.0 * 0.75 / np.pi) ** (1 / 3) * g.random((2 * n, 1)) ** (1 / 3)
+            x = L / 2 + r * v / np.linalg.norm(v, axis=1, keepdims=True)
+        s = Sampler(0)
+        s.add_coordination(list(range(n)), list(range(n, 2 * n)), 0.5, rcut=1.2)
+        s.set_box([L] * 3)
+        s.set_walkers(np.array([0, 2 * n], dtype=np.int64))
+        s.set_cell_lists(1)
+        s.metad([0.2], 1.0, 300.0, None, 500, 1000)
+        s.bind()
+        P = dev(x.astype(np.float32))
+        F = torch.zeros_like(P)
+        s.step(P, forces=F)
+        s.check()
+        t.append(min(s.time_cell(P, F, reps=5)[0] for _ in range(3)) * 1e3)
+    print(n, box, [round(x, 1) for x in t])
+    assert t[1] <= 2.8 * t[0]
