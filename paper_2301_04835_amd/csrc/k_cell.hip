@@ -42,6 +42,8 @@
 namespace sx {
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int kBuildBlock = 1024;
 constexpr int kBuildWords = 20448;  // LDS words of the build: the cells', then a 16-bit slot per member
 static_assert(kBuildWords >= kCellTotal, "every cell has a word");
@@ -67,9 +69,11 @@ __device__ __forceinline__ int cell_of(double x, double L, double iL, double cle
 // whatever the slots were.  Taking turns in member order instead (a wavefront
 // ranks its 64 members by shuffles and 16 wavefronts go one after the other)
 // was a chain of 16 barriers per 1,024 members: 96 groups of 20,000 took
-// 135 us, this way 72: 28 up to the slots, 17 the scattered stores of the
+// 135 us, this way 62: 28 up to the slots, 17 the scattered stores of the
 // records, the rest one compute unit's share of the loads and stores.  (A
-// placement kernel over all compute units, slots in memory: 42 and 55.)
+// placement kernel over all compute units, slots in memory: 42 and 55.  The
+// records requested ahead of the counts are vectors of the language: as
+// float4 they waited in scratch memory, 71.)
 // SMALL: the slots' members fit in LDS next to the cells' words (80 KB, two
 // workgroups a CU); otherwise they wait where the sorted records go (127 us).
 // Counting costs a cell the square of its members, so where the squares of a
@@ -216,13 +220,13 @@ __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosVi
     const uint32_t *s_two = reinterpret_cast<const uint32_t *>(s_slot);
     for (int32_t b = tid; b < n; b += 4 * kBuildBlock) {
         int32_t m[4], lo[4], hi[4], dst[4], len = 0;
-        float4 v[4];
+        f32x4 v[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int32_t e = b + k * kBuildBlock < n ? b + k * kBuildBlock : b;
             m[k] = SMALL ? e : slot[e];
             lo[k] = cid[m[k]];
-            if (SMALL) v[k] = tmp[m[k]];
+            if (SMALL) v[k] = *reinterpret_cast<const f32x4 *>(tmp + m[k]);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -248,9 +252,10 @@ __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosVi
             }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            if (b + k * kBuildBlock >= n) break;
-            if (SMALL) srt[dst[k]] = v[k];
-            cid[m[k]] = dst[k];  // from here on: the member's sorted position
+            if (b + k * kBuildBlock < n) {
+                if (SMALL) *reinterpret_cast<f32x4 *>(srt + dst[k]) = v[k];
+                cid[m[k]] = dst[k];  // from here on: the member's sorted position
+            }
         }
     }
     if (!SMALL) {
@@ -551,8 +556,6 @@ __device__ __forceinline__ void pair2(const Staged &sp, const int (&e)[2], float
         g.z = fmaf(f, dz[q], g.z);
     }
 }
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Partners [b0, b1) of the staged window (uniform per wavefront) against its
 // 16 home atoms; live: this lane's atom counts.  bo: the lane's word of the
