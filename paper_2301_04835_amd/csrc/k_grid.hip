@@ -33,7 +33,9 @@ __device__ __forceinline__ bool grid_cell(const GridArgs &g, const double *xi, i
 {
     bool inside = true;
 #pragma unroll
-    for (int d = 0; d < kMaxBiasDim; ++d) {  // compile-time indices (registers)
+    for (int d = 0; d < kMaxBiasDim; ++d) {  // compile-time indices, all of them set (registers)
+        i0[d] = i1[d] = 0;
+        t[d] = 0.0;
         if (d >= g.D) continue;
         const double u = (xi[d] - g.lo[d]) / g.delta[d];
         double fl = floor(u);
@@ -46,7 +48,6 @@ __device__ __forceinline__ bool grid_cell(const GridArgs &g, const double *xi, i
         } else {
             if (!(u >= 0.0 && u <= (double)g.nbins[d])) {
                 inside = false;
-                i0[d] = i1[d] = 0;
                 continue;
             }
             int32_t k = (int32_t)fl;

@@ -29,8 +29,10 @@ def report(source):
     return REPORTS[source]
 
 
-@pytest.mark.parametrize("source,kernel,instances", [("k_cell.hip", "k_cell_build", 4)])
+@pytest.mark.parametrize("source,kernel,instances", [("k_cell.hip", "k_cell_build", 4), ("k_grid.hip", "k_grid_step", 1),
+                                                     ("k_grid.hip", "k_grid_step_wave", 1),
+                                                     ("k_grid.hip", "k_grid_eval", 1)])
 def test_no_scratch(source, kernel, instances):
-    found = {k: v for k, v in report(source).items() if kernel + "I" in k or kernel + "E" in k}
+    found = {k: v for k, v in report(source).items() if re.search(r"\d%s[IE]" % kernel, k)}
     assert len(found) == instances
     assert not any(found.values()), found
