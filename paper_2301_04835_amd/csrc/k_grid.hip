@@ -307,12 +307,14 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
 // with v_mfma_f64_16x16x4_f64, each wavefront a 16 x 16 block of the 1 + D
 // sums; the groups' sums are joined in group order and added to the nodes, so
 // a grid's bits do not depend on the schedule.  FP64 multiply-adds bound it
-// (1 + D per (node, hill), 39 T/s), with the factors' exponentials (about 40
-// operations each, 1/16 per (node, hill)) on the vector units beside them.
+// (1 + D per (node, hill), 39 T/s), and the factors' exponentials (about 40
+// operations each, 1/16 per (node, hill)), which do not run beside them.
 // A whole list takes KG = 4 (16 wavefronts a CU) and as many slices as fill the
 // chip, a step's few hills KG = 1: less to launch on the many steps that
 // deposit nothing.  256 hills: 25 us (one workgroup for the whole grid:
-// 76.8 ms).
+// 76.8 ms).  KG = 4 spills 42 registers in two CVs and 70 in three; KG = 2 none,
+// but is no faster (30,000 hills onto 24 x 24 x 24 nodes 279 us, 250 with four;
+// 100 x 100 x 3 2,753 and 2,464; 30 x 30 x 20 339 and 376).
 //
 // k_grid_fill: a whole list in tiles of 64 x 64, half the factors per node.
 // 100,000 hills onto 512 x 512 nodes, upload included: 3.48 ms; in 32 x 32
@@ -330,7 +332,11 @@ constexpr int kTileHills = 16;  // hills per stage of a group
 constexpr int kTileLd = 48;
 constexpr int kLineSlices = 16;
 constexpr int kFillSide = 64;   // nodes per side of a rebuild's larger tile
-constexpr int kFillCost = 29;   // its time in tenths of a 32 x 32 tile's (512 x 512 nodes: 3.35 ms in 64 tiles, 4.63 in 256)
+// The larger tile's time in tenths of a 32 x 32 tile's.  60,000 hills, ms: 512 x
+// 512 nodes 2.06 in 64 tiles, 2.67 in 256 (31); 48 x 48 x 48 1.63 in 36, 2.16 in
+// 144 (30); 200 x 200 in 16 and 49 even (0.64 and 0.62; 30,000 hills 0.325 and
+// 0.342).
+constexpr int kFillCost = 30;
 constexpr int kMostSlices = 128;
 
 // 2^y for y <= 0 in FP64: y = n + f, |f| <= 1/2, and the Taylor series of
@@ -508,26 +514,13 @@ __global__ void __launch_bounds__(256 * KG) k_grid_tiles(GridArgs g, int32_t l0,
                 acc[D] = __builtin_amdgcn_mfma_f64_16x16x4f64(l0v, s_f[grp][D + 1][kk][b], acc[D], 0, 0, 0);
             }
         };
-        // Even groups form factors while odd groups multiply, then the other
-        // way round: every SIMD holds a wavefront of each group, so its
-        // matrix and vector units work at the same time.
         const int32_t stages = (k1 - k0 + KG * kTileHills - 1) / (KG * kTileHills);
         const int32_t kg0 = k0 + grp * kTileHills;
-        const bool odd = grp & 1;
         if (stages > 0) request(kg0 + fh);
-        for (int32_t i = 0; i < stages + (KG > 1 ? 1 : 0); ++i) {
-            if (odd) {
-                if (i > 0) products();
-            } else if (i < stages) {
-                factors(kg0 + i * KG * kTileHills);
-            }
+        for (int32_t i = 0; i < stages; ++i) {
+            factors(kg0 + i * KG * kTileHills);
             __syncthreads();
-            if (i < stages) {
-                if (odd)
-                    factors(kg0 + i * KG * kTileHills);
-                else
-                    products();
-            }
+            products();
             __syncthreads();
         }
         if (KG > 1) {  // join the groups' sums, group after group
@@ -821,10 +814,13 @@ int64_t tiles_of(int32_t D, const int32_t *n, int64_t N, int side)
 }
 
 // 64 x 64 tiles where they cost less with their padding (three CVs' 12 to 32
-// columns: 32 x 32).
+// columns: 32 x 32) and are more than one, which kMostSlices parts do not
+// spread over the chip (64 x 64 nodes 167 us, in 32 x 32 tiles 156).
 bool fill_tiles(int32_t D, const int32_t *n, int64_t N)
 {
-    return D > 1 && kFillCost * tiles_of(D, n, N, kFillSide) < 10 * tiles_of(D, n, N, kTileSide);
+    if (D == 1) return false;
+    const int64_t large = tiles_of(D, n, N, kFillSide);
+    return large > 1 && kFillCost * large < 10 * tiles_of(D, n, N, kTileSide);
 }
 
 template <bool REBUILD>
