@@ -402,7 +402,7 @@ __global__ void __launch_bounds__(kBlock) k_hill_finalize(HillArgs a, CvSet cs, 
     finalize_tail<D>(a, w, wr, cnt0, next_step, acc, s_xi, s_coef, small_lane, sg, nent, ent, jr);
 }
 
-// The same finalize in one wavefront, for walkers of at most 128 tiles and
+// The same finalize in one wavefront, for walkers of at most 256 tiles and
 // steps that gather forces through a table small enough for the kernel
 // arguments (at most 32 touched atoms, 8 slots each): the tile records are summed by a fixed butterfly across the
 // wavefront (every lane ends with the same bits, as each lane adds in the
@@ -587,10 +587,12 @@ hipError_t launch_hill_d(const HillArgs &a, const CvSet &cs, const PosView &pos,
         if (e != hipSuccess) return e;
     }
     if (which & 2) {
-        // one wavefront per walker while its tile records are two loads a
-        // lane; beyond, a workgroup with four in flight a lane (2,048 records
-        // of one 8.4M-hill walker: 5.2 us; in one wavefront 12.0)
-        if (a.small.on && a.do_forces && a.small.U > 0 && a.max_tiles <= 128)
+        // one wavefront per walker while its tile records are at most four
+        // loads a lane; beyond, a workgroup with four in flight a lane.  A
+        // replayed step in two CVs, us with a wavefront and a workgroup, one
+        // walker: 192 tiles 6.22 and 6.69, 256 6.55 and 6.75, 384 7.38 and
+        // 7.37, 512 7.95 and 7.49; 64 walkers of 192 33.8 and 34.0.
+        if (a.small.on && a.do_forces && a.small.U > 0 && a.max_tiles <= 256)
             hipLaunchKernelGGL((k_hill_finalize_wave<D, FUSE>), dim3(a.tabs.W), dim3(64), 0, s, a, cs, pos);
         else
             hipLaunchKernelGGL((k_hill_finalize<D, FUSE>), dim3(a.tabs.W), dim3(kBlock), 0, s, a, cs, pos);
