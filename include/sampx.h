@@ -116,7 +116,7 @@ sx_status sx_set_box(sx_ctx *ctx, const double L[3]);
 /* Coordination numbers with a hard cut (rcut > 0) in a periodic box at
  * least 3 rcut wide can be evaluated through cell lists (in x and y cells of
  * edge >= the largest such cut, 3 to 16 per dimension; in z such cells cut
- * into 4, 2 or 1 sub-cells, at most 4096 cells in all): each step sorts the
+ * into 4 sub-cells): each step sorts the
  * groups' members into cells (stable, so every sum has a fixed order), sums
  * pairs over the neighbour cells in one pass that also keeps each member's
  * gradient per (CV, side), and computes forces as a vector-Jacobian product

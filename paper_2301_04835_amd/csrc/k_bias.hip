@@ -513,7 +513,6 @@ __global__ void __launch_bounds__(kBlock) k_hill_step_one_tile(HillArgs a, CvSet
     const WalkerRec wr = ld_uniform(a.wrec);
     const int u = (int)threadIdx.x - (kBlock - 64);
     const bool small_lane = a.do_forces && a.small.on && u >= 0 && u < a.small.U;
-    const bool lds_rows = FUSE && a.nslots <= kLdsRows;
     SmallGather sg{0.f, 0.f, 0.f, nullptr};
     int nent = 0;
     int32_t ent[kSmallPer];
@@ -524,13 +523,8 @@ __global__ void __launch_bounds__(kBlock) k_hill_step_one_tile(HillArgs a, CvSet
     }
     const int32_t cnt0 = ld_uniform(a.count);  // what the tile sees: only the deposit below changes it
     double acc[1 + D];
-    hill_tile<D, U, FUSE, T>(a, cs, pos, 0, lds, s_xi, acc, lds_rows ? s_J : nullptr);
-    if (FUSE && small_lane) {
-        if (lds_rows)
-            small_jacobian(&s_J[0][0], ent, jr);
-        else
-            small_jacobian(a.J, ent, jr);
-    }
+    hill_tile<D, U, FUSE, T>(a, cs, pos, 0, lds, s_xi, acc, FUSE ? s_J : nullptr);
+    if (FUSE && small_lane) small_jacobian(&s_J[0][0], ent, jr);
     if (!FUSE) {
         if ((int)threadIdx.x < D) s_xi[threadIdx.x] = a.xi[threadIdx.x];
         __syncthreads();
@@ -541,6 +535,7 @@ __global__ void __launch_bounds__(kBlock) k_hill_step_one_tile(HillArgs a, CvSet
 template <int D, bool FUSE, typename T>
 hipError_t launch_step_one_tile(const HillArgs &a, const CvSet &cs, const PosView &pos, hipStream_t s)
 {
+    if (FUSE && a.nslots > kLdsRows) return hipErrorInvalidValue;  // at most three dihedrals
     switch (a.tile_units) {
     case 1: hipLaunchKernelGGL((k_hill_step_one_tile<D, 1, FUSE, T>), dim3(1), dim3(kBlock), 0, s, a, cs, pos); break;
     case 2: hipLaunchKernelGGL((k_hill_step_one_tile<D, 2, FUSE, T>), dim3(1), dim3(kBlock), 0, s, a, cs, pos); break;

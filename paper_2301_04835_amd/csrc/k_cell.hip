@@ -26,13 +26,11 @@
 //                  one lane per member in member order (groups identical
 //                  or disjoint: one writer per atom).
 
-// Cut-length cells (edge >= the cutoff, >= 3 per dimension) are cut into rxy
-// sub-cells in x and y and rz in z, so the (2 rxy + 1)^2 (2 rz + 1)
-// neighbour sub-cells of a sub-cell are distinct and hold exactly the one
-// image of every partner within the cutoff.  The sub-cells shrink the
-// partners a home atom visits from 27 cut-length cubes to
-// ((2 rxy + 1) / rxy)^2 (2 rz + 1) / rz: 14.1 at rxy = 2, rz = 4 (5.8 cut
-// spheres' worth of volume down to 3.4).
+// Cut-length cells (edge >= the cutoff, >= 3 per dimension) are cut into rz = 4
+// sub-cells in z, so the 9 (2 rz + 1) neighbour sub-cells of a sub-cell are
+// distinct and hold exactly the one image of every partner within the cutoff.
+// The sub-cells shrink the partners a home atom visits from 27 cut-length cubes
+// to 9 (2 rz + 1) / rz = 20.3 (6.4 cut spheres' worth of volume to 4.8).
 #include <algorithm>
 
 #include "sx_internal.h"
@@ -293,17 +291,16 @@ __device__ __forceinline__ const CvDesc &cell_cv(const CvSet &cs, int k)
 }
 
 // Stage the members of group gp in the region of column block (cx, cy, z0):
-// the n x n x (czb + 2 rz) sub-cells around it (n = 2 rxy + 1), slice by
-// slice (z offset -rz .. czb + rz - 1), each slice in (x, y) order, so that
-// the neighbour sub-cells of the block's k-th home sub-cell (z offsets
-// -rz .. rz around it) are the contiguous range s_seg[n^2 k] ..
-// s_seg[n^2 (k + 2 rz + 1)].  Positions
+// the 3 x 3 x (czb + 2 rz) sub-cells around it, slice by slice (z offset -rz
+// .. czb + rz - 1), each slice in (x, y) order, so that the neighbour
+// sub-cells of the block's k-th home sub-cell (z offsets -rz .. rz around it)
+// are the contiguous range s_seg[9 k] .. s_seg[9 (k + 2 rz + 1)].  Positions
 // relative to the origin of cell (cx, cy, z0), times sc, and their squared
 // length; entries [r0, r0 + kColStage) of the region, behind kFar entries and
 // followed by kTiles tiles outside any cut.  Returns how many are real.  Its
-// loads are waited for, not its instructions: with a sub-cell's two starts
-// and eight of its members in flight per thread instead of one load at a time
-// the pair pass without its pairs took 483 us, 514 before.
+// loads are waited for, not its instructions: with a sub-cell's two starts and
+// eight of its members in flight per thread instead of one load at a time the
+// pair pass without its pairs took 483 us, 514 before.
 constexpr int kJacBlock = 256;
 constexpr int kTile = 16;                       // home atoms of a wavefront, partners of a tile
 constexpr int kApp = kTile * kJacBlock / 64;    // home atoms per pass
@@ -313,7 +310,8 @@ constexpr int kFar = 4;                         // partners beyond every cut ahe
 constexpr int kStageLd = kFar + kColStage + kTiles * kTile + 12;  // with a step of padding
 static_assert(kStageLd % 64 == 16, "the four coordinates' reads of a tile hit different banks");
 constexpr int kLoads = 8;                       // members of a sub-cell in flight per thread
-constexpr int kRegMax = (2 * kXYReach + 1) * (2 * kXYReach + 1) * (kCzMax + 2 * kZReach);
+constexpr int kSide = 3, kXY = kSide * kSide;  // neighbour cells in x (y), in a layer
+constexpr int kRegMax = kXY * (kCzMax + 2 * kZReach);
 constexpr int kRegPer = (kRegMax + kJacBlock - 1) / kJacBlock;  // region sub-cells per thread
 
 // i + o wrapped into [0, n) for -n <= i + o < 2n (no division)
@@ -327,15 +325,13 @@ struct Staged {
     float c[4][kStageLd];  // x, y, z, x^2 + y^2 + z^2
 };
 
-template <int RXY>
 __device__ __forceinline__ int stage_column(const CellArgs &c, int w, int gp, int cx, int cy, int z0, int czb, int r0,
                                             float sc, float lim, Staged &sp, int32_t *s_seg,
                                             int32_t *s_first, int32_t *s_wsum, int32_t *s_odd)
 {
     const int32_t *cst = c.cstart + ((int64_t)w * c.G + gp) * (c.ncell + 1);
     const float4 *srt = c.sorted + (int64_t)w * c.gtotal + c.goff[gp];
-    constexpr int side = 2 * RXY + 1, nxy = side * side;  // RXY = c.rxy: divisions by constants
-    const int nreg = nxy * (czb + 2 * c.rz);
+    const int nreg = kXY * (czb + 2 * c.rz);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) *s_odd = 0;
     // thread tid's sub-cells are tid, tid + 256, ..: first sorted member and
@@ -348,9 +344,9 @@ __device__ __forceinline__ int stage_column(const CellArgs &c, int w, int gp, in
         const int t = q * kJacBlock + tid;
         n[q] = 0;
         if (t < nreg) {
-            const int sl = t / nxy, xy = t % nxy;
-            const int ox = xy / side - RXY, oy = xy % side - RXY, oz = sl - c.rz;
-            // |ox|, |oy| <= rxy < nc and -rz <= z0 + oz < nc2 + rz with rz <= nc2
+            const int sl = t / kXY, xy = t % kXY;
+            const int ox = xy / kSide - 1, oy = xy % kSide - 1, oz = sl - c.rz;
+            // |ox|, |oy| <= 1 < nc and -rz <= z0 + oz < nc2 + rz with rz <= nc2
             const int nx = wrap_cell(cx + ox, c.nc[0]), ny = wrap_cell(cy + oy, c.nc[1]);
             const int nz = wrap_cell(z0 + oz, c.nc[2]);
             const int nb = (nx * c.nc[1] + ny) * c.nc[2] + nz;
@@ -394,8 +390,8 @@ __device__ __forceinline__ int stage_column(const CellArgs &c, int w, int gp, in
         const int e0 = max(sg, r0), e1 = min(s_seg[t + 1], r0 + m);
         if (e0 >= e1) continue;
         const int f = s_first[t];
-        const int sl = t / nxy, xy = t % nxy;
-        const int ox = xy / side - RXY, oy = xy % side - RXY, oz = sl - c.rz;
+        const int sl = t / kXY, xy = t % kXY;
+        const int ox = xy / kSide - 1, oy = xy % kSide - 1, oz = sl - c.rz;
         const float shx = (float)(ox * c.clen[0]), shy = (float)(oy * c.clen[1]), shz = (float)(oz * c.clen[2]);
         for (int eb = e0; eb < e1; eb += kLoads) {  // past the last member: its copy, dropped
             float4 v[kLoads];
@@ -621,7 +617,7 @@ __device__ __forceinline__ void home_pairs(const Staged &sp, int b0, int b1, flo
     }
 }
 
-template <bool S612, int RXY>
+template <bool S612>
 __global__ void __launch_bounds__(kJacBlock, 5) k_cell_jac(CellArgs c, CvSet cs, PosView pos)
 {
     __shared__ Staged s_p;
@@ -641,8 +637,7 @@ __global__ void __launch_bounds__(kJacBlock, 5) k_cell_jac(CellArgs c, CvSet cs,
     __syncthreads();
     const int a0 = s_home[0], a1 = s_home[czb];
     const int64_t aoff = c.atom_off[w];
-    constexpr int nxy = (2 * RXY + 1) * (2 * RXY + 1);  // RXY = c.rxy
-    const int nreg = nxy * (czb + 2 * c.rz), span = nxy * (2 * c.rz + 1);
+    const int nreg = kXY * (czb + 2 * c.rz), span = kXY * (2 * c.rz + 1);
     for (int u = 0; u < c.ninv[g]; ++u) {
         const CvDesc &cv = cs.cv[c.inv_cv[g][u]];
         const bool sideA = c.inv_side[g][u] == 0;
@@ -659,7 +654,7 @@ __global__ void __launch_bounds__(kJacBlock, 5) k_cell_jac(CellArgs c, CvSet cs,
                    3.003f * ext * ext};
         double ssum = 0.0;  // this lane's switch sums (A side), over its home atoms
         for (int r0 = 0;; r0 += kColStage) {
-            const int m = stage_column<RXY>(c, w, c.inv_p[g][u], cx, cy, z0, czb, r0, sc, pc.lim,
+            const int m = stage_column(c, w, c.inv_p[g][u], cx, cy, z0, czb, r0, sc, pc.lim,
                                             s_p, s_seg, s_first, s_wsum, &s_odd);
             pc.r0 = r0;
             for (int h0 = a0 + kTile * wave; h0 < a1; h0 += kApp) {  // uniform per wavefront
@@ -673,7 +668,7 @@ __global__ void __launch_bounds__(kJacBlock, 5) k_cell_jac(CellArgs c, CvSet cs,
                 }
                 // partners in the staged window of the first atom's cell to the last's
                 const int kf = __builtin_amdgcn_readlane(kc, 0), kl = __builtin_amdgcn_readlane(kc, 15);
-                const int b0 = max(0, s_seg[nxy * kf] - r0), b1 = min(m, s_seg[nxy * kl + span] - r0);
+                const int b0 = max(0, s_seg[kXY * kf] - r0), b1 = min(m, s_seg[kXY * kl + span] - r0);
                 // home atoms are stored relative to their own cell: the kc-th
                 // cell of the block sits kc cell edges above the block origin
                 const float3 o = make_float3(pi.x * sc, pi.y * sc, (pi.z + (float)(kc * c.clen[2])) * sc);
@@ -804,15 +799,10 @@ hipError_t launch_cell_cv(const CellArgs &c, const CvSet &cs, const PosView &pos
     for (int d = 0; d < cs.ncv; ++d)
         if (cs.cv[d].kind == CV_COORD_CELL) all612 = all612 && cs.cv[d].n == 6 && cs.cv[d].m == 12;
     const dim3 grid(c.nblk, c.G, c.W);
-    if (c.rxy != 1 && c.rxy != 2) return hipErrorInvalidValue;
-    if (all612 && c.rxy == 2)
-        hipLaunchKernelGGL((k_cell_jac<true, 2>), grid, dim3(kJacBlock), 0, s, c, cs, pos);
-    else if (all612)
-        hipLaunchKernelGGL((k_cell_jac<true, 1>), grid, dim3(kJacBlock), 0, s, c, cs, pos);
-    else if (c.rxy == 2)
-        hipLaunchKernelGGL((k_cell_jac<false, 2>), grid, dim3(kJacBlock), 0, s, c, cs, pos);
+    if (all612)
+        hipLaunchKernelGGL(k_cell_jac<true>, grid, dim3(kJacBlock), 0, s, c, cs, pos);
     else
-        hipLaunchKernelGGL((k_cell_jac<false, 1>), grid, dim3(kJacBlock), 0, s, c, cs, pos);
+        hipLaunchKernelGGL(k_cell_jac<false>, grid, dim3(kJacBlock), 0, s, c, cs, pos);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_cn_cell_fin, dim3(c.ncn, c.W), dim3(kBlock), 0, s, c, cs, xi);

@@ -455,18 +455,15 @@ __global__ void __launch_bounds__(256 * KG) k_grid_tiles(GridArgs g, int32_t l0,
     for (int64_t tile = wg; tile < tiles; tile += per) {
         const int64_t r0 = tile / tc * kTileSide, c0 = tile % tc * kTileSide;
         double xr[2][D - 1], xc[2];
-        bool okr[2], okc[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             int64_t r = r0 + fq + 16 * q;
-            okr[q] = r < nr;
 #pragma unroll
             for (int d = D - 2; d >= 0; --d) {
                 xr[q][d] = g.lo[d] + (double)(r % g.n[d]) * g.delta[d];
                 r /= g.n[d];
             }
             const int64_t c = c0 + fq + 16 * q;
-            okc[q] = c < nc;
             xc[q] = g.lo[D - 1] + (double)c * g.delta[D - 1];
         }
         f64x4 acc[1 + D];  // V, G_0 .. G_{D-1}

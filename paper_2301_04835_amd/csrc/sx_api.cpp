@@ -314,15 +314,7 @@ sx_status make_plan(sx_ctx *c)
                 cl.L[k] = c->box[k];
                 cl.inv_L[k] = 1.0 / c->box[k];
             }
-            // sub-cells: a home sub-cell's partners span (2 r + 1) / r cut
-            // lengths per dimension instead of 3
-            cl.rxy = kXYReach;
             cl.rz = kZReach;
-            auto total = [&] { return cl.nc[0] * cl.nc[1] * cl.nc[2] * cl.rxy * cl.rxy * cl.rz; };
-            while (cl.rz > 1 && total() > kCellTotal) cl.rz /= 2;
-            while (cl.rxy > 1 && total() > kCellTotal) cl.rxy /= 2;
-            cl.nc[0] *= cl.rxy;
-            cl.nc[1] *= cl.rxy;
             cl.nc[2] *= cl.rz;
             cl.ncell = cl.nc[0] * cl.nc[1] * cl.nc[2];
             for (int k = 0; k < 3; ++k) {
@@ -351,7 +343,7 @@ sx_status make_plan(sx_ctx *c)
             cl.nzb = std::max(1, (cl.nc[2] + 5 * cl.rz - 1) / (5 * cl.rz));
             if ((cl.nc[2] + cl.nzb - 1) / cl.nzb > kCzMax) return fail(c, SX_EINVAL, "cell column block too tall");
             cl.nblk = cl.nc[0] * cl.nc[1] * cl.nzb;
-            cl.ext = (float)(std::max({(1 + cl.rxy) * cl.clen[0], (1 + cl.rxy) * cl.clen[1],
+            cl.ext = (float)(std::max({2 * cl.clen[0], 2 * cl.clen[1],
                                        ((cl.nc[2] + cl.nzb - 1) / cl.nzb + cl.rz) * cl.clen[2]}));
             cl.jtotal = 0;
             for (int g = 0; g < cl.G; ++g)

@@ -337,24 +337,23 @@ struct MlpStep {
 
 // Cell lists of coordination-number groups (orthorhombic periodic box):
 // cut-length cells (edge >= the cutoff, 3 to 16 per dimension), each cut into
-// rxy sub-cells in x and y and rz = 4, 2 or 1 in z (the largest that keep
-// the total within kCellTotal, rz reduced first), so partners within the cut
-// lie within rxy sub-cells in x and y and rz in z.  rxy = 1: with rxy = 2 a
-// home atom visits 1.44x fewer candidates, but each column block stages
-// 25/9 as many partners per home atom over 25/9 as many sub-cells, and the
-// pair pass of the 512-walker workload took 21.2 ms (column blocks of 40
-// sub-cells) or 25.1 ms (20) instead of 13.0.
+// rz = 4 sub-cells in z, so partners within the cut lie within one cell in x
+// and y and rz sub-cells in z.  Cut in two in x and y as well, a home atom
+// visits 1.44x fewer candidates, but each column block stages 25/9 as many
+// partners per home atom over 25/9 as many sub-cells, and the pair pass of 512
+// walkers took 21.2 ms (column blocks of 40 sub-cells) or 25.1 ms (20) instead
+// of 13.0.
 constexpr int kCellMax = 16;   // cut-length cells per dimension
 constexpr int kCellTotal = 16384;
-constexpr int kXYReach = 1;    // largest rxy
-constexpr int kZReach = 4;     // largest rz
+constexpr int kZReach = 4;     // rz
+static_assert(kCellMax * kCellMax * kCellMax * kZReach <= kCellTotal, "sub-cells fit");
 constexpr int kCzMax = 24;     // home sub-cells (in z) of one column block
 constexpr int kMaxGroups = 8;  // distinct groups of the cell-list CVs
 constexpr int kMaxInv = 8;     // (CV, side) uses of one group
 struct CellArgs {
     int32_t W, G, ncn;                 // walkers, distinct groups, cell-list CVs
     int32_t nc[3], ncell;              // cells per dimension, total
-    int32_t rxy, rz;                   // reach in x and y, and in z, in sub-cells
+    int32_t rz;                        // reach in z, in sub-cells
     double L[3], inv_L[3];             // box edges
     double clen[3], inv_clen[3];       // cell edges
     float ext;                         // largest coordinate of a column block's region from its origin
