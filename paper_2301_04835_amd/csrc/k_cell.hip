@@ -43,7 +43,7 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBuildBlock = 1024;
-constexpr int kBuildWords = 20448;  // LDS words of the build: the cells', then a 16-bit slot per member
+constexpr int kBuildWords = 20448;  // LDS words of the counting build: the cells', then a 16-bit slot per member
 static_assert(kBuildWords >= kCellTotal, "every cell has a word");
 
 // The cell of a coordinate and the position within it (iclen = 1 / clen, its
@@ -62,34 +62,46 @@ __device__ __forceinline__ int cell_of(double x, double L, double iL, double cle
     return c;
 }
 
-// Members take the slots of their cell in any order (an LDS atomic), then
-// each counts the earlier members among its cell's: the place in member order,
-// whatever the slots were.  Taking turns in member order instead (a wavefront
-// ranks its 64 members by shuffles and 16 wavefronts go one after the other)
-// was a chain of 16 barriers per 1,024 members: 96 groups of 20,000 took
-// 135 us, this way 62: 28 up to the slots, 17 the scattered stores of the
-// records, the rest one compute unit's share of the loads and stores.  (A
-// placement kernel over all compute units, slots in memory: 42 and 55.  The
-// records requested ahead of the counts are vectors of the language: as
-// float4 they waited in scratch memory, 71.)
-// SMALL: the slots' members fit in LDS next to the cells' words (80 KB, two
-// workgroups a CU); otherwise they wait where the sorted records go (127 us).
-// Counting costs a cell the square of its members, so where the squares of a
-// group's cells add up to more than crowded() per member (a dense droplet in a
-// large box, whose cells are capped at 16 a side) its members take the turns.
-// Counting and turns, us, of a group in 16,384 cells (slots in memory):
-//   20,000 members, squares of 10 / 18 / 55 / 388   111 135 214 967   129
-//   of 32 walkers                                   147 171 259 1,023 137
-//   60,000, squares of 10 / 19 / 58 / 403           311 379 642 2,755 346
-// in 432 (slots in LDS): 20,000, squares of 186, 178 and 118; 5,000, of 47, 34
-// and 35; in 16,384: 5,000, of 32 / 48 / 145, 41 49 82 and 46; 2,000, of 22 /
-// 50, 28 33 and 29.
-__device__ __forceinline__ float crowded(bool in_lds, int32_t n) { return !in_lds ? 12.f : n > 8192 ? 90.f : 40.f; }
+// Two ways to place members in member order within their cells.
+//
+// Turns: of 1,024 members at a time a wavefront finds each lane's cell mates
+// among its 64 (bit by bit of the cells' numbers, with ballots) and the 16
+// wavefronts go one after the other, each taking its cells' next places: a
+// chain of 16 LDS round trips, with the next members' loads and the last ones'
+// stores in flight beside it.  (With 64 shuffles a rank and barriers that wait
+// for memory too, 20,000 members took 127 us, now 77.)
+//
+// Counting (SMALL: a 16-bit slot per member fits in LDS next to the cells'
+// words, 80 KB, two workgroups a CU): members take the slots of their cell in
+// any order (an LDS atomic), then each counts the earlier members among its
+// cell's: the place in member order, whatever the slots were.  The records
+// requested ahead of the counts are vectors of the language: as float4 they
+// waited in scratch memory (96 groups of 20,000 members 71 us, 62 now).
+//
+// Counting costs a cell the square of its members: the turns serve groups whose
+// cells' squares add up to more than crowded() per member (a dense droplet in a
+// large box, whose cells are capped at 16 a side).  Counting and turns, us:
+//   20,000 members, squares of 4 / 11 / 56 / 186   47 50 95 176   72
+//    8,000, squares of 5 / 23 / 32 / 52            24 30 32 44    34
+//    5,000, squares of 3 / 15 / 20 / 33            21 25 26 32    26
+//    2,000, squares of 2 / 9 / 14 / 20             14 15 17 17    16
+// Slots in memory, where they don't fit, were slower than the turns at any
+// density (20,000 members in 16,384 cells, squares of 5: 99 and 82).
+__device__ __forceinline__ float crowded(int32_t n) { return fminf(35.f, (float)n * (1.f / 256)); }
+
+// A barrier that orders LDS alone: loads and stores of memory stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 template <typename T, bool SMALL>
 __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosView pos)
 {
-    __shared__ int32_t s_off[kBuildWords];  // a cell's count, first slot, end; then (SMALL) the slots' members
+    // a cell's count, first slot, end; then (SMALL) the slots' members
+    __shared__ int32_t s_off[SMALL ? kBuildWords : kCellTotal];
     __shared__ int32_t s_tot[kBuildBlock / 64];
     __shared__ float s_sq[kBuildBlock / 64];
     const int w = blockIdx.x / c.G, g = blockIdx.x % c.G;
@@ -101,8 +113,6 @@ __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosVi
     int32_t *cst = c.cstart + ((int64_t)w * c.G + g) * (c.ncell + 1);
     float4 *srt = c.sorted + (int64_t)w * c.gtotal + c.goff[g];
     float4 *tmp = c.jac + (int64_t)w * c.jtotal + c.joff[g][0];  // records the pair pass writes later
-    int32_t *slot = reinterpret_cast<int32_t *>(srt);
-    uint16_t *s_slot = reinterpret_cast<uint16_t *>(s_off + c.ncell);
     for (int i = tid; i < c.ncell; i += kBuildBlock) s_off[i] = 0;
     __syncthreads();
     // cells, counts and positions in their cells, four members per thread at a
@@ -169,31 +179,43 @@ __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosVi
     }
     if (tid == 0) cst[c.ncell] = n;
     __syncthreads();
-    if (sq > crowded(SMALL, n) * (float)n) {  // uniform
+    if (!SMALL || sq > crowded(n) * (float)n) {  // uniform
+        // a chunk's cells and records are requested ahead of the turns before it
+        int cell = tid < n ? cid[tid] : -1;
+        float4 v = tmp[tid < n ? tid : 0];
         for (int32_t base = 0; base < n; base += kBuildBlock) {
-            const int32_t i = base + tid;
+            const int32_t i = base + tid, in = i + kBuildBlock;
             const bool valid = i < n;
-            const int cell = valid ? cid[i] : -1;
-            const float4 v = tmp[valid ? i : base];  // in flight during the ranking
-            int rank = 0, cnt = 0;
-            for (int k = 0; k < 64; ++k) {
-                const int ck = __shfl(cell, k, 64);
-                cnt += ck == cell ? 1 : 0;
-                rank += (ck == cell && k < lane) ? 1 : 0;
+            const int next_cell = in < n ? cid[in] : -1;
+            const float4 next_v = tmp[in < n ? in : 0];
+            // the lanes of this lane's cell, bit by bit of its number; how many,
+            // and how many of them before it
+            uint64_t same = __ballot(valid);
+#pragma unroll
+            for (int b = 0; (kCellTotal - 1) >> b; ++b) {
+                const bool bit = (cell >> b) & 1;
+                const uint64_t m = __ballot(bit);
+                same &= bit ? m : ~m;
             }
+            const int cnt = __popcll(same), rank = __popcll(same & ((1ull << lane) - 1));
+            int dst = 0;
             for (int t = 0; t < kBuildBlock / 64; ++t) {
-                __syncthreads();
+                lds_barrier();
                 if (wave == t && valid) {
-                    const int dst = s_off[cell] + rank;
-                    srt[dst] = v;
-                    cid[i] = dst;  // from here on: the member's sorted position
-                    if (rank == cnt - 1) s_off[cell] += cnt;  // after every lane of the wavefront read it
+                    dst = s_off[cell] + rank;
+                    if (rank == cnt - 1) s_off[cell] = dst + 1;  // after every lane of the wavefront read it
                 }
             }
-            __syncthreads();
+            if (valid) {
+                srt[dst] = v;
+                cid[i] = dst;  // from here on: the member's sorted position
+            }
+            cell = next_cell;
+            v = next_v;
         }
         return;
     }
+    uint16_t *s_slot = reinterpret_cast<uint16_t *>(s_off + c.ncell);
     for (int32_t b = tid; b < n; b += 4 * kBuildBlock) {
         int32_t cell[4];
 #pragma unroll
@@ -202,63 +224,46 @@ __global__ void __launch_bounds__(kBuildBlock, 8) k_cell_build(CellArgs c, PosVi
         for (int k = 0; k < 4; ++k) {
             const int32_t i = b + k * kBuildBlock;
             if (i >= n) break;
-            const int32_t e = atomicAdd(&s_off[cell[k]], 1);
-            if (SMALL)
-                s_slot[e] = (uint16_t)i;
-            else
-                slot[e] = i;
+            s_slot[atomicAdd(&s_off[cell[k]], 1)] = (uint16_t)i;
         }
     }
     __syncthreads();
-    // four members' counts side by side.  SMALL: in member order, two slots a
-    // word: all of the cell's words, less what its first and last hold of the
-    // neighbour cells; otherwise in slot order, where lanes share cells.
-    // A member that is not there (past the group's end) is the thread's first:
-    // no other thread's, which may be done with it.
+    // four members' counts side by side, two slots a word: all of the cell's
+    // words, less what its first and last hold of the neighbour cells.  A member
+    // that is not there (past the group's end) is the thread's first: no other
+    // thread's, which may be done with it.
     const uint32_t *s_two = reinterpret_cast<const uint32_t *>(s_slot);
     for (int32_t b = tid; b < n; b += 4 * kBuildBlock) {
         int32_t m[4], lo[4], hi[4], dst[4], len = 0;
         f32x4 v[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int32_t e = b + k * kBuildBlock < n ? b + k * kBuildBlock : b;
-            m[k] = SMALL ? e : slot[e];
+            m[k] = b + k * kBuildBlock < n ? b + k * kBuildBlock : b;
             lo[k] = cid[m[k]];
-            if (SMALL) v[k] = *reinterpret_cast<const f32x4 *>(tmp + m[k]);
+            v[k] = *reinterpret_cast<const f32x4 *>(tmp + m[k]);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             hi[k] = s_off[lo[k]];
             dst[k] = lo[k] = lo[k] > 0 ? s_off[lo[k] - 1] : 0;
-            len = max(len, SMALL ? ((hi[k] + 1) >> 1) - (lo[k] >> 1) : hi[k] - lo[k]);
-            if (SMALL) {
-                dst[k] -= (lo[k] & 1) && s_slot[lo[k] - 1] < m[k] ? 1 : 0;
-                dst[k] -= (hi[k] & 1) && s_slot[hi[k]] < m[k] ? 1 : 0;
-            }
+            len = max(len, ((hi[k] + 1) >> 1) - (lo[k] >> 1));
+            dst[k] -= (lo[k] & 1) && s_slot[lo[k] - 1] < m[k] ? 1 : 0;
+            dst[k] -= (hi[k] & 1) && s_slot[hi[k]] < m[k] ? 1 : 0;
         }
         for (int32_t q = 0; q < len; ++q)
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (SMALL) {
-                    const int32_t e = (lo[k] >> 1) + q, last = (hi[k] - 1) >> 1;
-                    const uint32_t two = s_two[min(e, last)] | (e > last ? ~0u : 0u);
-                    dst[k] += ((two & 0xffffu) < (uint32_t)m[k] ? 1 : 0) + ((two >> 16) < (uint32_t)m[k] ? 1 : 0);
-                } else {
-                    const int32_t e = lo[k] + q;
-                    dst[k] += e < hi[k] && slot[min(e, hi[k] - 1)] < m[k] ? 1 : 0;
-                }
+                const int32_t e = (lo[k] >> 1) + q, last = (hi[k] - 1) >> 1;
+                const uint32_t two = s_two[min(e, last)] | (e > last ? ~0u : 0u);
+                dst[k] += ((two & 0xffffu) < (uint32_t)m[k] ? 1 : 0) + ((two >> 16) < (uint32_t)m[k] ? 1 : 0);
             }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             if (b + k * kBuildBlock < n) {
-                if (SMALL) *reinterpret_cast<f32x4 *>(srt + dst[k]) = v[k];
+                *reinterpret_cast<f32x4 *>(srt + dst[k]) = v[k];
                 cid[m[k]] = dst[k];  // from here on: the member's sorted position
             }
         }
-    }
-    if (!SMALL) {
-        __syncthreads();  // the slots lie in srt
-        for (int32_t i = tid; i < n; i += kBuildBlock) srt[cid[i]] = tmp[i];
     }
 }
 

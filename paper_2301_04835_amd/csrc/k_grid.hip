@@ -317,8 +317,8 @@ __global__ void __launch_bounds__(64) k_grid_step_wave(GridArgs g)
 // 100 x 100 x 3 2,753 and 2,464; 30 x 30 x 20 339 and 376).
 //
 // k_grid_fill: a whole list in tiles of 64 x 64, half the factors per node.
-// 100,000 hills onto 512 x 512 nodes, upload included: 3.48 ms; in 32 x 32
-// tiles 4.85, with one exponential and two divisions per (node, hill) and one
+// 100,000 hills onto 512 x 512 nodes, upload included: 3.42 ms; in 32 x 32
+// tiles 4.4, with one exponential and two divisions per (node, hill) and one
 // lane per node 121.  The matrix units' FP64 rate and the factors, which do
 // not overlap, bound it: 2.1 and 0.9 ms.
 //
@@ -942,8 +942,7 @@ hipError_t launch_grid_step(const GridArgs &g0, hipStream_t s)
 // parts, as many as give the fewest rounds per part, at most four
 // rounds.  Records of (1 + D) N sums a slice, joined in order.  30,000
 // hills, upload included: 100 x 100 nodes 1,499 us unsliced in
-// 32 x 32 tiles, 167 now; 400 x 400 1,521 and 900; 24 x 24 x 24 2,427 and 328;
-// 4,000 nodes in one CV 1,553 and 249.
+// 32 x 32 tiles, 147 now; 24 x 24 x 24 2,427 and 249; 512 x 512 1,057 now.
 int32_t grid_slices(int32_t D, const int32_t *n, int64_t N)
 {
     const int64_t tiles = tiles_of(D, n, N, fill_tiles(D, n, N) ? kFillSide : kTileSide);

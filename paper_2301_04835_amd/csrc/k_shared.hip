@@ -33,10 +33,10 @@
 //     query's chunks in chunk order (bitwise deterministic), forms dV/dxi,
 //     and appends one hill per walker for a deposition step, in walker order;
 //     the last of its workgroups to arrive then moves the count.
-// A step of 256 walkers on 100,000 hills: 22.8 us (34.7 with a CV launch, a
+// A step of 256 walkers on 100,000 hills: 22.7 us (34.7 with a CV launch, a
 // count launch, 18 slots per pair and 784 unequal workgroups); 131,072 points
-// on 100,000 hills: 5.79 ms = 2.26 x 10^12 pairs/s, 36 T of the 38 T issue
-// slots/s a loop of multiply-adds reaches (6.24 ms).
+// on 100,000 hills: 5.45 ms = 2.4 x 10^12 pairs/s, the 38 T issue slots/s that
+// a loop of multiply-adds reaches (6.24 ms).
 #include "sx_internal.h"
 #include "dev_cv.h"
 #include "dev_reduce.h"

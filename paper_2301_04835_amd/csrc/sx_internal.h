@@ -427,8 +427,9 @@ bool shared_sums_cvs(const SharedArgs &a);
 hipError_t launch_cell_cv(const CellArgs &c, const CvSet &cs, const PosView &pos, double *xi, hipStream_t s,
                           int which = 3);
 // out += sign * sum_d coef[w][d] dxi_d/dr for the cell-list coordination
-// numbers (pair recompute, one writer per atom); needs the cell lists of the
-// same positions (launch_cell_cv first)
+// numbers, from the gradients that the pair pass stored (one writer per atom);
+// needs the cell lists and the pair pass of the same positions (launch_cell_cv
+// first)
 hipError_t launch_cell_vjp(const CellArgs &c, const CvSet &cs, const PosView &pos, const double *coef, double sign,
                            ForceView out, hipStream_t s);
 int32_t mlp_param_count(int32_t H, int32_t D);

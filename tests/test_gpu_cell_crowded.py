@@ -1,8 +1,9 @@
-"""Cell lists of groups crowded into a few cells, whose build places members in
-turns instead of counting: values and the vector-Jacobian product against the
-FP64 oracle (1e-6 relative, 1e-5 inf-norm, the bars of the cell path), bitwise
-the same again, at group sizes around the build's chunks (1,024 members), the
-size where the rule changes (8,192) and where the slots no longer fit LDS."""
+"""The two ways in which the cell build places members, in turns (groups
+crowded into a few cells, or whose slots do not fit LDS) and by counting:
+values and the vector-Jacobian product against the FP64 oracle (1e-6 relative,
+1e-5 inf-norm, the bars of the cell path), bitwise the same again, at group
+sizes around the build's chunks (1,024 members) and the largest whose slots fit
+(8,128 members beside 16,384 cells)."""
 import numpy as np
 import pytest
 import torch
@@ -27,7 +28,19 @@ def test_crowded_groups(gpu, na, L, dtype):
     some = np.flatnonzero(g.random(n) < 0.75)
     pos[some] = g.normal(scale=0.1, size=(len(some), 3))
     pos[na:na + 20] = g.normal(scale=0.4, size=(20, 3))
-    pos = pos.astype(dtype)
+    check(pos.astype(dtype), na, nb, L3, gpu)
+
+
+@pytest.mark.parametrize("na,L", [(1024, 19.3), (4097, 9.0), (8128, 19.3), (8129, 19.3), (20000, 10.0)])
+def test_even_groups(gpu, na, L):
+    """The group all over the box: counted where the slots fit."""
+    g = np.random.default_rng(na)
+    pos = g.uniform(0.0, L, size=(na + 30, 3)).astype(np.float32)
+    check(pos, na, 30, np.full(3, L), gpu)
+
+
+def check(pos, na, nb, L3, gpu):
+    n = na + nb
     cvs = pair_cvs(na, nb, (6, 12))[:1]
     s = cell_ctx(cvs, L3, n)
     assert s.cell_list_cvs() == 1
